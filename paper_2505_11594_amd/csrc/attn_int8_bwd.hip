@@ -29,7 +29,12 @@
 // Each workgroup stages the operands its four waves share -- a query block
 // (Q^, dO, L, D and a transposed Q^ or dO^) for dV and dK, a KV block (K^, V,
 // K^T) for dQ -- in LDS in MFMA-operand order with global loads that write
-// LDS, one block ahead of the block being computed.
+// LDS, one block ahead of the block being computed.  Nothing inside a block
+// waits for those loads: each kernel keeps one LDS array (see sage_common.h),
+// its inner barriers order LDS only, dK stores a block's dS^ state after the
+// next block's first barrier, and dQ reads the row sums a block ahead.  With the
+// waits that each of these brought, one forward and backward of B1 H32 N8192
+// D128 took 5836 us, without them 5224 us; B2 H12 N1000 D64 causal 148 -> 138 us.
 #include "sage_common.h"
 
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -155,6 +160,12 @@ __device__ __forceinline__ void bw_wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
 
+// Workgroup barrier that orders ordinary LDS accesses only: loads in flight,
+// direct-to-LDS ones included, stay in flight (__syncthreads and the workgroup
+// fences also wait for every one of them, so the next block's prefetch would be
+// waited for at the barriers inside a block).
+__device__ __forceinline__ void bw_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // The dV and dK kernels: a workgroup owns 128 keys (4 waves x 32) of one
 // (b,h) and walks the query blocks; S = Q^ K^T puts a key in each lane's
 // column and 16 queries in its rows.  LDS holds the query block's operands in
@@ -222,8 +233,8 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     float c2) {
   using T = BwDvLds<D>;
   constexpr int NKS = T::NKS, NDB = T::NDB, NU = BW_Q / 32;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
-  __shared__ float red[2][4];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * T::BYTES + 2 * 4 * 4];
+  float* const red = reinterpret_cast<float*>(lds + 2 * T::BYTES);   // [2][4] wave maxima
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, hi = lane >> 5;
@@ -243,7 +254,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
 
   auto issue = [&](int i, int buf) {
     const int q0 = i * BW_Q;
-    uint8_t* L = lds[buf];
+    uint8_t* L = lds + buf * T::BYTES;
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k;
@@ -260,7 +271,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     bw_wait_all();                                 // this wave's loads of block i have landed
     __syncthreads();                               // everyone's; every wave is done with block i - 1
     if (i + 1 < nqb) issue(i + 1, a ^ 1);
-    const uint8_t* L = lds[a];
+    const uint8_t* L = lds + a * T::BYTES;
     const float sQ = qs[(size_t)bh * nqb + i];
     const float ct = __builtin_fmaxf(sQ * sK * c2, 1.17549435e-38f);   // see the forward kernel
     const bool need_mask = (q0 + BW_Q > N) || (kb + BW_K > N) || (CAUSAL && q0 < kb + BW_K - 1);
@@ -290,9 +301,9 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
       }
     }
     am = wave_max(am);
-    if (lane == 0) red[a][wave] = am;
-    __syncthreads();
-    am = __builtin_fmaxf(__builtin_fmaxf(red[a][0], red[a][1]), __builtin_fmaxf(red[a][2], red[a][3]));
+    if (lane == 0) red[4 * a + wave] = am;
+    bw_lds_barrier();
+    am = __builtin_fmaxf(__builtin_fmaxf(red[4 * a], red[4 * a + 1]), __builtin_fmaxf(red[4 * a + 2], red[4 * a + 3]));
     const float pm = __builtin_amdgcn_exp2f(am);   // max P of the block (0 when it is fully masked)
     const float sP = pm / 127.0f, rP = pm > 0.0f ? 1.0f / sP : 0.0f;
 
@@ -374,12 +385,14 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     int nqb, int bh0, float c2, float rsd) {
   using T = BwDkLds<D>;
   constexpr int NKS = T::NKS, NKS16 = T::NKS16, NDB = T::NDB, NU = BW_Q / 32, NH = NDB / 2;
-  __shared__ __attribute__((aligned(16))) uint8_t ldsA[2][T::A_BYTES];
-  __shared__ __attribute__((aligned(16))) uint8_t ldsT[T::T_BYTES];
-  __shared__ __attribute__((aligned(16))) uint8_t cx[4 * NU * 1024];   // dS^ codes: (key group, subtile) blocks
-  __shared__ __attribute__((aligned(16))) uint8_t dsl[STORE_DS ? 16 * 1024 : 16];
-  __shared__ float red2[STORE_DS ? 4 * BW_Q : 1];
-  __shared__ float red[2][BW_DK_WAVES];
+  constexpr int T_OFF = 2 * T::A_BYTES, CX_OFF = T_OFF + T::T_BYTES, DSL_OFF = CX_OFF + 4 * NU * 1024;
+  constexpr int RED2_OFF = DSL_OFF + (STORE_DS ? 16 * 1024 : 0), RED_OFF = RED2_OFF + (STORE_DS ? 4 * BW_Q * 4 : 0);
+  __shared__ __attribute__((aligned(16))) uint8_t lds[RED_OFF + 2 * BW_DK_WAVES * 4];
+  uint8_t* const ldsT = lds + T_OFF;
+  uint8_t* const cx = lds + CX_OFF;                 // dS^ codes: (key group, subtile) blocks
+  uint8_t* const dsl = lds + DSL_OFF;
+  float* const red2 = reinterpret_cast<float*>(lds + RED2_OFF);
+  float* const red = reinterpret_cast<float*>(lds + RED_OFF);   // [2][BW_DK_WAVES] wave maxima
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave & 3, qh = wave >> 2;          // key group; query half (subtiles 2qh, 2qh + 1); channel half
@@ -407,7 +420,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
 
   auto issue_A = [&](int i, int buf) {
     const int q0 = i * BW_Q;
-    uint8_t* L = ldsA[buf];
+    uint8_t* L = lds + buf * T::A_BYTES;
 #pragma unroll
     for (int k = 0; k < T::AJ; ++k) {
       const int b = wave + BW_DK_WAVES * k;
@@ -428,17 +441,29 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     }
   };
 
+  // the dS^ state of one block, from registers (see the end of the loop)
+  v4i dsv[16 / BW_DK_WAVES];
+  float rsv = 0.0f, sdsv = 0.0f;
+  auto store_ds = [&](int i) {
+    const size_t pair = ((size_t)lbh * nqb + i) * nkb + kblk;
+#pragma unroll
+    for (int b2 = 0; b2 < 16 / BW_DK_WAVES; ++b2)
+      *reinterpret_cast<v4i*>(dsc + (pair * 16 + wave * (16 / BW_DK_WAVES) + b2) * 1024 + lane * 16) = dsv[b2];
+    if (tid < BW_Q) drs[((size_t)lbh * nkb + kblk) * Np + i * BW_Q + tid] = rsv;
+    if (tid == 0) dss[pair] = sdsv;
+  };
   const int i0 = CAUSAL ? kb / BW_Q : 0;
-  if (wave == 0) bw_load_ld(lb, drow, ldsA[i0 & 1] + T::LD_OFF, bh, Np, i0 * BW_Q, lane);
+  if (wave == 0) bw_load_ld(lb, drow, lds + (i0 & 1) * T::A_BYTES + T::LD_OFF, bh, Np, i0 * BW_Q, lane);
   issue_A(i0, i0 & 1);
   for (int i = i0; i < nqb; ++i) {
     const int q0 = i * BW_Q, a = i & 1;
     bw_wait_all();                                 // this wave's loads of block i have landed
     __syncthreads();                               // everyone's; every wave is done with block i - 1
-    if (i + 1 < nqb && wave == 0) bw_load_ld(lb, drow, ldsA[a ^ 1] + T::LD_OFF, bh, Np, q0 + BW_Q, lane);
+    if (STORE_DS && i > i0) store_ds(i - 1);
+    if (i + 1 < nqb && wave == 0) bw_load_ld(lb, drow, lds + (a ^ 1) * T::A_BYTES + T::LD_OFF, bh, Np, q0 + BW_Q, lane);
     issue_T(i);
     if (i + 1 < nqb) issue_A(i + 1, a ^ 1);
-    const uint8_t* L = ldsA[a];
+    const uint8_t* L = lds + a * T::A_BYTES;
     const float sQ = qs[(size_t)bh * nqb + i];
     const float ct = __builtin_fmaxf(sQ * sK * c2, 1.17549435e-38f);   // see the forward kernel
     const bool need_mask = (q0 + BW_Q > N) || (kb + BW_K > N) || (CAUSAL && q0 < kb + BW_K - 1);
@@ -482,14 +507,14 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     if (need_mask) phase1(ic<1>{});
     else phase1(ic<0>{});
     dm = wave_max(dm);
-    if (lane == 0) red[a][wave] = dm;
+    if (lane == 0) red[a * BW_DK_WAVES + wave] = dm;
     // the T loads of this block were issued before the next block's A loads
     if (i + 1 < nqb) bw_wait_vm<T::AJ>();
     else bw_wait_all();
-    __syncthreads();
+    bw_lds_barrier();
     dm = 0.0f;
 #pragma unroll
-    for (int w = 0; w < BW_DK_WAVES; ++w) dm = __builtin_fmaxf(dm, red[a][w]);
+    for (int w = 0; w < BW_DK_WAVES; ++w) dm = __builtin_fmaxf(dm, red[a * BW_DK_WAVES + w]);
     const float sdS = dm / 127.0f, rdS = dm > 0.0f ? 1.0f / sdS : 0.0f;
 
 #pragma unroll
@@ -525,7 +550,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
         }
       }
     }
-    __syncthreads();                               // every wave's codes (and, storing dS^, its staging) are in LDS
+    bw_lds_barrier();                              // every wave's codes (and, storing dS^, its staging) are in LDS
     v4i cs[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) cs[u] = *reinterpret_cast<const v4i*>(cx + (kg * NU + u) * 1024 + lane * 16);
@@ -541,21 +566,17 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
 #pragma unroll
       for (int e = 0; e < 16; ++e) dka[h][e] = __builtin_fmaf((float)dki[e], fk, dka[h][e]);
     }
+    // the block's staged codes and row sums; they are stored after the next
+    // block's first barrier, so the wait in front of it does not wait for them
     if constexpr (STORE_DS) {
-      const size_t pair = ((size_t)lbh * nqb + i) * nkb + kblk;
 #pragma unroll
-      for (int b2 = 0; b2 < 16 / BW_DK_WAVES; ++b2) {
-        const int b = wave * (16 / BW_DK_WAVES) + b2;
-        *reinterpret_cast<v4i*>(dsc + (pair * 16 + b) * 1024 + lane * 16) =
-            *reinterpret_cast<const v4i*>(dsl + b * 1024 + lane * 16);
-      }
-      if (tid < BW_Q) {
-        const float x = (red2[tid] + red2[BW_Q + tid]) + (red2[2 * BW_Q + tid] + red2[3 * BW_Q + tid]);
-        drs[((size_t)lbh * nkb + kblk) * Np + q0 + tid] = x;
-      }
-      if (tid == 0) dss[pair] = sdS;
+      for (int b2 = 0; b2 < 16 / BW_DK_WAVES; ++b2)
+        dsv[b2] = *reinterpret_cast<const v4i*>(dsl + (wave * (16 / BW_DK_WAVES) + b2) * 1024 + lane * 16);
+      if (tid < BW_Q) rsv = (red2[tid] + red2[BW_Q + tid]) + (red2[2 * BW_Q + tid] + red2[3 * BW_Q + tid]);
+      sdsv = sdS;
     }
   }
+  if (STORE_DS && i0 < nqb) store_ds(nqb - 1);
 
   // dK^T: lane holds key kb + 32 kg + col and channels 32db + 8g + 4hi + r
   if (key < N) {
@@ -594,9 +615,9 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     const float* __restrict__ kmean, float* __restrict__ dq, int N, int Np, int nqb, float c2, float rsd) {
   using T = BwQLds<D>;
   constexpr int NKS = T::NKS, NKS16 = T::NKS16, NDB = T::NDB, NT = T::NT;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
-  __shared__ __attribute__((aligned(16))) float kms[D];
-  __shared__ float red[2][4];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * T::BYTES + D * 4 + 2 * 4 * 4];
+  float* const kms = reinterpret_cast<float*>(lds + 2 * T::BYTES);
+  float* const red = kms + D;                       // [2][4] wave maxima
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, hi = lane >> 5;
@@ -623,7 +644,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
   // >= N read row N - 1 (those keys are masked)
   auto issue = [&](int j, int buf) {
     const int kb = j * BW_K;
-    uint8_t* L = lds[buf];
+    uint8_t* L = lds + buf * T::BYTES;
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k;
@@ -649,7 +670,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     bw_wait_all();
     __syncthreads();                               // block j has landed; every wave is done with block j - 1
     if (j + 1 < nkb) issue(j + 1, buf ^ 1);
-    const uint8_t* L = lds[buf];
+    const uint8_t* L = lds + buf * T::BYTES;
     const float sK = ks[(size_t)bh * (Np / BW_K) + j];
     const float ct = __builtin_fmaxf(sQ * sK * c2, 1.17549435e-38f);
     const bool need_mask = (q0 + BW_Q > N) || (kb + BW_K > N) || (CAUSAL && kb + BW_K - 1 > q0);
@@ -702,9 +723,10 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     if (need_mask) phase1(ic<1>{});
     else phase1(ic<0>{});
     dm = wave_max(dm);
-    if (lane == 0) red[buf][wave] = dm;
-    __syncthreads();
-    dm = __builtin_fmaxf(__builtin_fmaxf(red[buf][0], red[buf][1]), __builtin_fmaxf(red[buf][2], red[buf][3]));
+    if (lane == 0) red[4 * buf + wave] = dm;
+    bw_lds_barrier();
+    dm = __builtin_fmaxf(__builtin_fmaxf(red[4 * buf], red[4 * buf + 1]),
+                         __builtin_fmaxf(red[4 * buf + 2], red[4 * buf + 3]));
     const float sdS = dm / 127.0f, rdS = dm > 0.0f ? 1.0f / sdS : 0.0f;
     // codes of the block, then per channel block the product over its four
     // subtiles (exact int32), folded into fp32 once per block
@@ -770,8 +792,8 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
     float* __restrict__ dq, int N, int Np, int nqb, int bh0, float rsd) {
   using T = BwQdsLds<D>;
   constexpr int NDB = T::NDB, NT = T::NT;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
-  __shared__ __attribute__((aligned(16))) float kms[D];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * T::BYTES + D * 4];
+  float* const kms = reinterpret_cast<float*>(lds + 2 * T::BYTES);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, hi = lane >> 5;
@@ -785,15 +807,17 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
 
   auto issue = [&](int j, int buf) {
     const int kb = j * BW_K;
-    uint8_t* L = lds[buf];
+    uint8_t* L = lds + buf * T::BYTES;
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k, db = b / NT, t = b % NT;
       bw_lds_load16(kt + ((size_t)bh * D + 32 * db + col) * Np + kb + 32 * t + 16 * hi, L + b * 1024);
     }
   };
-  // this wave's dS^ operand blocks (query group `wave`, key subtiles 0..NT-1) of pair (i, j)
-  auto load_ds = [&](int j, v4i (&d)[NT]) {
+  // this wave's dS^ operand blocks (query group `wave`, key subtiles 0..NT-1) of pair (i, j), and
+  // rowsum(dS) of this lane's query
+  auto load_ds = [&](int j, v4i (&d)[NT], float& r) {
+    r = drs[((size_t)lbh * nkbt + j) * Np + qi];
     const int8_t* p = dsc + ((((size_t)lbh * nqb + i) * nkbt + j) * (size_t)((BW_Q / 32) * NT) + wave * NT) * 1024 +
                       lane * 16;
 #pragma unroll
@@ -803,21 +827,22 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
   int nkb = nkbt;
   if (CAUSAL) nkb = min(nkb, min(q0 + BW_Q - 1, N - 1) / BW_K + 1);
   v4i dcur[NT], dnext[NT];
+  float rcur = 0.0f, rnext = 0.0f;
   issue(0, 0);
-  load_ds(0, dcur);
+  load_ds(0, dcur, rcur);
   for (int j = 0; j < nkb; ++j) {
     const int buf = j & 1;
     bw_wait_all();
     __syncthreads();                               // block j has landed; every wave is done with block j - 1
     if (j + 1 < nkb) {
       issue(j + 1, buf ^ 1);
-      load_ds(j + 1, dnext);
+      load_ds(j + 1, dnext, rnext);
     }
-    const uint8_t* L = lds[buf];
+    const uint8_t* L = lds + buf * T::BYTES;
     const float sK = ks[(size_t)bh * nkbt + j];
     const float sdS = dss[((size_t)lbh * nqb + i) * nkbt + j];
     const float fq = (sdS * sK) * rsd;
-    const float rr = drs[((size_t)lbh * nkbt + j) * Np + qi] * rsd;   // rowsum(dS) of this lane's query, / sqrt(D)
+    const float rr = rcur * rsd;
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
       v16i dqi = v16i{};
@@ -839,6 +864,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
     }
 #pragma unroll
     for (int t = 0; t < NT; ++t) dcur[t] = dnext[t];
+    rcur = rnext;
   }
   if (qi < N) {
 #pragma unroll

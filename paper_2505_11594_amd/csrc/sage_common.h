@@ -6,10 +6,20 @@
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+// LDS in kernels that prefetch with direct-to-LDS loads.  In front of an LDS
+// read that carries alias information -- a kernel with several __shared__
+// variables, or a read through HIP's struct vector types (uint2, float4) -- the
+// compiler waits for every direct-to-LDS load in flight (s_waitcnt vmcnt(0)),
+// the next tile's included, so a prefetch issued at the top of a tile was
+// waited for right there.  The attention kernels therefore keep one __shared__
+// array each and read it through scalars and ext_vector types only; their own
+// waits (vmcnt before the barrier of each tile) order the loads.
 
 namespace sage {
 
