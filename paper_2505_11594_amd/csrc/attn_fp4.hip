@@ -1,8 +1,9 @@
 // Microscaled-FP4 attention forward for gfx950 (SageAttention3, Algorithm 1
 // without smoothing Q; two-level quantization of P~, Sec. 3.2).
 //
-// Work decomposition: one workgroup = 4 waves = 128 queries of one (b,h);
-// each wave owns 32 queries and walks all KV tiles (BKV = 64 or 128 keys).
+// Work decomposition: one workgroup = 4 waves = 128 queries of one (b,h) (8
+// waves and 256 queries with SAGE_WG256); each wave owns 32 queries and walks
+// all KV tiles (BKV = 64, 128 or 256 keys).
 // Both products run on v_mfma_scale_f32_32x32x64_f8f6f4 with FP4 (E2M1)
 // operands and E8M0 block scales:
 //   S^T (keys x queries) = K^ . Q^T    A = K^ tile (LDS), B = Q^ (registers)
@@ -27,43 +28,30 @@
 // Data movement: KV tiles go from HBM straight into LDS with global loads
 // that write LDS (no staging registers).  LDS holds each tile in MFMA-operand
 // order -- one 1 KiB block per 64-lane operand read, lane l's 16 bytes at
-// 16 l -- so operand reads are linear and bank-conflict free.  Three LDS
-// stages and one barrier per tile: after the barrier of tile j every wave
-// has finished tile j-1, the loads of tile j+2 go to that stage, and the
-// S^T products of tile j+1 are issued between the row max of tile j and its
-// exponentials, so the MFMAs run under tile j's softmax.
+// 16 l -- so operand reads are linear and bank-conflict free.  Two LDS stages
+// and one barrier per tile: after the barrier of tile j every wave has finished
+// tile j - 1, and the loads of tile j + 1 go to that stage while tile j runs.
+//
+// What bounds it is instruction issue (exponentials, packs and plain VALU work
+// nearly in series with the MFMAs), so the tile's S is computed at its top and
+// the registers go to waves instead of a second S: 64- and 128-key tiles run
+// three waves per SIMD (four at D = 64 with 64 keys), 256-key tiles, whose S
+// takes 128 registers, two.  Against two waves per SIMD with the next tile's S
+// computed ahead and three LDS stages, a call on B2 H32 N4096 D128 took 344
+// instead of 373 us with 128-key tiles and 387 instead of 408 with 64-key tiles,
+// B1 H24 N19200 D64 1766 instead of 1801 us.
 #include "sage_common.h"
 
 namespace sage {
 
-constexpr int AQ = 128;   // queries per workgroup (4 waves x 32)
-
-// HBM -> LDS loads (global_load_lds): lane l's bytes land at dst + l * size.
-__device__ __forceinline__ void lds_load16(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-__device__ __forceinline__ void lds_load4(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
-}
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
-// A raw buffer resource over `bytes` bytes at `base` (reads past the end return
-// zero), and direct-to-LDS buffer loads from it: lane l's bytes land at
-// dst + size * l; the byte address is base + voff (per lane) + soff (uniform).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
-}
-__device__ __forceinline__ void buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff,
-                                           (uint32_t)__builtin_amdgcn_readfirstlane((int)soff), 0, 0);
-}
-__device__ __forceinline__ void buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 4, voff,
-                                           (uint32_t)__builtin_amdgcn_readfirstlane((int)soff), 0, 0);
-}
+__device__ __forceinline__ v8i as_op(const v4i x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; }
 
 // One LDS stage of a KV tile, in MFMA-operand order (plus, with smoothing Q,
-// the tile's BKV entries of the query block's GEMV bias).
+// the tile's BKV entries of the query block's GEMV bias).  Np is a multiple of
+// 128: when the last 256-key tile reaches past Np its upper 128 keys are loaded
+// from its lower half (finite values, masked as keys >= N).
 template <int D, int BKV, bool SQ>
 struct Fp4Stage {
   static constexpr int NSUB = BKV / 32;        // 32-key subtiles (S^T rows)
@@ -74,347 +62,23 @@ struct Fp4Stage {
   static constexpr int NVB = NDB * NG;         // V^T operand blocks, 1 KiB each
   static constexpr int KC_OFF = 0;
   static constexpr int VC_OFF = KC_OFF + NKB * 1024;
-  static constexpr int KS_OFF = VC_OFF + NVB * 1024;   // K^ scales: BKV rows x D/32 bytes, as in HBM
-  static constexpr int KS_BYTES = BKV * (D / 32);
-  static constexpr int VS_OFF = KS_OFF + KS_BYTES;      // V^T scales: one dword per dim row
-  static constexpr int BIAS_OFF = VS_OFF + D * 4;       // smoothing Q: fp32 bias of the tile's keys
-  static constexpr int BYTES = BIAS_OFF + (SQ ? BKV * 4 : 0);
-  static constexpr int NKSJ = (KS_BYTES / 4 + 63) / 64;   // dword loads of K^ scales (64 lanes each)
-  static constexpr int NVSJ = D / 64;                     // dword loads of V^T scales
-};
-
-__device__ __forceinline__ v8i as_op(const v4i x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; }
-
-// OUT: 0 = fp32, 1 = bf16, 2 = fp16.  SQ: smoothing Q -- S += qkb[bh, query
-// block, key] (Algorithm 1's GEMV of the block mean with K', one row of Np
-// floats per 128-query block, which is this workgroup's query tile).
-template <int D, int BKV, bool CAUSAL, int OUT, bool SQ>
-__global__ __launch_bounds__(256, 2) void attn_fp4_mx_kernel(
-    const uint8_t* __restrict__ qc, const uint8_t* __restrict__ qs, const uint8_t* __restrict__ kc,
-    const uint8_t* __restrict__ ks, const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs,
-    const float* __restrict__ qkb, void* __restrict__ o, int BH, int N, int Np, int nqt, float c2, float log6) {
-  using T = Fp4Stage<D, BKV, SQ>;
-  constexpr int NSUB = T::NSUB, NKS = T::NKS, NDB = T::NDB, NG = T::NG;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[3][T::BYTES];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: scalar branches
-  const int col = lane & 31, hi = lane >> 5;
-
-  // XCD-aware order: consecutive workgroups go round-robin over the 8 XCDs,
-  // so give each XCD a contiguous range of (b,h, q-tile) work to keep one
-  // head's K^/V^ in that XCD's L2.
-  const int total = nqt * BH;
-  int lin = blockIdx.x;
-  if ((total & 7) == 0) lin = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
-  const long long bh = lin / nqt;
-  int qt = lin % nqt;
-  if (CAUSAL) qt = nqt - 1 - qt;            // longest rows first
-  const int q0 = qt * AQ;
-  const int qw = q0 + wave * 32;
-  const int qi = qw + col;
-
-  // Q^ fragment (B operand of S^T = K^ Q^T): 32 codes of block (2s + hi) per K-step s
-  v4i qreg[NKS];
-  uint32_t qsc = 0;
-  if (qi < N) {
-    const uint8_t* qrow = qc + ((size_t)bh * N + qi) * (D / 2);
-#pragma unroll
-    for (int s = 0; s < NKS; ++s) qreg[s] = *reinterpret_cast<const v4i*>(qrow + (2 * s + hi) * 16);
-    const uint8_t* srow = qs + ((size_t)bh * N + qi) * (D / 32);
-    qsc = (D == 128) ? *reinterpret_cast<const uint32_t*>(srow) : (uint32_t)*reinterpret_cast<const uint16_t*>(srow);
-  } else {
-#pragma unroll
-    for (int s = 0; s < NKS; ++s) qreg[s] = v4i{0, 0, 0, 0};
-  }
-  qsc >>= 8 * hi;   // byte 2s = scale of block 2s + hi
-
-  int ntiles = (N + BKV - 1) / BKV;
-  if (CAUSAL) {
-    const int qlast = min(q0 + AQ - 1, N - 1);
-    ntiles = min(ntiles, qlast / BKV + 1);
-  }
-
-  // ---- tile loads: HBM -> LDS without registers ---------------------------
-  // Wave w loads K^ operand blocks w, w + 4, ... (block b = (t, s) = (b / NKS,
-  // b % NKS): key row 32t + col, bytes [32s + 16hi, +16)), V^T operand blocks
-  // w, w + 4, ... (b = (db, g) = (b / NG, b % NG): dim row 32db + col, bytes
-  // [32g + 16hi, +16) of the tile) and scale job w: K^ scale dwords c = w for
-  // w < NKSJ (64 per job), then V^T scale dwords (one per dim row).  Each
-  // load is a wave-uniform tile base plus a fixed 32-bit lane offset.  (The
-  // buffer-resource form of the 256-key kernel made this kernel 4% slower at
-  // D = 64, so it keeps global loads.)
-  constexpr int KJ = (T::NKB + 3) / 4, VJ = (T::NVB + 3) / 4;
-  static_assert(T::NKSJ + T::NVSJ <= 4, "one scale job per wave");
-  const uint8_t* kbase = kc + (size_t)bh * Np * (D / 2);
-  const uint8_t* vbase = vc + (size_t)bh * D * (Np / 2);
-  const uint8_t* ksbase = ks + (size_t)bh * Np * (D / 32);
-  const uint8_t* vsbase = vs + (size_t)bh * D * (Np / 32);
-  uint32_t ko[KJ], vo[VJ], so;
-#pragma unroll
-  for (int i = 0; i < KJ; ++i) {
-    const int b = wave + 4 * i, t = b / NKS, s = b % NKS;
-    ko[i] = (32 * t + col) * (D / 2) + 32 * s + 16 * hi;
-  }
-#pragma unroll
-  for (int i = 0; i < VJ; ++i) {
-    const int b = wave + 4 * i, db = b / NG, g = b % NG;
-    vo[i] = (32 * db + col) * (Np / 2) + 32 * g + 16 * hi;
-  }
-  const bool ks_job = wave < T::NKSJ, vs_job = !ks_job && wave < T::NKSJ + T::NVSJ;
-  const bool ks_lane = 64 * (wave + 1) <= T::KS_BYTES / 4 || 64 * wave + lane < T::KS_BYTES / 4;
-  so = ks_job ? (64 * wave + lane) * 4 : (64 * (wave - T::NKSJ) + lane) * (Np / 32);
-  const float* brow = SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr;   // this query block's bias row
-  auto issue = [&](int j, int stage) {
-    const int kb = j * BKV;
-    uint8_t* L = lds[stage];
-    // a head's base in SGPRs plus a 32-bit lane offset that carries the tile
-    // offset (one 32-bit add per load, no 64-bit address arithmetic)
-    const uint32_t kto = (uint32_t)kb * (D / 2), vto = (uint32_t)kb / 2;
-#pragma unroll
-    for (int i = 0; i < KJ; ++i)
-      if (T::NKB % 4 == 0 || wave + 4 * i < T::NKB)
-        lds_load16(kbase + (ko[i] + kto), L + T::KC_OFF + (wave + 4 * i) * 1024);
-#pragma unroll
-    for (int i = 0; i < VJ; ++i)
-      if (T::NVB % 4 == 0 || wave + 4 * i < T::NVB)
-        lds_load16(vbase + (vo[i] + vto), L + T::VC_OFF + (wave + 4 * i) * 1024);
-    if (ks_job) {
-      if (ks_lane)
-        lds_load4(ksbase + (size_t)kb * (D / 32) + so, L + T::KS_OFF + wave * 256);
-    } else if (vs_job) {
-      // the aligned dword holding the tile's BKV/32 scale bytes of dim row 64c + lane
-      lds_load4(vsbase + ((kb / 32) & ~3) + so, L + T::VS_OFF + (wave - T::NKSJ) * 256);
-    }
-    if constexpr (SQ) {
-      if (wave == 0 && lane < BKV / 4) lds_load16(brow + kb + 4 * lane, L + T::BIAS_OFF);
-    }
-  };
-
-  v16f oacc[NDB];
-#pragma unroll
-  for (int db = 0; db < NDB; ++db) oacc[db] = v16f{};
-  float m = -INFINITY, mc_old = -INFINITY, f_old = 0.0f, lsum_acc = 0.0f;
-
-  // S^T = K^ . Q^T for one tile (LDS stage base L)
-  auto qk = [&](const uint8_t* L, v16f (&sacc)[NSUB]) {
-#pragma unroll
-    for (int t = 0; t < NSUB; ++t) {
-      uint32_t ksc;
-      if constexpr (D == 128) ksc = *reinterpret_cast<const uint32_t*>(L + T::KS_OFF + (32 * t + col) * 4) >> (8 * hi);
-      else ksc = L[T::KS_OFF + (32 * t + col) * 2 + hi];
-      v16f acc = v16f{};
-      static_for<NKS>([&](auto S_) {
-        constexpr int s = decltype(S_)::value;
-        const v4i a = *reinterpret_cast<const v4i*>(L + T::KC_OFF + (t * NKS + s) * 1024 + lane * 16);
-        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(qreg[s]), acc, 4, 4, 2 * s, (int)ksc,
-                                                              2 * s, (int)qsc);
-      });
-      sacc[t] = acc;
-    }
-  };
-
-  issue(0, 0);
-  if (ntiles > 1) issue(1, 1);
-  wait_loads();
-  __syncthreads();
-  v16f sbuf[2][NSUB];
-  if (!CAUSAL || 0 <= qw + 31) qk(lds[0], sbuf[0]);
-
-  auto tile = [&](auto P_, int j, int stage) {
-    constexpr int P = decltype(P_)::value;     // sbuf[P] holds this tile's S^T, sbuf[P ^ 1] gets the next
-    v16f (&sacc)[NSUB] = sbuf[P];
-    const uint8_t* L = lds[stage];
-    const int kb = j * BKV;
-    const bool active = !CAUSAL || kb <= qw + 31;
-    float t = 0.f, m_new = 0.f, mc = 0.f, f = 0.f, gam = 1.f, bias = 0.f;
-    int kfold = 0;
-    float bm[NG];
-    float ps[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // independent partial row sums
-    // V^T scale bytes of the tile for this lane's rows: byte 2g = block 2g + hi
-    const int vshift = 8 * (((kb / 32) & 3) + hi);
-
-    if (active) {
-      if constexpr (SQ) {
-        // smoothing Q: S = fl32(S + bias); element (u, v) is key kb + 64 (u >> 1) + 32 hi + 16 (u & 1) + v
-#pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-          const float* bp = reinterpret_cast<const float*>(L + T::BIAS_OFF) + 64 * (u >> 1) + 32 * hi + 16 * (u & 1);
-#pragma unroll
-          for (int w4 = 0; w4 < 4; ++w4) {
-            const v4f b = *reinterpret_cast<const v4f*>(bp + 4 * w4);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sacc[u][4 * w4 + r] = sacc[u][4 * w4 + r] + b[r];
-          }
-        }
-      }
-      // ---- masking (tail keys >= N; causal keys > query) ---------------
-      const bool need_mask = (kb + BKV > N) || (CAUSAL && kb + BKV - 1 > qw);
-      if (need_mask) {
-        // element (u, v) is key kb + 32 hi + c with c = 64 (u >> 1) + 16 (u & 1) + v;
-        // it is kept iff c < rem.  The sign bit of c - rem turns -inf into the
-        // bound +inf for kept keys, and min(S, bound) applies it -- plain bit
-        // arithmetic, so no per-element lane masks are formed.
-        const int rem = (CAUSAL ? min(N, qi + 1) : N) - kb - 32 * hi;
-#pragma unroll
-        for (int u = 0; u < NSUB; ++u)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int c = 64 * (u >> 1) + 16 * (u & 1) + v;
-            const float bound = __uint_as_float(0xFF800000u ^ ((uint32_t)(c - rem) & 0x80000000u));
-            sacc[u][v] = smin(sacc[u][v], bound);
-          }
-      }
-      // ---- tile row max (raw scores); block max is lane-local ----------
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        // a serial chain: the compiler fuses it into v_maximum3
-        float x = sacc[2 * g][0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) x = smax(x, sacc[2 * g][v]);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) x = smax(x, sacc[2 * g + 1][v]);
-        bm[g] = x;
-      }
-      float tl = bm[0];
-#pragma unroll
-      for (int g = 1; g < NG; ++g) tl = smax(tl, bm[g]);
-      // row max over the two lane halves that share a query
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tl), __float_as_uint(tl), false, false);
-      t = smax(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      m_new = smax(m, t);
-      const float tc = t * c2;
-      mc = m_new * c2;
-      const float delta = tc - mc;                       // c2 (t - m_new) <= 0
-      const float kf = __builtin_floorf(delta);
-      f = delta - kf;                                    // in [0, 1)
-      gam = __builtin_amdgcn_exp2f((mc_old - mc) + (f_old - f));
-      kfold = (int)__builtin_fmaxf(kf, -300.0f);
-      bias = log6 - tc;                                  // P~2 = 2^{fma(S, c2, log2 6 - t c2)}
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[db][v] *= gam;
-    }
-
-    // ---- P~2, unquantized row sum, FP4 pack with E8M0 block scales; O^T += V^T . P^T
-    auto group = [&](auto G_) {
-      constexpr int g = decltype(G_)::value;
-      // smallest e with 6 2^e >= blockmax(P~2) = 6 2^{c2 (bm - t)}; a fully
-      // masked block (bm = -inf) takes the floor -126
-      const int e = (int)__builtin_fmaxf(__builtin_ceilf((bm[g] - t) * c2), -126.0f);
-      const float escale = __builtin_ldexpf(1.0f, e);   // the convert divides by it exactly
-      uint32_t w[4];
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int tt = 2 * g + half;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          // the four converts write all four bytes, so the word starts from the
-          // bits of the first value rather than from a zero
-          uint32_t word = 0;
-          static_for<4>([&](auto I_) {
-            constexpr int i = decltype(I_)::value;
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tt][8 * q + 2 * i], c2, bias));
-            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tt][8 * q + 2 * i + 1], c2, bias));
-            ps[(2 * half + q) & 3] += p0;
-            ps[(2 * half + q) & 3] += p1;
-            if constexpr (i == 0) word = __float_as_uint(p0);
-            word = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(word, p0, p1, escale, i);
-          });
-          w[2 * half + q] = word;
-        }
-      }
-      const v4i pw = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      const int sb = e + kfold + 127;
-      const int psb = sb < 0 ? 0 : sb;
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const uint32_t vsc = *reinterpret_cast<const uint32_t*>(L + T::VS_OFF + (32 * db + col) * 4) >> vshift;
-        const v4i a = *reinterpret_cast<const v4i*>(L + T::VC_OFF + (db * NG + g) * 1024 + lane * 16);
-        oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(pw), oacc[db], 4, 4, 2 * g,
-                                                                   (int)vsc, 0, psb);
-      }
-    };
-
-    if (j + 1 < ntiles) {
-      wait_loads();                         // this wave's loads of tile j+1 have landed
-      __syncthreads();                      // everyone's have; every wave is past tile j-1
-      const int nstage = stage == 2 ? 0 : stage + 1;
-      if (j + 2 < ntiles) issue(j + 2, nstage == 2 ? 0 : nstage + 1);
-      if (!CAUSAL || kb + BKV <= qw + 31) qk(lds[nstage], sbuf[P ^ 1]);
-    }
-    if (active) {
-      static_for<NG>(group);
-      const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
-      lsum_acc = lsum_acc * gam + __builtin_ldexpf(psum, kfold);
-      m = m_new;
-      mc_old = mc;
-      f_old = f;
-    }
-  };
-
-  int stage = 0;
-  for (int j = 0; j < ntiles; j += 2) {
-    tile(ic<0>{}, j, stage);
-    stage = stage == 2 ? 0 : stage + 1;
-    if (j + 1 < ntiles) {
-      tile(ic<1>{}, j + 1, stage);
-      stage = stage == 2 ? 0 : stage + 1;
-    }
-  }
-
-  // ---- epilogue: O = O^T / l, stored row-major ----------------------------
-  const float ltot = lsum_acc + __shfl_xor(lsum_acc, 32, 64);
-  const float inv = 1.0f / ltot;
-  if (qi < N) {
-    uint8_t* obase = reinterpret_cast<uint8_t*>(o);
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d0 = 32 * db + 8 * g + 4 * hi;
-        const size_t idx = ((size_t)bh * N + qi) * D + d0;
-        const float a0 = oacc[db][4 * g] * inv, a1 = oacc[db][4 * g + 1] * inv;
-        const float a2 = oacc[db][4 * g + 2] * inv, a3 = oacc[db][4 * g + 3] * inv;
-        if (OUT == 0) {
-          *reinterpret_cast<float4*>(obase + idx * 4) = make_float4(a0, a1, a2, a3);
-        } else {
-          uint16_t h0, h1, h2, h3;
-          if (OUT == 1) { h0 = f32_to_bf16_rne(a0); h1 = f32_to_bf16_rne(a1); h2 = f32_to_bf16_rne(a2); h3 = f32_to_bf16_rne(a3); }
-          else { h0 = f32_to_fp16_rne(a0); h1 = f32_to_fp16_rne(a1); h2 = f32_to_fp16_rne(a2); h3 = f32_to_fp16_rne(a3); }
-          *reinterpret_cast<uint2*>(obase + idx * 2) = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
-        }
-      }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// 256-key tiles.  The per-tile work -- the accumulator rescale (one multiply
-// per O element), the tile's softmax scalars and its block scales -- is spread
-// over twice the keys; the tile's S (128 VGPRs) takes the place of the
-// double-buffered S of the 128-key kernel, so S is computed at the top of each
-// tile and two LDS stages (load tile j + 1 while tile j runs, one barrier per
-// tile) keep two workgroups per CU.  Same per-lane layouts as above, with
-// four 64-key groups per tile.  Np is a multiple of 128: when the last tile
-// reaches past Np its upper 128 keys are loaded from its lower half (finite
-// values, masked as keys >= N).
-// ---------------------------------------------------------------------------
-template <int D, bool SQ>
-struct Fp4Stage256 {
-  static constexpr int BKV = 256;
-  static constexpr int NSUB = BKV / 32, NKS = D / 64, NDB = D / 32, NG = BKV / 64;
-  static constexpr int NKB = NSUB * NKS, NVB = NDB * NG;
-  static constexpr int KC_OFF = 0;
-  static constexpr int VC_OFF = KC_OFF + NKB * 1024;
   static constexpr int KS_OFF = VC_OFF + NVB * 1024;     // K^ scales: BKV rows x D/32 bytes
   static constexpr int KS_BYTES = BKV * (D / 32);
-  static constexpr int VS_OFF = KS_OFF + KS_BYTES;       // V^T scales: 8 bytes (the tile's 8 blocks) per dim row
-  static constexpr int BIAS_OFF = VS_OFF + D * 8;
+  static constexpr int VW = BKV == 256 ? 2 : 1;          // dwords of V^T scales per dim row (64 keys: half of one)
+  static constexpr int VS_OFF = KS_OFF + (KS_BYTES + 255) / 256 * 256;
+  static constexpr int BIAS_OFF = VS_OFF + D * 4 * VW;   // smoothing Q: fp32 bias of the tile's keys
   static constexpr int BYTES = BIAS_OFF + (SQ ? BKV * 4 : 0);
-  static constexpr int NKSJ = KS_BYTES / 4 / 64, NVSJ = D * 2 / 64;   // dword-load jobs of 64 lanes
-  static_assert(NKB % 8 == 0 && NVB % 8 == 0, "operand blocks split evenly over 4 or 8 waves");
+  static constexpr int NKSJ = (KS_BYTES / 4 + 63) / 64, NVSJ = D * VW / 64;   // dword-load jobs of 64 lanes
 };
+
+// Waves per SIMD that the register budget is set for: a tile's S takes BKV/2
+// registers, O D/2; with smoothing Q at D = 128 and 128 keys a third wave would
+// spill about 30 registers.
+constexpr int fp4_waves(int D, int BKV, int W, bool SQ) {
+  if (BKV == 256) return 8 / W;
+  if (BKV == 128) return D == 128 && SQ ? 2 : 3;
+  return D == 128 ? 3 : 4;
+}
 
 // W waves per workgroup (32 queries each).  W = 4 is the default.  W = 8
 // (flag SAGE_WG256; non-causal, without smoothing Q, whose GEMV bias rows
@@ -423,13 +87,16 @@ struct Fp4Stage256 {
 // 128: about half the fetch traffic.  The two waves on a SIMD then belong to
 // one workgroup and meet at the same barrier, so they overlap less; with the
 // tile loads as buffer loads the time stays within 2% of W = 4.
-template <int D, bool CAUSAL, int OUT, bool SQ, int W>
-__global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
+// OUT: 0 = fp32, 1 = bf16, 2 = fp16.  SQ: smoothing Q -- S += qkb[bh, query
+// block, key] (Algorithm 1's GEMV of the block mean with K', one row of Np
+// floats per 128-query block, which is this workgroup's query tile).
+template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W>
+__global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_kernel(
     const uint8_t* __restrict__ qc, const uint8_t* __restrict__ qs, const uint8_t* __restrict__ kc,
     const uint8_t* __restrict__ ks, const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs,
     const float* __restrict__ qkb, void* __restrict__ o, int BH, int N, int Np, int nqt, float c2, float log6) {
-  using T = Fp4Stage256<D, SQ>;
-  constexpr int BKV = T::BKV, NSUB = T::NSUB, NKS = T::NKS, NDB = T::NDB, NG = T::NG;
+  using T = Fp4Stage<D, BKV, SQ>;
+  constexpr int NSUB = T::NSUB, NKS = T::NKS, NDB = T::NDB, NG = T::NG;
   constexpr int AQW = 32 * W;
   static_assert((W == 4 || W == 8) && (!SQ || W == 4), "4 or 8 waves; smoothing Q blocks are 128 queries");
   __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
@@ -472,50 +139,55 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
   // Each load is a buffer resource over the head's tensor, a uniform offset --
   // tile, job and the tail redirect -- and one of five fixed lane offsets, so
   // a load costs no VALU and no 64-bit address arithmetic.
-  static_assert(W % NKS == 0 && NG == 4 && W % NG == 0, "job layout");
-  constexpr int KJ = T::NKB / W, VJ = T::NVB / W, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + W - 1) / W;
+  static_assert(W % NKS == 0 && W % NG == 0, "job layout");
+  constexpr int KJ = (T::NKB + W - 1) / W, VJ = (T::NVB + W - 1) / W, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + W - 1) / W;
   const uint32_t ko0 = (uint32_t)((32 * (wave / NKS) + col) * (D / 2) + 16 * (wave % NKS) + 16 * NKS * hi);
   const uint32_t vo0 = (uint32_t)((32 * (wave / NG) + col) * (Np / 2) + 32 * (wave % NG) + 16 * hi);
   const uint32_t kso = (uint32_t)(4 * lane);
-  const uint32_t vso = (uint32_t)((lane >> 1) * (Np / 32) + 4 * (lane & 1));
-  const uint32_t vso_hi = (uint32_t)(4 * (lane & 1));   // the second dword: subtracted when it lies past Np
+  constexpr int VW = T::VW;
+  const uint32_t vso = (uint32_t)((lane / VW) * (Np / 32) + 4 * (lane % VW));
+  const uint32_t vso_hi = (uint32_t)(4 * (lane % VW));   // the second dword: subtracted when it lies past Np
   const uint8_t* kbase = kc + (size_t)bh * Np * (D / 2);
   const uint8_t* vbase = vc + (size_t)bh * D * (Np / 2);
   const uint8_t* ksbase = ks + (size_t)bh * Np * (D / 32);
   const uint8_t* vsbase = vs + (size_t)bh * D * (Np / 32);
-  const float* brow = SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr;
   // buffer resources over this head's K^, V^T codes and scales: every load is
   // the resource, a uniform byte offset and one fixed lane offset
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase, Np * (D / 2)), rv = make_rsrc(vbase, D * (Np / 2));
   const __amdgpu_buffer_rsrc_t rks = make_rsrc(ksbase, Np * (D / 32)), rvs = make_rsrc(vsbase, D * (Np / 32));
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr, SQ ? Np * 4 : 0);
   auto issue = [&](int j, int stage) {
     const int kb = j * BKV;
-    const bool short_tail = kb + BKV > Np;                 // keys [kb + 128, kb + 256) lie past Np
+    const bool short_tail = BKV == 256 && kb + BKV > Np;   // keys [kb + 128, kb + 256) lie past Np
     uint8_t* L = lds[stage];
 #pragma unroll
     for (int i = 0; i < KJ; ++i) {
       const int b = wave + W * i, t = b / NKS;
+      if (T::NKB % W != 0 && b >= T::NKB) break;
       const uint32_t back = (short_tail && t >= NSUB / 2) ? 128u * (D / 2) : 0u;
       buf_load16(rk, ko0, (uint32_t)kb * (D / 2) + (uint32_t)i * (32 * W / NKS) * (D / 2) - back, L + T::KC_OFF + b * 1024);
     }
 #pragma unroll
     for (int i = 0; i < VJ; ++i) {
+      if (T::NVB % W != 0 && wave + W * i >= T::NVB) break;
       const uint32_t back = (short_tail && (wave % NG) >= NG / 2) ? 64u : 0u;
-      buf_load16(rv, vo0, (uint32_t)kb / 2 + (uint32_t)i * 8 * W * (Np / 2) - back, L + T::VC_OFF + (wave + W * i) * 1024);
+      buf_load16(rv, vo0, (uint32_t)kb / 2 + (uint32_t)i * (32 * W / NG) * (Np / 2) - back, L + T::VC_OFF + (wave + W * i) * 1024);
     }
 #pragma unroll
     for (int i = 0; i < SJ; ++i) {
       const int jb = wave + W * i;
       if (jb < T::NKSJ) {
         const uint32_t back = (short_tail && 64 * jb * 4 >= T::KS_BYTES / 2) ? T::KS_BYTES / 2 : 0u;
-        buf_load4(rks, kso, (uint32_t)kb * (D / 32) + 256u * jb - back, L + T::KS_OFF + jb * 256);
+        if (T::KS_BYTES % 256 == 0 || 256 * jb + 4 * lane < T::KS_BYTES)
+          buf_load4(rks, kso, (uint32_t)kb * (D / 32) + 256u * jb - back, L + T::KS_OFF + jb * 256);
       } else if (jb < NSJ) {
-        buf_load4(rvs, vso - (short_tail ? vso_hi : 0u), (uint32_t)kb / 32 + (uint32_t)(jb - T::NKSJ) * Np,
+        // 64-key tiles: the aligned dword that holds the tile's two scale bytes
+        buf_load4(rvs, vso - (short_tail ? vso_hi : 0u), ((uint32_t)kb / 32 & ~3u) + (uint32_t)(jb - T::NKSJ) * (2 / VW) * Np,
               L + T::VS_OFF + (jb - T::NKSJ) * 256);
       }
     }
     if constexpr (SQ) {
-      if (wave == 0) lds_load16(brow + (uint32_t)min(kb + 4 * lane, Np - 4), L + T::BIAS_OFF);
+      if (wave == 0 && (BKV == 256 || lane < BKV / 4)) buf_load16(rb, 4u * (uint32_t)min(kb + 4 * lane, Np - 4), 0u, L + T::BIAS_OFF);
     }
   };
 
@@ -555,6 +227,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
       sacc[t] = acc;
     }
     if constexpr (SQ) {
+      // S = fl32(S + bias), elements as below
 #pragma unroll
       for (int u = 0; u < NSUB; ++u) {
         const float* bp = reinterpret_cast<const float*>(L + T::BIAS_OFF) + 64 * (u >> 1) + 32 * hi + 16 * (u & 1);
@@ -568,6 +241,10 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
     }
     const bool need_mask = (kb + BKV > N) || (CAUSAL && kb + BKV - 1 > qw);
     if (need_mask) {
+      // element (u, v) is key kb + 32 hi + c with c = 64 (u >> 1) + 16 (u & 1) + v;
+      // it is kept iff c < rem.  The sign bit of c - rem turns -inf into the
+      // bound +inf for kept keys, and min(S, bound) applies it -- plain bit
+      // arithmetic, so no per-element lane masks are formed.
       const int rem = (CAUSAL ? min(N, qi + 1) : N) - kb - 32 * hi;
 #pragma unroll
       for (int u = 0; u < NSUB; ++u)
@@ -578,6 +255,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
           sacc[u][v] = smin(sacc[u][v], bound);
         }
     }
+    // tile row max (raw scores); the max of a P block is lane-local
     float bm[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -591,42 +269,54 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
     float tl = bm[0];
 #pragma unroll
     for (int g = 1; g < NG; ++g) tl = smax(tl, bm[g]);
+    // row max over the two lane halves that share a query
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tl), __float_as_uint(tl), false, false);
     const float t = smax(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     const float m_new = smax(m, t);
     const float tc = t * c2;
     const float mc = m_new * c2;
     const float delta = tc - mc;
-    const float kf = __builtin_floorf(delta);
+    const float kf = __builtin_floorf(delta);              // c2 (t - m_new) <= 0 split into k and f in [0, 1)
     const float f = delta - kf;
     const float gam = __builtin_amdgcn_exp2f((mc_old - mc) + (f_old - f));
     const int kfold = (int)__builtin_fmaxf(kf, -300.0f);
     const int kf127 = kfold + 127;                         // P's scale byte is e + kfold + 127, clamped at 0
-    const float bias = log6 - tc;
+    const float bias = log6 - tc;                          // P~2 = 2^{fma(S, c2, log2 6 - t c2)}
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[db][v] *= gam;
 
-    // V^T scale bytes of this lane's dim rows: dword h of the row's 8 bytes holds blocks 4h .. 4h + 3
-    uint32_t vsw[NDB][2];
+    // V^T scale bytes of this lane's dim rows, block 2g + hi of the tile in byte 2(g & 1) of dword g >> 1
+    // (read as v2u, not uint2: see sage_common.h; as uint2 this read waited for
+    // the whole prefetch of tile j + 1: B4 H32 N4096 D128 681 -> 643 us a call)
+    uint32_t vsw[NDB][VW];
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      const uint2 w2 = *reinterpret_cast<const uint2*>(L + T::VS_OFF + (32 * db + col) * 8);
-      vsw[db][0] = w2.x >> (8 * hi);
-      vsw[db][1] = w2.y >> (8 * hi);
+      const uint8_t* vp = L + T::VS_OFF + (32 * db + col) * 4 * VW;
+      if constexpr (VW == 2) {
+        const v2u w2 = *reinterpret_cast<const v2u*>(vp);
+        vsw[db][0] = w2[0] >> (8 * hi);
+        vsw[db][1] = w2[1] >> (8 * hi);
+      } else {
+        vsw[db][0] = *reinterpret_cast<const uint32_t*>(vp) >> (8 * ((BKV == 64 ? (kb / 32) & 3 : 0) + hi));
+      }
     }
     float ps[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     static_for<NG>([&](auto G_) {
       constexpr int g = decltype(G_)::value;
+      // smallest e with 6 2^e >= blockmax(P~2) = 6 2^{c2 (bm - t)}; a fully
+      // masked block (bm = -inf) takes the floor -126
       const int e = (int)__builtin_fmaxf(__builtin_ceilf((bm[g] - t) * c2), -126.0f);
-      const float escale = __builtin_ldexpf(1.0f, e);
+      const float escale = __builtin_ldexpf(1.0f, e);      // the convert divides by it exactly
       uint32_t w[4];
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         const int tt = 2 * g + half;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
+          // the four converts write all four bytes, so the word starts from the
+          // bits of the first value rather than from a zero
           uint32_t word = 0;
           static_for<4>([&](auto I_) {
             constexpr int i = decltype(I_)::value;
@@ -681,52 +371,32 @@ __global__ __launch_bounds__(64 * W, 8 / W) void attn_fp4_mx256_kernel(
   }
 }
 
-template <int D, bool CAUSAL, int OUT, bool SQ, int W>
-static hipError_t launch_fp4_256_t(const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
-                                   const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2,
-                                   float log6, hipStream_t st) {
-  const int nqt = (N + 32 * W - 1) / (32 * W);
-  hipLaunchKernelGGL((attn_fp4_mx256_kernel<D, CAUSAL, OUT, SQ, W>), dim3((unsigned)(nqt * BH)), dim3(64 * W), 0, st,
-                     (const uint8_t*)qc, (const uint8_t*)qs, (const uint8_t*)kc, (const uint8_t*)ks, (const uint8_t*)vc,
-                     (const uint8_t*)vs, qkb, o, BH, N, Np, nqt, c2, log6);
-  return hipGetLastError();
-}
-
-template <int D, bool CAUSAL, bool SQ, int W>
-static hipError_t launch_fp4_256_o(int out, const void* qc, const void* qs, const void* kc, const void* ks,
-                                   const void* vc, const void* vs, const float* qkb, void* o, int BH, int N, int Np,
-                                   float c2, float log6, hipStream_t st) {
-  if (out == 0) return launch_fp4_256_t<D, CAUSAL, 0, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  if (out == 1) return launch_fp4_256_t<D, CAUSAL, 1, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  return launch_fp4_256_t<D, CAUSAL, 2, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-}
-
-template <int D, int BKV, bool CAUSAL, int OUT, bool SQ>
+template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W>
 static hipError_t launch_fp4_t(const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  const int nqt = (N + AQ - 1) / AQ;
-  hipLaunchKernelGGL((attn_fp4_mx_kernel<D, BKV, CAUSAL, OUT, SQ>), dim3((unsigned)(nqt * BH)), dim3(256), 0, st,
+  const int nqt = (N + 32 * W - 1) / (32 * W);
+  hipLaunchKernelGGL((attn_fp4_mx_kernel<D, BKV, CAUSAL, OUT, SQ, W>), dim3((unsigned)(nqt * BH)), dim3(64 * W), 0, st,
                      (const uint8_t*)qc, (const uint8_t*)qs, (const uint8_t*)kc, (const uint8_t*)ks, (const uint8_t*)vc,
                      (const uint8_t*)vs, qkb, o, BH, N, Np, nqt, c2, log6);
   return hipGetLastError();
 }
 
-template <int D, int BKV, bool CAUSAL, bool SQ>
+template <int D, int BKV, bool CAUSAL, bool SQ, int W>
 static hipError_t launch_fp4_o(int out, const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  if (out == 0) return launch_fp4_t<D, BKV, CAUSAL, 0, SQ>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  if (out == 1) return launch_fp4_t<D, BKV, CAUSAL, 1, SQ>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  return launch_fp4_t<D, BKV, CAUSAL, 2, SQ>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (out == 0) return launch_fp4_t<D, BKV, CAUSAL, 0, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (out == 1) return launch_fp4_t<D, BKV, CAUSAL, 1, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  return launch_fp4_t<D, BKV, CAUSAL, 2, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
 }
 
 template <int D, int BKV, bool CAUSAL>
 static hipError_t launch_fp4_s(int out, const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  return qkb ? launch_fp4_o<D, BKV, CAUSAL, true>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-             : launch_fp4_o<D, BKV, CAUSAL, false>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
+             : launch_fp4_o<D, BKV, CAUSAL, false, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
 }
 
 // qkb: smoothing-Q bias [BH, ceil(N/128), Np] fp32, or null without smoothing Q.
@@ -736,21 +406,13 @@ hipError_t launch_attn_fp4_mx(const void* qc, const void* qs, const void* kc, co
 #define SAGE_A(DD, BB)                                                                                    \
   return causal ? launch_fp4_s<DD, BB, true>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st) \
                 : launch_fp4_s<DD, BB, false>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-  if (bkv == 256) {
-    // 256-query workgroups: non-causal, without smoothing Q (checked by the caller)
-    if (wg256) {
-      if (D == 128) return launch_fp4_256_o<128, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-      return launch_fp4_256_o<64, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-    }
-#define SAGE_A256(DD, CC)                                                                                         \
-  return qkb ? launch_fp4_256_o<DD, CC, true, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st) \
-             : launch_fp4_256_o<DD, CC, false, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-    if (D == 128) { if (causal) { SAGE_A256(128, true); } else { SAGE_A256(128, false); } }
-    else { if (causal) { SAGE_A256(64, true); } else { SAGE_A256(64, false); } }
-#undef SAGE_A256
+  if (wg256) {
+    // 256-query workgroups: 256-key tiles, non-causal, without smoothing Q (checked by the caller)
+    if (D == 128) return launch_fp4_o<128, 256, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+    return launch_fp4_o<64, 256, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
   }
-  if (D == 128) { if (bkv == 128) { SAGE_A(128, 128); } else { SAGE_A(128, 64); } }
-  else { if (bkv == 128) { SAGE_A(64, 128); } else { SAGE_A(64, 64); } }
+  if (D == 128) { if (bkv == 256) { SAGE_A(128, 256); } else if (bkv == 128) { SAGE_A(128, 128); } else { SAGE_A(128, 64); } }
+  if (bkv == 256) { SAGE_A(64, 256); } else if (bkv == 128) { SAGE_A(64, 128); } else { SAGE_A(64, 64); }
 #undef SAGE_A
 }
 

@@ -37,6 +37,24 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Status codes mirrored from the public header (kept in one place for kernels).
 enum { kFmtMX = 0, kFmtNV16 = 1 };
 
+// A raw buffer resource over `bytes` bytes at `base` (reads past the end return
+// zero), and direct-to-LDS buffer loads from it: lane l's bytes land at
+// dst + size * l; the byte address is base + voff (per lane) + soff (uniform).
+// Unlike global_load_lds, which the compiler also counts as an LDS access that
+// may finish out of order (each later LDS read then waits for all reads before
+// it), they leave the waits of operand reads counted.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ void buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff,
+                                           (uint32_t)__builtin_amdgcn_readfirstlane((int)soff), 0, 0);
+}
+__device__ __forceinline__ void buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, void* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 4, voff,
+                                           (uint32_t)__builtin_amdgcn_readfirstlane((int)soff), 0, 0);
+}
+
 // ---- 16-bit input widening (exact) ----------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ float fp16_to_f32(uint16_t h) {
