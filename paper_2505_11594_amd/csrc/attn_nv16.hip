@@ -35,19 +35,7 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ v8h as_h(const v4i x) { return __builtin_bit_cast(v8h, x); }
 
-// Direct-to-LDS 16-byte load: lane l's bytes land at dst + 16 l.
-__device__ __forceinline__ void nv_lds_load16(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
 __device__ __forceinline__ void nv_wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-// a workgroup-uniform address in scalar registers (scalar base + lane offset)
-__device__ __forceinline__ const uint8_t* nv_sbase(const void* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return reinterpret_cast<const uint8_t*>((hi << 32) | lo);
-}
-
 // Exact f16 expansion of K^ and V^T.  Both are flat arrays of 32-element
 // units (16 code bytes, two E4M3 scale bytes, one per 16 elements); unit u of
 // K^ (row-major [BH, Np, D]) and of V^T ([BH, D, Np]) expands to the 32 f16
@@ -176,27 +164,32 @@ __global__ __launch_bounds__(256, 2) void attn_nv16_kernel(
   constexpr int KRJ = 1024 / T::KROW, VRJ = 1024 / T::VROW;
   constexpr int NKJ = BKV * T::KROW / 1024 / 4, NVJ = D * T::VROW / 1024 / 4;   // jobs per wave
   static_assert(BKV * T::KROW % 4096 == 0 && D * T::VROW % 4096 == 0, "jobs split evenly over 4 waves");
+  // The loads are buffer loads (see sage_common.h) over the tile's rows of K~
+  // and, for V~^T, from the tile's first column on (a head's f16 tensor may
+  // span 4 GiB, so the resource starts at the tile): B1 H24 N19200 D64 3087 ->
+  // 2993 us a call, B1 H32 N4096 D128 (both LDS changes) 536 -> 478.
   uint32_t klo, vlo;
   {
     const int kr = wave * KRJ + lane / T::KCH, vr = wave * VRJ + lane / T::VCH;
-    klo = (uint32_t)((lane / T::KCH) * (D * 2) + bswz<T::KCH>(kr, lane % T::KCH) * 16);
-    vlo = (uint32_t)((lane / T::VCH) * (Np * 2) + bswz<T::VCH>(vr, lane % T::VCH) * 16);
+    klo = (uint32_t)(kr * (D * 2) + bswz<T::KCH>(kr, lane % T::KCH) * 16);
+    vlo = (uint32_t)vr * ((uint32_t)Np * 2) + (uint32_t)(bswz<T::VCH>(vr, lane % T::VCH) * 16);
   }
-  const uint8_t* kbase = kh + ((size_t)bh * Np + wave * KRJ) * (D * 2);
-  const uint8_t* vbase = vth + ((size_t)bh * D + wave * VRJ) * ((size_t)Np * 2);
+  const uint8_t* kbase = kh + (size_t)bh * Np * (D * 2);
+  const uint8_t* vbase = vth + (size_t)bh * D * ((size_t)Np * 2);
+  const size_t vbytes = (size_t)D * Np * 2;
   // smoothing Q: the tile's BKV bias entries, 16 bytes per lane of wave 0
-  const float* brow = SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr;
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr, SQ ? (uint32_t)Np * 4u : 0u);
   auto issue = [&](int kb, uint8_t* L) {
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase + (size_t)kb * (D * 2), (uint32_t)(BKV * D * 2));
+    const __amdgpu_buffer_rsrc_t rv =
+        make_rsrc(vbase + (size_t)kb * 2, (uint32_t)min(vbytes - (size_t)kb * 2, (size_t)0xFFFFFFFFu));
 #pragma unroll
-    for (int i = 0; i < NKJ; ++i)
-      nv_lds_load16(nv_sbase(kbase + ((size_t)kb + (size_t)4 * KRJ * i) * (D * 2)) + klo,
-                    L + T::K_OFF + (wave + 4 * i) * 1024);
+    for (int i = 0; i < NKJ; ++i) buf_load16(rk, klo, (uint32_t)(4 * KRJ * i * (D * 2)), L + T::K_OFF + (wave + 4 * i) * 1024);
 #pragma unroll
     for (int i = 0; i < NVJ; ++i)
-      nv_lds_load16(nv_sbase(vbase + (size_t)4 * VRJ * i * ((size_t)Np * 2) + (size_t)kb * 2) + vlo,
-                    L + T::V_OFF + (wave + 4 * i) * 1024);
+      buf_load16(rv, vlo, (uint32_t)(4 * VRJ * i) * ((uint32_t)Np * 2), L + T::V_OFF + (wave + 4 * i) * 1024);
     if constexpr (SQ) {
-      if (wave == 0 && lane < BKV / 4) nv_lds_load16(brow + kb + 4 * lane, L + BIAS_OFF);
+      if (wave == 0 && lane < BKV / 4) buf_load16(rb, 16u * lane, 4u * (uint32_t)kb, L + BIAS_OFF);
     }
   };
   issue(0, lds);
