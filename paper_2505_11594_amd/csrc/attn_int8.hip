@@ -45,12 +45,6 @@ namespace sage {
 
 constexpr int I8_AQ = 128;   // queries per workgroup (4 waves x 32)
 
-__device__ __forceinline__ void i8_lds_load16(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-__device__ __forceinline__ void i8_lds_load4(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
-}
 __device__ __forceinline__ void i8_wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
 // rint of four values in [0, 255], packed (element 0 in the low byte):
@@ -123,38 +117,32 @@ __global__ __launch_bounds__(256, 2) void attn_int8_kernel(
   }
 
   // ---- tile loads: HBM -> LDS ------------------------------------------
-  // Wave w loads K^ operand blocks w, w + 4, ... (block b = (t, s): key row
-  // 32t + col, channels [32s + 16hi, +16)) and V^T operand blocks w, w + 4, ...
-  // (b = (db, u): dim row 32db + col, tile keys [32u + 16hi, +16)); wave 0's
-  // lanes 0 and 1 load s_K and s_V of the tile.
-  constexpr int KJ = (T::NKB + 3) / 4, VJ = (T::NVB + 3) / 4;
-  const int8_t* kbase = kc + (size_t)bh * Np * D;
-  const int8_t* vbase = vc + (size_t)bh * D * Np;
+  // Wave w loads K^ operand blocks b = w + 4i (key row 32t + col, channels
+  // [32s + 16hi, +16) with t = b / NKS, s = b % NKS) and V^T operand blocks
+  // b = w + 4i (dim row 32db + col, tile keys [32u + 16hi, +16) with
+  // db = b / NSUB, u = b % NSUB); lane 0 of waves 0 and 1 loads s_K and s_V.
+  // Buffer loads: the head's tensor, a uniform offset and one fixed lane offset
+  // per operand.  (global_load_lds also counts as an LDS access of unknown
+  // order, so with it every operand read waited for all LDS reads before it:
+  // B2 H32 N8192 D128 1743 us a call with it, 1710 so.)
+  constexpr int KJ = T::NKB / 4, VJ = T::NVB / 4;
+  static_assert(T::NKB % 4 == 0 && T::NVB % 4 == 0 && 4 % NKS == 0 && 4 % NSUB == 0, "job layout");
   const int nkt = Np / BKV;
-  uint32_t ko[KJ], vo[VJ];
-#pragma unroll
-  for (int i = 0; i < KJ; ++i) {
-    const int b = wave + 4 * i, t = b / NKS, s = b % NKS;
-    ko[i] = (32 * t + col) * D + 32 * s + 16 * hi;
-  }
-#pragma unroll
-  for (int i = 0; i < VJ; ++i) {
-    const int b = wave + 4 * i, db = b / NSUB, u = b % NSUB;
-    vo[i] = (32 * db + col) * Np + 32 * u + 16 * hi;
-  }
-  const float* sc_src = (lane == 0 ? ks : vs) + (size_t)bh * nkt;
+  const uint32_t hb = (uint32_t)Np * (uint32_t)D;          // bytes of one head's K^ (and V^T), at most 2^31
+  const __amdgpu_buffer_rsrc_t rk = make_rsrc(kc + (size_t)bh * hb, hb), rv = make_rsrc(vc + (size_t)bh * hb, hb);
+  const __amdgpu_buffer_rsrc_t rs = make_rsrc((wave == 0 ? ks : vs) + (size_t)bh * nkt, (uint32_t)nkt * 4u);
+  const uint32_t ko = (uint32_t)((32 * (wave / NKS) + col) * D + 32 * (wave % NKS) + 16 * hi);
+  const uint32_t vo = (uint32_t)(32 * (wave / NSUB) + col) * (uint32_t)Np + 32 * (wave % NSUB) + 16 * hi;
   auto issue = [&](int j, int stage) {
-    const int kb = j * BKV;
+    const uint32_t kb = (uint32_t)j * BKV;
     uint8_t* L = lds[stage];
-    const int8_t* kt = kbase + (size_t)kb * D;
-    const int8_t* vt = vbase + kb;
 #pragma unroll
     for (int i = 0; i < KJ; ++i)
-      if (T::NKB % 4 == 0 || wave + 4 * i < T::NKB) i8_lds_load16(kt + ko[i], L + T::KC_OFF + (wave + 4 * i) * 1024);
+      buf_load16(rk, ko, (kb + (uint32_t)i * (128 / NKS)) * D, L + T::KC_OFF + (wave + 4 * i) * 1024);
 #pragma unroll
     for (int i = 0; i < VJ; ++i)
-      if (T::NVB % 4 == 0 || wave + 4 * i < T::NVB) i8_lds_load16(vt + vo[i], L + T::VC_OFF + (wave + 4 * i) * 1024);
-    if (wave == 0 && lane < 2) i8_lds_load4(sc_src + j, L + T::SC_OFF);
+      buf_load16(rv, vo, kb + (uint32_t)i * (128 / NSUB) * (uint32_t)Np, L + T::VC_OFF + (wave + 4 * i) * 1024);
+    if (wave < 2 && lane == 0) buf_load4(rs, 0u, 4u * (uint32_t)j, L + T::SC_OFF + 4 * wave);
   };
 
   v16f oacc[NDB];
