@@ -35,6 +35,8 @@
 // next block's first barrier, and dQ reads the row sums a block ahead.  With the
 // waits that each of these brought, one forward and backward of B1 H32 N8192
 // D128 took 5836 us, without them 5224 us; B2 H12 N1000 D64 causal 148 -> 138 us.
+// Buffer loads and maxima and row sums exchanged without LDS: 5224 -> 5146 and
+// 138 -> 132 us (the forward's share of that included).
 #include "sage_common.h"
 
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -80,17 +82,25 @@ __device__ __forceinline__ uint32_t quad_byte_transpose(uint32_t w, int lane) {
 
 // One step of a butterfly reduction over lanes: each lane keeps one half of
 // its 2H values (the upper half where `upper`), adds the partner lane's other
-// half to it, the partner given by a DPP control (CTRL >= 0) or lane ^ 16.
+// half to it, the partner given by a DPP control.
 template <int H, int CTRL>
 __device__ __forceinline__ void bw_fold(float (&x)[16], bool upper) {
 #pragma unroll
   for (int i = 0; i < H; ++i) {
     const float send = upper ? x[i] : x[i + H];
     const float keep = upper ? x[i + H] : x[i];
-    float recv;
-    if constexpr (CTRL < 0) recv = __shfl_xor(send, 16, 64);
-    else recv = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), CTRL, 0xF, 0xF, true));
-    x[i] = keep + recv;
+    x[i] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), CTRL, 0xF, 0xF, true));
+  }
+}
+// The same step for partner lane ^ 16, upper where lane & 16: swapping the odd
+// 16-lane rows of x[i] with the even rows of x[i + H] leaves in every lane the
+// two values to add.
+template <int H>
+__device__ __forceinline__ void bw_fold16(float (&x)[16]) {
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i + H]), false, false);
+    x[i] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
   }
 }
 
@@ -108,10 +118,21 @@ __device__ __forceinline__ v4i bw_codes_u(const float (&x)[16], float r) {
   return v4i{w[0], w[1], w[2], w[3]};
 }
 
+// maximum over the wave, in every lane (no LDS: six swaps through it were a
+// serial chain of LDS latencies in front of each block's barrier)
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return __builtin_fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)));
+}
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = __builtin_fmaxf(x, __shfl_xor(x, off, 64));
-  return x;
+  x = dpp_max<0xB1>(x);      // quad_perm [1,0,3,2]
+  x = dpp_max<0x4E>(x);      // quad_perm [2,3,0,1]
+  x = dpp_max<0x141>(x);     // row_half_mirror
+  x = dpp_max<0x140>(x);     // row_mirror
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __builtin_fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __builtin_fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // ---------------------------------------------------------------------------
@@ -149,9 +170,6 @@ __global__ __launch_bounds__(256) void i8_bwd_prep_kernel(const uint16_t* __rest
   }
 }
 
-__device__ __forceinline__ void bw_lds_load16(const void* src, void* dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
 __device__ __forceinline__ void bw_wait_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 // vmcnt(n) for the counts used below (n < 16: the low field of the immediate)
 template <int N>
@@ -174,29 +192,41 @@ __device__ __forceinline__ void bw_lds_barrier() { asm volatile("s_waitcnt lgkmc
 // [32s + 16hi, +16) --, dO operand blocks (u, s16) -- channels [16s16 + 8hi,
 // +8) --, transposed operand blocks (db, u) -- channel rows 32db + col,
 // queries [32u + 16hi, +16) of the block --, and the block's Lb and D (128
-// floats each).  Query rows >= N read row N - 1 (those entries are masked).
+// floats each).
 
-// query-block loads shared by the two kernels (wave w takes operand blocks
-// w, w + 4, ...)
-template <int D>
-__device__ __forceinline__ void bw_load_qa(const int8_t* qc, uint8_t* dst, int b, int bh, int N, int q0, int col,
-                                           int hi) {
-  constexpr int NKS = D / 32;
-  const int u = b / NKS, s = b % NKS;
-  const int q = min(q0 + 32 * u + col, N - 1);
-  bw_lds_load16(qc + ((size_t)bh * N + q) * D + 32 * s + 16 * hi, dst);
+// Loads of 128-row blocks, as buffer loads (see sage_common.h): a resource
+// over the rows of the block that exist (rows past the end read zero; those
+// entries are masked), one fixed lane offset per operand, and a uniform offset
+// per operand block.
+//
+// Row-major operand (E bytes per element), rows [r0, r0 + 128) of x [BH, rows, D]:
+// operand block b = wave + W i is (32-row group b / NS, K-step b % NS), lane
+// bytes [KB s + 16 hi, +16) of row 32u + col with KB = 32 bytes per K-step.
+template <int D, int E>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bw_rows_rsrc(const void* x, int bh, int rows, int r0) {
+  const int n = min(rows - r0, 128);
+  return make_rsrc(static_cast<const uint8_t*>(x) + ((size_t)bh * rows + r0) * (D * E), (uint32_t)n * (D * E));
 }
-template <int D>
-__device__ __forceinline__ void bw_load_t(const int8_t* xt, uint8_t* dst, int t, int bh, int Np, int q0, int col,
-                                          int hi) {
-  const int db = t / 4, u = t % 4;
-  bw_lds_load16(xt + ((size_t)bh * D + 32 * db + col) * Np + q0 + 32 * u + 16 * hi, dst);
+template <int D, int E>
+__device__ __forceinline__ uint32_t bw_rows_voff(int col, int hi) { return (uint32_t)(col * D * E + 16 * hi); }
+template <int D, int E>
+__device__ __forceinline__ uint32_t bw_rows_soff(int b) {
+  constexpr int NS = D * E / 32;
+  return (uint32_t)((b / NS) * 32 * D * E + (b % NS) * 32);
 }
-// Lb and D of the query block (one wave: lanes 0-31 Lb, 32-63 D)
+// Transposed operand, columns [c0, c0 + 128) of x [BH, D, Np] (int8): operand
+// block t is (channel block t / 4, 32-column group t % 4).
+template <int D>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bw_cols_rsrc(const void* x, int bh, int Np, int c0) {
+  return make_rsrc(static_cast<const uint8_t*>(x) + (size_t)bh * D * Np + c0, (uint32_t)D * (uint32_t)Np - (uint32_t)c0);
+}
+__device__ __forceinline__ uint32_t bw_cols_voff(int Np, int col, int hi) { return (uint32_t)col * (uint32_t)Np + 16u * hi; }
+__device__ __forceinline__ uint32_t bw_cols_soff(int Np, int t) { return 32u * (t / 4) * (uint32_t)Np + 32u * (t % 4); }
+// Lb and D of the query block: lanes 0-31 of wave 0 load Lb, of wave 1 D
 __device__ __forceinline__ void bw_load_ld(const float* lb, const float* drow, uint8_t* dst, int bh, int Np, int q0,
-                                           int lane) {
-  const float* src = lane < 32 ? lb + (size_t)bh * Np + q0 + 4 * lane : drow + (size_t)bh * Np + q0 + 4 * (lane - 32);
-  bw_lds_load16(src, dst);
+                                           int wave, int lane) {
+  if (wave < 2 && lane < 32)
+    buf_load16(make_rsrc((wave == 0 ? lb : drow) + (size_t)bh * Np + q0, 512u), 16u * lane, 0u, dst + 512 * wave);
 }
 
 // visible iff q < N, key < N and (causal) key <= q: the three sign bits,
@@ -255,13 +285,14 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
   auto issue = [&](int i, int buf) {
     const int q0 = i * BW_Q;
     uint8_t* L = lds + buf * T::BYTES;
+    const __amdgpu_buffer_rsrc_t rq = bw_rows_rsrc<D, 1>(qc, bh, N, q0), rt = bw_cols_rsrc<D>(gt, bh, Np, q0);
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k;
-      if (b < T::NQA) bw_load_qa<D>(qc, L + T::QA_OFF + b * 1024, b, bh, N, q0, col, hi);
-      else bw_load_t<D>(gt, L + T::GT_OFF + (b - T::NQA) * 1024, b - T::NQA, bh, Np, q0, col, hi);
+      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::QA_OFF + b * 1024);
+      else buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, b - T::NQA), L + T::GT_OFF + (b - T::NQA) * 1024);
     }
-    if (wave == 0) bw_load_ld(lb, drow, L + T::LD_OFF, bh, Np, q0, lane);
+    bw_load_ld(lb, drow, L + T::LD_OFF, bh, Np, q0, wave, lane);
   };
 
   const int i0 = CAUSAL ? kb / BW_Q : 0;
@@ -421,23 +452,20 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
   auto issue_A = [&](int i, int buf) {
     const int q0 = i * BW_Q;
     uint8_t* L = lds + buf * T::A_BYTES;
+    const __amdgpu_buffer_rsrc_t rq = bw_rows_rsrc<D, 1>(qc, bh, N, q0), rg = bw_rows_rsrc<D, 2>(dout, bh, N, q0);
 #pragma unroll
     for (int k = 0; k < T::AJ; ++k) {
-      const int b = wave + BW_DK_WAVES * k;
-      if (b < T::NQA) {
-        bw_load_qa<D>(qc, L + T::QA_OFF + b * 1024, b, bh, N, q0, col, hi);
-      } else {
-        const int g = b - T::NQA, u = g / NKS16, s = g % NKS16;
-        const int q = min(q0 + 32 * u + col, N - 1);
-        bw_lds_load16(dout + ((size_t)bh * N + q) * D + 16 * s + 8 * hi, L + T::GA_OFF + g * 1024);
-      }
+      const int b = wave + BW_DK_WAVES * k, g = b - T::NQA;
+      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::QA_OFF + b * 1024);
+      else buf_load16(rg, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), L + T::GA_OFF + g * 1024);
     }
   };
   auto issue_T = [&](int i) {
+    const __amdgpu_buffer_rsrc_t rt = bw_cols_rsrc<D>(qt, bh, Np, i * BW_Q);
 #pragma unroll
     for (int k = 0; k < T::TJ; ++k) {
       const int t = wave + BW_DK_WAVES * k;
-      bw_load_t<D>(qt, ldsT + t * 1024, t, bh, Np, i * BW_Q, col, hi);
+      buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, t), ldsT + t * 1024);
     }
   };
 
@@ -453,14 +481,14 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     if (tid == 0) dss[pair] = sdsv;
   };
   const int i0 = CAUSAL ? kb / BW_Q : 0;
-  if (wave == 0) bw_load_ld(lb, drow, lds + (i0 & 1) * T::A_BYTES + T::LD_OFF, bh, Np, i0 * BW_Q, lane);
+  bw_load_ld(lb, drow, lds + (i0 & 1) * T::A_BYTES + T::LD_OFF, bh, Np, i0 * BW_Q, wave, lane);
   issue_A(i0, i0 & 1);
   for (int i = i0; i < nqb; ++i) {
     const int q0 = i * BW_Q, a = i & 1;
     bw_wait_all();                                 // this wave's loads of block i have landed
     __syncthreads();                               // everyone's; every wave is done with block i - 1
     if (STORE_DS && i > i0) store_ds(i - 1);
-    if (i + 1 < nqb && wave == 0) bw_load_ld(lb, drow, lds + (a ^ 1) * T::A_BYTES + T::LD_OFF, bh, Np, q0 + BW_Q, lane);
+    if (i + 1 < nqb) bw_load_ld(lb, drow, lds + (a ^ 1) * T::A_BYTES + T::LD_OFF, bh, Np, q0 + BW_Q, wave, lane);
     issue_T(i);
     if (i + 1 < nqb) issue_A(i + 1, a ^ 1);
     const uint8_t* L = lds + a * T::A_BYTES;
@@ -539,7 +567,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
         float x[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) x[e] = dS[uu][e];
-        bw_fold<8, -1>(x, (col & 16) != 0);
+        bw_fold16<8>(x);
         bw_fold<4, 0x128>(x, (col & 8) != 0);      // row_ror:8
         bw_fold<2, 0x141>(x, (col & 4) != 0);      // row_half_mirror
         bw_fold<1, 0x4E>(x, (col & 2) != 0);       // quad_perm [2,3,0,1]
@@ -641,24 +669,18 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
   for (int db = 0; db < NDB; ++db) dqa[db] = v16f{};
 
   // loads of KV block j: wave w takes operand blocks w, w + 4, ...; V rows
-  // >= N read row N - 1 (those keys are masked)
+  // >= N read zero (those keys are masked)
   auto issue = [&](int j, int buf) {
     const int kb = j * BW_K;
     uint8_t* L = lds + buf * T::BYTES;
+    const __amdgpu_buffer_rsrc_t rk = bw_rows_rsrc<D, 1>(kc, bh, Np, kb), rv = bw_rows_rsrc<D, 2>(v, bh, N, kb);
+    const __amdgpu_buffer_rsrc_t rt = bw_cols_rsrc<D>(kt, bh, Np, kb);
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
-      const int b = wave + 4 * k;
-      if (b < T::NKA) {
-        const int t = b / NKS, s = b % NKS;
-        bw_lds_load16(kc + ((size_t)bh * Np + kb + 32 * t + col) * D + 32 * s + 16 * hi, L + T::KA_OFF + b * 1024);
-      } else if (b < T::NKA + T::NVA) {
-        const int g = b - T::NKA, t = g / NKS16, s = g % NKS16;
-        const int kr = min(kb + 32 * t + col, N - 1);
-        bw_lds_load16(v + ((size_t)bh * N + kr) * D + 16 * s + 8 * hi, L + T::VA_OFF + g * 1024);
-      } else {
-        const int g = b - T::NKA - T::NVA, db = g / NT, t = g % NT;
-        bw_lds_load16(kt + ((size_t)bh * D + 32 * db + col) * Np + kb + 32 * t + 16 * hi, L + T::KT_OFF + g * 1024);
-      }
+      const int b = wave + 4 * k, g = b - T::NKA, t = g - T::NVA;
+      if (b < T::NKA) buf_load16(rk, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::KA_OFF + b * 1024);
+      else if (g < T::NVA) buf_load16(rv, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), L + T::VA_OFF + g * 1024);
+      else buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, t), L + T::KT_OFF + t * 1024);
     }
   };
 
@@ -808,10 +830,11 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
   auto issue = [&](int j, int buf) {
     const int kb = j * BW_K;
     uint8_t* L = lds + buf * T::BYTES;
+    const __amdgpu_buffer_rsrc_t rt = bw_cols_rsrc<D>(kt, bh, Np, kb);
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
-      const int b = wave + 4 * k, db = b / NT, t = b % NT;
-      bw_lds_load16(kt + ((size_t)bh * D + 32 * db + col) * Np + kb + 32 * t + 16 * hi, L + b * 1024);
+      const int b = wave + 4 * k;
+      buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, b), L + b * 1024);
     }
   };
   // this wave's dS^ operand blocks (query group `wave`, key subtiles 0..NT-1) of pair (i, j), and
