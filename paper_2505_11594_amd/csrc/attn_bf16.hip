@@ -1,107 +1,87 @@
 // bf16-MFMA comparison kernel for gfx950: FlashAttention forward (Sec. 2)
-// with the same work decomposition as the FP4 kernel -- 4 waves x 32
-// queries per workgroup, K and V^T tiles double-buffered in LDS, online
-// softmax in registers -- on v_mfma_f32_32x32x16_bf16:
+// with the same work decomposition as the FP4 kernel -- 4 waves x 32 queries
+// per workgroup, K and V tiles double-buffered in LDS, online softmax in
+// registers -- on v_mfma_f32_32x32x16_bf16:
 //   S^T (keys x queries) = K . Q^T     A = K tile (LDS), B = Q (registers)
 //   O^T (dims x queries) += V^T . P^T  A = V^T tile (LDS), B = P in bf16
 // S is fp32, the softmax is fp32, P is rounded to bf16 (nearest even) for the
 // second product.  Layout (32x32x16): lane l holds row/column l%32 and
 // K-indices [8*(l/32), +8); the accumulator of lane l holds column l%32 and
-// rows 8g + 4*(l/32) + r.  The V^T pre-pass stores the tokens of every
-// 16-token group with offset bits 2 and 3 swapped, so the 8 scores a lane
-// holds for one 16-key K-step are exactly the keys its P operand slots need.
+// rows 8g + 4*(l/32) + r.
+//
+// Both tiles go from HBM straight into LDS, row-major as they lie in memory.
+// V is transposed by the LDS read: ds_read_b64_tr_b16 gives the 16 lanes of a
+// group, each addressing 4 channels of one key, the 4 keys of one channel
+// each, and two such reads are the 8 keys 16w + {0, 8} + 4 (l/32) + r of K-step w
+// whose scores the lane holds.  (A pre-pass that wrote V^T to a workspace took
+// 46 us of 1247 on B4 H32 N4096 D128, and its allocation as much as 370 us of a
+// call that starts on an idle GPU.)  MFMA issue bounds it: 1250 -> 1090 us there,
+// 1.01 PFLOP/s, against 1.27 that a large bf16 matrix product reaches.
 #include "sage_common.h"
 #include "bf16_tile.h"
 
 namespace sage {
 
-constexpr int BQ = 128;        // queries per workgroup
 constexpr int BK = 64;         // keys per tile
-template <int D> using Bf16Tile = Bf16TileT<D, BK>;
+constexpr int BW = 4;          // waves per workgroup (32 queries each)
 
-__device__ __forceinline__ int vt_pos(int t) {
-  // offset bits (b3 b2) swapped inside each 16-token group (an involution)
-  return (t & ~12) | ((t & 4) << 1) | ((t & 8) >> 1);
+// Chunk swizzle of the V tile (16-byte chunks of a key's row): the 8 keys whose
+// chunk pairs one read instruction touches fall on distinct bank groups.
+template <int D>
+__device__ __forceinline__ int vswz(int row, int ch) {
+  return D == 128 ? ch ^ ((row & 7) << 1) : ch ^ (((row >> 1) & 3) << 1);
 }
 
-// V [bh, N, D] -> V^T [bh, D, Np] (bf16), tokens permuted by vt_pos, tail zero.
-template <int D>
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t* __restrict__ v, uint16_t* __restrict__ vt,
-                                                          int N, int Np) {
-  __shared__ uint16_t tile[64][D + 2];
-  const int t0 = blockIdx.x * 64, bh = blockIdx.y, tid = threadIdx.x;
-  const uint16_t* vb = v + (size_t)bh * N * D;
-  constexpr int UPR = D / 8;
-  for (int i = tid; i < 64 * UPR; i += 256) {
-    const int r = i / UPR, cu = i % UPR;
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (t0 + r < N) raw = *reinterpret_cast<const uint4*>(vb + (size_t)(t0 + r) * D + cu * 8);
-    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) tile[r][cu * 8 + j] = h[j];
-  }
-  __syncthreads();
-  // thread -> (channel d, 8 consecutive stored positions): one 16-byte store
-  for (int i = tid; i < D * 8; i += 256) {
-    const int d = i / 8, p0 = (i % 8) * 8;
-    uint16_t o[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) o[j] = tile[vt_pos(p0 + j)][d];
-    uint4 w;
-    w.x = o[0] | ((uint32_t)o[1] << 16); w.y = o[2] | ((uint32_t)o[3] << 16);
-    w.z = o[4] | ((uint32_t)o[5] << 16); w.w = o[6] | ((uint32_t)o[7] << 16);
-    *reinterpret_cast<uint4*>(vt + ((size_t)bh * D + d) * Np + t0 + p0) = w;
-  }
+// The A operands (V^T) of one K-step for two channel blocks: per block two
+// transposing reads 8 keys apart, at LDS byte addresses a + OFF and a + OFF + 8
+// rows.  One asm block with its own wait: for the builtin the compiler first
+// waits for every direct-to-LDS load in flight (see sage_common.h).
+template <int OFF, int OFF8>
+__device__ __forceinline__ void vt_read2(uint32_t a0, uint32_t a1, v8bf& r0, v8bf& r1) {
+  v2u x0, x1, x2, x3;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4 offset:%6\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+      "ds_read_b64_tr_b16 %2, %5 offset:%6\n\tds_read_b64_tr_b16 %3, %5 offset:%7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3)
+      : "v"(a0), "v"(a1), "n"(OFF), "n"(OFF8)
+      : "memory");
+  r0 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x0, x1, 0, 1, 2, 3));
+  r1 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x2, x3, 0, 1, 2, 3));
 }
-
-template <int D>
-struct Bf16Stage {
-  using T = Bf16Tile<D>;
-  v4i k[T::KPT], v[T::VPT];
-  __device__ __forceinline__ void load(const uint16_t* __restrict__ kg, const uint16_t* __restrict__ vtg, long long bh,
-                                       int N, int Np, int kb, int tid) {
-#pragma unroll
-    for (int i = 0; i < T::KPT; ++i) {
-      const int u = tid + 256 * i;
-      const int row = u / T::KCH, ch = u % T::KCH;
-      const int key = min(kb + row, N - 1);          // rows past N repeat a valid key (masked later)
-      k[i] = *reinterpret_cast<const v4i*>(kg + ((size_t)bh * N + key) * D + ch * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < T::VPT; ++i) {
-      const int u = tid + 256 * i;
-      const int d = u / T::VCH, ch = u % T::VCH;
-      v[i] = *reinterpret_cast<const v4i*>(vtg + ((size_t)bh * D + d) * Np + kb + ch * 8);
-    }
-  }
-  __device__ __forceinline__ void store(uint8_t* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < T::KPT; ++i) {
-      const int u = tid + 256 * i;
-      const int row = u / T::KCH, ch = u % T::KCH;
-      *reinterpret_cast<v4i*>(lds + T::K_OFF + row * T::KROW + bswz<T::KCH>(row, ch) * 16) = k[i];
-    }
-#pragma unroll
-    for (int i = 0; i < T::VPT; ++i) {
-      const int u = tid + 256 * i;
-      const int row = u / T::VCH, ch = u % T::VCH;
-      *reinterpret_cast<v4i*>(lds + T::V_OFF + row * T::VROW + bswz<T::VCH>(row, ch) * 16) = v[i];
-    }
-  }
-};
-
+// The same for four channel blocks, with one wait.
+template <int OFF, int OFF8>
+__device__ __forceinline__ void vt_read4(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, v8bf& r0, v8bf& r1, v8bf& r2,
+                                         v8bf& r3) {
+  v2u x0, x1, x2, x3, x4, x5, x6, x7;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8 offset:%12\n\tds_read_b64_tr_b16 %1, %8 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %2, %9 offset:%12\n\tds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %4, %10 offset:%12\n\tds_read_b64_tr_b16 %5, %10 offset:%13\n\t"
+      "ds_read_b64_tr_b16 %6, %11 offset:%12\n\tds_read_b64_tr_b16 %7, %11 offset:%13\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7)
+      : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "n"(OFF), "n"(OFF8)
+      : "memory");
+  r0 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x0, x1, 0, 1, 2, 3));
+  r1 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x2, x3, 0, 1, 2, 3));
+  r2 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x4, x5, 0, 1, 2, 3));
+  r3 = __builtin_bit_cast(v8bf, __builtin_shufflevector(x6, x7, 0, 1, 2, 3));
+}
 
 template <int D, bool CAUSAL, bool OUT_F32>
-__global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                                                           const uint16_t* __restrict__ vt, void* __restrict__ o,
-                                                           int BH, int N, int Np, int nqt, float c2) {
-  using T = Bf16Tile<D>;
+__global__ __launch_bounds__(64 * BW, 2) void attn_bf16_kernel(const uint16_t* __restrict__ q,
+                                                               const uint16_t* __restrict__ k,
+                                                               const uint16_t* __restrict__ v, void* __restrict__ o,
+                                                               int BH, int N, int nqt, float c2) {
   constexpr int NSUB = BK / 32;    // 2 key subtiles
   constexpr int NKS = D / 16;      // QK K-steps
   constexpr int NPK = BK / 16;     // PV K-steps
   constexpr int NDB = D / 32;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int ROW = D * 2, CH = ROW / 16;            // bytes and chunks per key row
+  constexpr int TB = BK * ROW;                         // bytes of a K (or V) tile
+  __shared__ __attribute__((aligned(16))) uint8_t lds[4 * TB];   // stage: K tile, V tile
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, hi = lane >> 5;
 
   const int total = nqt * BH;
@@ -110,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t* __res
   const long long bh = lin / nqt;
   int qt = lin % nqt;
   if (CAUSAL) qt = nqt - 1 - qt;
-  const int q0 = qt * BQ, qw = q0 + wave * 32, qi = qw + col;
+  const int q0 = qt * (32 * BW), qw = q0 + wave * 32, qi = qw + col;
 
   v4i qreg[NKS];
   {
@@ -120,102 +100,125 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t* __res
     for (int s = 0; s < NKS; ++s) qreg[s] = *reinterpret_cast<const v4i*>(qrow + 16 * s + 8 * hi);
   }
   int ntiles = (N + BK - 1) / BK;
-  if (CAUSAL) ntiles = min(ntiles, min(q0 + BQ - 1, N - 1) / BK + 1);
+  if (CAUSAL) ntiles = min(ntiles, min(q0 + 32 * BW - 1, N - 1) / BK + 1);
 
-  // per-lane V^T operand offsets (row col of each 32-row block, chunk 2u + hi)
-  int vo[NPK];
+  // Tile loads (see sage_common.h): job J covers 1 KiB of a tile (JR rows), wave
+  // J % BW; lane l fills LDS chunk l of the job, which holds the swizzled
+  // logical chunk of its row.  Rows past N read zero (those keys are masked).
+  constexpr int JR = 1024 / ROW, NJ = BK / JR, JW = (NJ + BW - 1) / BW;
+  uint32_t klo[JW], vlo[JW];
 #pragma unroll
-  for (int u = 0; u < NPK; ++u) vo[u] = T::V_OFF + col * T::VROW + bswz<T::VCH>(col, 2 * u + hi) * 16;
+  for (int i = 0; i < JW; ++i) {
+    const int r = (wave + BW * i) * JR + lane / CH;
+    klo[i] = (uint32_t)(r * ROW + bswz<CH>(r, lane % CH) * 16);
+    vlo[i] = (uint32_t)(r * ROW + vswz<D>(r, lane % CH) * 16);
+  }
+  const uint8_t* kbase = reinterpret_cast<const uint8_t*>(k) + (size_t)bh * N * ROW;
+  const uint8_t* vbase = reinterpret_cast<const uint8_t*>(v) + (size_t)bh * N * ROW;
+  auto issue = [&](int j, int stage) {
+    const int kb = j * BK;
+    uint8_t* L = lds + stage * 2 * TB;
+    const uint32_t bytes = (uint32_t)min(N - kb, BK) * ROW;
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase + (size_t)kb * ROW, bytes), rv = make_rsrc(vbase + (size_t)kb * ROW, bytes);
+#pragma unroll
+    for (int i = 0; i < JW; ++i)
+      if (NJ % BW == 0 || wave + BW * i < NJ) {
+        buf_load16(rk, klo[i], 0u, L + (wave + BW * i) * 1024);
+        buf_load16(rv, vlo[i], 0u, L + TB + (wave + BW * i) * 1024);
+      }
+  };
+
+  // V^T operand address: this lane of its 16-lane group reads key 4 hi + (lane % 16) / 4 of a
+  // K-step, channels [32db + 16 (lane / 16 % 2) + 4 (lane % 4), +4)
+  uint32_t vo[NDB];
+  {
+    const uint32_t l0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lds;
+    const int r = 4 * hi + (lane & 15) / 4, c0 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) vo[db] = l0 + TB + r * ROW + vswz<D>(r, 4 * db + c0) * 16 + 8 * (lane & 1);
+  }
 
   v16f oacc[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db) oacc[db] = v16f{};
   float m = -INFINITY, l = 0.0f;
 
-  Bf16Stage<D> stg;
-  stg.load(k, vt, bh, N, Np, 0, tid);
-  stg.store(lds[0], tid);
-  __syncthreads();
-
-  auto tile = [&](auto BUF_, int j) {
-    constexpr int buf = decltype(BUF_)::value;
-    const uint8_t* L = lds[buf];
+  issue(0, 0);
+  for (int j = 0; j < ntiles; ++j) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's loads of tile j have landed
+    __syncthreads();                                   // everyone's; every wave is past tile j - 1
+    if (j + 1 < ntiles) issue(j + 1, (j + 1) & 1);
+    const uint8_t* L = lds + (j & 1) * 2 * TB;
     const int kb = j * BK;
-    const bool more = j + 1 < ntiles;
-    if (more) stg.load(k, vt, bh, N, Np, kb + BK, tid);
-    if (!CAUSAL || kb <= qw + 31) {
-      v16f sacc[NSUB];
+    if (CAUSAL && kb > qw + 31) continue;
+    v16f sacc[NSUB];
 #pragma unroll
-      for (int t = 0; t < NSUB; ++t) {
-        const int row = 32 * t + col;
-        v16f acc = v16f{};
+    for (int t = 0; t < NSUB; ++t) {
+      const int row = 32 * t + col;
+      v16f acc = v16f{};
 #pragma unroll
-        for (int s = 0; s < NKS; ++s) {
-          const v4i a = *reinterpret_cast<const v4i*>(L + T::K_OFF + row * T::KROW + bswz<T::KCH>(row, 2 * s + hi) * 16);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a), as_bf(qreg[s]), acc, 0, 0, 0);
-        }
-        sacc[t] = acc;
+      for (int s = 0; s < NKS; ++s) {
+        const v4i a = *reinterpret_cast<const v4i*>(L + row * ROW + bswz<CH>(row, 2 * s + hi) * 16);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a), as_bf(qreg[s]), acc, 0, 0, 0);
       }
-      if ((kb + BK > N) || (CAUSAL && kb + BK - 1 > qw)) {
-#pragma unroll
-        for (int t = 0; t < NSUB; ++t)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int key = kb + 32 * t + 8 * (v >> 2) + 4 * hi + (v & 3);
-            if (!(key < N && (!CAUSAL || key <= qi))) sacc[t][v] = -INFINITY;
-          }
-      }
-      float x = sacc[0][0];
+      sacc[t] = acc;
+    }
+    if ((kb + BK > N) || (CAUSAL && kb + BK - 1 > qw)) {
+      // element (t, v) is key kb + 4 hi + c with c = 32t + 8 (v >> 2) + (v & 3), kept iff
+      // c < rem: the sign bit of c - rem turns -inf into the bound +inf for kept keys
+      const int rem = (CAUSAL ? min(N, qi + 1) : N) - kb - 4 * hi;
 #pragma unroll
       for (int t = 0; t < NSUB; ++t)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) x = __builtin_fmaxf(x, sacc[t][v]);
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-      const float tmax = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      const float m_new = __builtin_fmaxf(m, tmax);
-      const float mc = m_new * c2;
-      const float alpha = __builtin_amdgcn_exp2f(m * c2 - mc);      // 0 on the first tile
-      float ps[2] = {0.0f, 0.0f};
-      v4i pk[NPK];
-#pragma unroll
-      for (int u = 0; u < NPK; ++u) {
-        const int t = u >> 1, base = 8 * (u & 1);
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][base + 2 * i], c2, -mc));
-          const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][base + 2 * i + 1], c2, -mc));
-          ps[i & 1] += p0;
-          ps[i & 1] += p1;
-          typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-          const v2bf pb = {(__bf16)p0, (__bf16)p1};
-          w[i] = __builtin_bit_cast(uint32_t, pb);
+        for (int e = 0; e < 16; ++e) {
+          const int c = 32 * t + 8 * (e >> 2) + (e & 3);
+          sacc[t][e] = smin(sacc[t][e], __uint_as_float(0xFF800000u ^ ((uint32_t)(c - rem) & 0x80000000u)));
         }
-        pk[u] = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      }
-      l = l * alpha + (ps[0] + ps[1]);
-      // rescale only when some row's max moved (alpha == 1 is an exact no-op)
-      if (__ballot(alpha != 1.0f) != 0) {
+    }
+    float x = sacc[0][0];
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+    for (int t = 0; t < NSUB; ++t)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
-      }
+      for (int e = (t == 0 ? 1 : 0); e < 16; ++e) x = smax(x, sacc[t][e]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float m_new = smax(m, smax(__uint_as_float(sw[0]), __uint_as_float(sw[1])));
+    const float mc = m_new * c2;
+    const float alpha = __builtin_amdgcn_exp2f(m * c2 - mc);      // 0 on the first tile
+    m = m_new;
+    // rescale only when some row's max moved (alpha == 1 is an exact no-op)
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int u = 0; u < NPK; ++u) {
-          const v4i a = *reinterpret_cast<const v4i*>(L + vo[u] + 32 * db * T::VROW);
-          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a), as_bf(pk[u]), oacc[db], 0, 0, 0);
-        }
-      m = m_new;
+        for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
     }
-    if (more) stg.store(lds[buf ^ 1], tid);
-    __syncthreads();
-  };
-  for (int j = 0; j < ntiles; j += 2) {
-    tile(ic<0>{}, j);
-    if (j + 1 < ntiles) tile(ic<1>{}, j + 1);
+    uint32_t va[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) va[db] = vo[db] + (uint32_t)((j & 1) * 2 * TB);
+    float ps[2] = {0.0f, 0.0f};
+    static_for<NPK>([&](auto U_) {
+      constexpr int u = decltype(U_)::value, t = u >> 1, base = 8 * (u & 1);
+      v8bf a[NDB];
+      constexpr int OFF = 16 * u * ROW, OFF8 = OFF + 8 * ROW;
+      if constexpr (NDB == 4) vt_read4<OFF, OFF8>(va[0], va[1], va[2], va[3], a[0], a[1], a[2], a[3]);
+      else vt_read2<OFF, OFF8>(va[0], va[1], a[0], a[1]);
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][base + 2 * i], c2, -mc));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[t][base + 2 * i + 1], c2, -mc));
+        ps[i & 1] += p0;
+        ps[i & 1] += p1;
+        typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+        const v2bf pb = {(__bf16)p0, (__bf16)p1};
+        w[i] = __builtin_bit_cast(uint32_t, pb);
+      }
+      const v4i pk = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[db], as_bf(pk), oacc[db], 0, 0, 0);
+    });
+    l = l * alpha + (ps[0] + ps[1]);
   }
 
   const float ltot = l + __shfl_xor(l, 32, 64);
@@ -239,30 +242,22 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_kernel(const uint16_t* __res
   }
 }
 
-hipError_t launch_transpose_v_bf16(const void* v, void* vt, int BH, int N, int Np, int D, hipStream_t st) {
-  if (D == 128)
-    hipLaunchKernelGGL((transpose_v_kernel<128>), dim3(Np / 64, BH), dim3(256), 0, st, (const uint16_t*)v, (uint16_t*)vt, N, Np);
-  else
-    hipLaunchKernelGGL((transpose_v_kernel<64>), dim3(Np / 64, BH), dim3(256), 0, st, (const uint16_t*)v, (uint16_t*)vt, N, Np);
-  return hipGetLastError();
-}
-
 template <int D, bool CAUSAL, bool OUT_F32>
-static hipError_t launch_bf16_t(const void* q, const void* k, const void* vt, void* o, int BH, int N, int Np, float c2,
+static hipError_t launch_bf16_t(const void* q, const void* k, const void* v, void* o, int BH, int N, float c2,
                                 hipStream_t st) {
-  const int nqt = (N + BQ - 1) / BQ;
-  hipLaunchKernelGGL((attn_bf16_kernel<D, CAUSAL, OUT_F32>), dim3((unsigned)(nqt * BH)), dim3(256), 0, st,
-                     (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)vt, o, BH, N, Np, nqt, c2);
+  const int nqt = (N + 32 * BW - 1) / (32 * BW);
+  hipLaunchKernelGGL((attn_bf16_kernel<D, CAUSAL, OUT_F32>), dim3((unsigned)(nqt * BH)), dim3(64 * BW), 0, st,
+                     (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, o, BH, N, nqt, c2);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bf16(const void* q, const void* k, const void* vt, void* o, int BH, int N, int Np, int D,
-                            bool causal, bool out_f32, float c2, hipStream_t st) {
-#define SAGE_B(DD)                                                                                        \
-  if (causal) return out_f32 ? launch_bf16_t<DD, true, true>(q, k, vt, o, BH, N, Np, c2, st)              \
-                             : launch_bf16_t<DD, true, false>(q, k, vt, o, BH, N, Np, c2, st);            \
-  return out_f32 ? launch_bf16_t<DD, false, true>(q, k, vt, o, BH, N, Np, c2, st)                         \
-                 : launch_bf16_t<DD, false, false>(q, k, vt, o, BH, N, Np, c2, st)
+hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, int BH, int N, int D, bool causal,
+                            bool out_f32, float c2, hipStream_t st) {
+#define SAGE_B(DD)                                                                        \
+  if (causal) return out_f32 ? launch_bf16_t<DD, true, true>(q, k, v, o, BH, N, c2, st)   \
+                             : launch_bf16_t<DD, true, false>(q, k, v, o, BH, N, c2, st); \
+  return out_f32 ? launch_bf16_t<DD, false, true>(q, k, v, o, BH, N, c2, st)              \
+                 : launch_bf16_t<DD, false, false>(q, k, v, o, BH, N, c2, st)
   if (D == 128) { SAGE_B(128); }
   SAGE_B(64);
 #undef SAGE_B

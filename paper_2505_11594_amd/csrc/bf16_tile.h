@@ -1,6 +1,6 @@
-// bf16 tile layout in LDS shared by the bf16 and the NV16 attention kernels:
-// a K tile [BKV rows][D bf16] and a V^T tile [D rows][BKV bf16], each row cut
-// into 16-byte chunks that are XOR-swizzled against LDS bank conflicts.
+// 16-bit tile layout in LDS of the NV16 attention kernel (the bf16 kernel shares
+// the K tile's swizzle): a K tile [BKV rows][D] and a V^T tile [D rows][BKV],
+// each row cut into 16-byte chunks that are XOR-swizzled against LDS bank conflicts.
 #pragma once
 #include "sage_common.h"
 
@@ -15,8 +15,6 @@ struct Bf16TileT {
   static constexpr int K_OFF = 0;
   static constexpr int V_OFF = BKV * KROW;
   static constexpr int BYTES = V_OFF + D * VROW;
-  static constexpr int KU = BKV * KCH, VU = D * VCH;
-  static constexpr int KPT = KU / 256, VPT = VU / 256;
 };
 
 // 16-byte chunk swizzle: lanes of one operand read sit on consecutive rows at

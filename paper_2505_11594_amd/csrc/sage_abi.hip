@@ -27,9 +27,8 @@ hipError_t launch_attn_nv16(const void* qc, const void* qs, const void* kc, cons
                             const void* vs, void* kv16, const float* qkb, void* o, int BH, int N, int Np, int D,
                             int bkv, bool causal, int out, float c2, float logR, hipStream_t st);
 size_t nv16_expand_bytes(int BH, int Np, int D);
-hipError_t launch_attn_bf16(const void* q, const void* k, const void* vt, void* o, int BH, int N, int Np, int D,
-                            bool causal, bool out_f32, float c2, hipStream_t st);
-hipError_t launch_transpose_v_bf16(const void* v, void* vt, int BH, int N, int Np, int D, hipStream_t st);
+hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, int BH, int N, int D, bool causal,
+                            bool out_f32, float c2, hipStream_t st);
 hipError_t launch_quant_i8(const void* x, const float* mu, void* codes, float* scales, int BH, int N, int Nout,
                            int D, int R, int role, bool bf16, hipStream_t st);
 hipError_t launch_attn_int8(const void* qc, const float* qs, const void* kc, const float* ks, const void* vc,
@@ -522,17 +521,8 @@ int sage_attn_bf16_fwd(const void* q, const void* k, const void* v, void* o, int
   if (!(flags & SAGE_IN_BF16)) return SAGE_ERR_INVALID_ARG;
   int rc = attn_args(q, k, v, o, B, H, N, D, causal, flags);
   if (rc != SAGE_OK) return rc;
-  const int Np = pad128(N);
-  const size_t bytes = (size_t)B * H * D * Np * 2;
-  void* vt = nullptr;
-  if (hipMallocAsync(&vt, bytes, stream) != hipSuccess) return SAGE_ERR_HIP;
-  hipError_t e = sage::launch_transpose_v_bf16(v, vt, B * H, N, Np, D, stream);
-  if (e == hipSuccess)
-    e = sage::launch_attn_bf16(q, k, vt, o, B * H, N, Np, D, causal != 0, (flags & SAGE_OUT_F32) != 0, softmax_c2(D),
-                               stream);
-  rc = hip_status(e);
-  if (hipFreeAsync(vt, stream) != hipSuccess && rc == SAGE_OK) rc = SAGE_ERR_HIP;
-  return rc;
+  return hip_status(sage::launch_attn_bf16(q, k, v, o, B * H, N, D, causal != 0, (flags & SAGE_OUT_F32) != 0,
+                                           softmax_c2(D), stream));
 }
 
 int sage_quant_int8_sizes(int role, int B, int H, int N, int D, unsigned flags, size_t* codes_bytes,
