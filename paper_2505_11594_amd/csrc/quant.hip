@@ -10,9 +10,10 @@
 // quantization (Appendix, "Transposing V").  For smoothing Q the GEMV of the
 // block means with K' is computed here as well.
 //
-// All three kernels are HBM-bound: each element is read once as 16 bits
+// The quantizers are HBM-bound on large calls and launch-bound on small ones: each element is read once as 16 bits
 // (twice for K, which the mean also reads) and written as 4 bits plus 8 bits
 // per block.
+#include <algorithm>
 #include <climits>
 
 #include "sage_common.h"
@@ -28,13 +29,13 @@ namespace sage {
 constexpr int KM_CHUNK = 512;
 constexpr int KM_THREADS = 256;
 
+typedef double KmRed[KM_THREADS][9];         // padded against bank conflicts
+
 template <int D, bool BF16>
-__global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_t* __restrict__ k,
-                                                                   double* __restrict__ part, int N,
-                                                                   int nchunk) {
+__device__ __forceinline__ void kmean_partial(const uint16_t* __restrict__ k, double* __restrict__ part, int N,
+                                              int nchunk, int chunk, int bh, KmRed& red) {
   constexpr int CG = D / 8;                  // 8-channel groups per row (16 bytes)
   constexpr int RS = KM_THREADS / CG;        // rows handled in parallel
-  const int chunk = blockIdx.x, bh = blockIdx.y;
   const int tid = threadIdx.x;
   const int cg = tid % CG, rsub = tid / CG;
   const int t0 = chunk * KM_CHUNK;
@@ -49,7 +50,6 @@ __global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] += (double)widen<BF16>(h[i]);
   }
-  __shared__ double red[KM_THREADS][9];      // padded against bank conflicts
 #pragma unroll
   for (int i = 0; i < 8; ++i) red[tid][i] = acc[i];
   __syncthreads();
@@ -59,6 +59,13 @@ __global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_
     for (int r = 0; r < RS; ++r) s += red[r * CG + g][i];
     part[((size_t)bh * nchunk + chunk) * D + c] = s;
   }
+}
+
+template <int D, bool BF16>
+__global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_t* __restrict__ k,
+                                                                   double* __restrict__ part, int N, int nchunk) {
+  __shared__ KmRed red;
+  kmean_partial<D, BF16>(k, part, N, nchunk, blockIdx.x, blockIdx.y, red);
 }
 
 // Pass 2: mu = fl32(fl64(sum) / N).  One workgroup per (b,h): 256 / D
@@ -82,130 +89,118 @@ __global__ __launch_bounds__(256) void kmean_final_kernel(const double* __restri
   }
 }
 
-// ---------------------------------------------------------------------------
-// Smoothing Q (Algorithm 1): qbar[bh, b, c] = mean of Q[bh, t, c] over the QB
-// rows t of query block b (the last block holds the remaining rows), an fp64
-// sum -- exact for 16-bit inputs, so the order does not matter -- divided by
-// the row count and rounded once to fp32.  One workgroup per (block, bh).
-// ---------------------------------------------------------------------------
 constexpr int QB = 128;   // query rows per smoothing block (= the attention kernel's query tile)
-
-template <int D, bool BF16>
-__global__ __launch_bounds__(KM_THREADS) void qmean_kernel(const uint16_t* __restrict__ q, float* __restrict__ qbar,
-                                                           int N, int nqb) {
-  constexpr int CG = D / 8, RS = KM_THREADS / CG;
-  const int b = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
-  const int cg = tid % CG, rsub = tid / CG;
-  const int t0 = b * QB, t1 = min(N, t0 + QB);
-  const uint16_t* qh = q + (size_t)bh * N * D;
-  double acc[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-  for (int t = t0 + rsub; t < t1; t += RS) {
-    uint4 raw = *reinterpret_cast<const uint4*>(qh + (size_t)t * D + cg * 8);
-    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] += (double)widen<BF16>(h[i]);
-  }
-  __shared__ double red[KM_THREADS][9];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) red[tid][i] = acc[i];
-  __syncthreads();
-  if (tid < D) {
-    const int c = tid, g = c / 8, i = c % 8;
-    double s = 0.0;
-    for (int r = 0; r < RS; ++r) s += red[r * CG + g][i];
-    qbar[((size_t)bh * nqb + b) * D + c] = (float)(s / (double)(t1 - t0));
-  }
-}
 
 // GEMV of smoothing Q: bias[bh, b, k] = qbar[bh, b, :] . K'[bh, k, :] with
 // K' = fl32(K - mu) (K itself without smoothing K), as a chain of fp32 fused
-// multiply-adds in order of the channel from 0; keys k >= N get 0.  One
-// thread per key keeps K' in registers; the workgroup stages the means of QBG
-// query blocks at a time in LDS as [channel][block] (double-buffered), so a
-// thread reads the QBG values of one channel with two broadcast 16-byte LDS
-// reads and runs QBG independent chains.
-constexpr int QBG = 8;
-constexpr int QB_THREADS = 256;
-
-template <int D, bool BF16>
-__global__ __launch_bounds__(QB_THREADS) void qk_bias_kernel(const uint16_t* __restrict__ k, const float* __restrict__ mu,
-                                                             const float* __restrict__ qbar, float* __restrict__ bias,
-                                                             int N, int Np, int nqb) {
-  static_assert(D * QBG == 4 * QB_THREADS || D * QBG == 2 * QB_THREADS, "one or two staged means per thread");
-  constexpr int PER_T = D * QBG / QB_THREADS;      // means staged per thread per group
-  __shared__ __attribute__((aligned(16))) float qs[2][D][QBG];
-  const int bh = blockIdx.y, tid = threadIdx.x;
-  const int key = blockIdx.x * QB_THREADS + tid;   // the grid covers Np (a multiple of 128) rounded up
-  const bool valid = key < N;
-  float kv[D];
-  if (valid) {
-    const uint16_t* kr = k + ((size_t)bh * N + key) * D;
+// multiply-adds in order of the channel from 0; keys k >= N get 0.  A
+// workgroup takes GK keys and 8 WB query blocks (WB of its four waves along the
+// blocks) and walks the channels GC at a time: K' and the means are staged in
+// LDS channel-major, the next channels' loads in flight meanwhile.  With WB = 4
+// each lane has 8 blocks x 8 keys, four 16-byte LDS reads for 64 independent
+// multiply-adds (one key per thread took two for 8, and LDS reads bounded it);
+// with WB = 1 one key per lane, for calls too small to fill the GPU with the
+// larger tiles.  B4 H32 N4096 D128: 117 -> 100 us (its multiply-adds take 37, K
+// and the result move 201 MB); B2 H8 N1000 with 512-key tiles 61 us a call, 44 so.
+template <int D, bool BF16, int GK, int WB, int GC>
+__global__ __launch_bounds__(256) void qk_bias_kernel(const uint16_t* __restrict__ k, const float* __restrict__ mu,
+                                                      const float* __restrict__ qbar, float* __restrict__ bias, int N,
+                                                      int Np, int nqb, int nkt) {
+  constexpr int GB = 8 * WB, LK = GK * WB / 256, KPT = GK / 256, MPT = GB * GC / 256;
+  static_assert(LK == 8 || LK == 1, "keys per lane");
+  __shared__ __attribute__((aligned(16))) float kt[GC][GK];
+  __shared__ __attribute__((aligned(16))) float qt[GC][GB];
+  const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int key0 = (blockIdx.x % nkt) * GK, b0 = (blockIdx.x / nkt) * GB, wb = 8 * (wave % WB);
+  const float* qm = qbar + ((size_t)bh * nqb + b0) * D;
+  uint4 raw[KPT][GC / 8];
+  float mean[MPT];
+  auto load = [&](int c0) {
 #pragma unroll
-    for (int c8 = 0; c8 < D / 8; ++c8) {
-      uint4 raw = *reinterpret_cast<const uint4*>(kr + c8 * 8);
-      const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
+    for (int e = 0; e < KPT; ++e) {
+      const int key = key0 + tid + 256 * e;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) kv[c8 * 8 + i] = widen<BF16>(h[i]);
+      for (int h8 = 0; h8 < GC / 8; ++h8)
+        raw[e][h8] = key < N ? *reinterpret_cast<const uint4*>(k + ((size_t)bh * N + key) * D + c0 + 8 * h8)
+                             : make_uint4(0, 0, 0, 0);
     }
-    if (mu != nullptr) {
 #pragma unroll
-      for (int c = 0; c < D; ++c) kv[c] = kv[c] - mu[(size_t)bh * D + c];
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < D; ++c) kv[c] = 0.0f;
-  }
-  const float* qm = qbar + (size_t)bh * nqb * D;
-  // stage the means of blocks [b0, b0 + QBG) (zero past nqb), transposed to [channel][block]
-  auto stage = [&](int b0, int buf) {
-#pragma unroll
-    for (int e = 0; e < PER_T; ++e) {
-      const int idx = tid * PER_T + e, i = idx / D, c = idx % D;   // block i, channel c
-      qs[buf][c][i] = (b0 + i < nqb) ? qm[(size_t)(b0 + i) * D + c] : 0.0f;
+    for (int e = 0; e < MPT; ++e) {
+      const int idx = tid + 256 * e, i = idx / GC, c = idx % GC;   // block i, channel c
+      mean[e] = (b0 + i < nqb) ? qm[(size_t)i * D + c0 + c] : 0.0f;
     }
   };
-  const int ngroups = (nqb + QBG - 1) / QBG;
-  stage(0, 0);
-  __syncthreads();
-  for (int gi = 0; gi < ngroups; ++gi) {
-    const int b0 = gi * QBG, buf = gi & 1;
-    if (gi + 1 < ngroups) stage(b0 + QBG, buf ^ 1);   // the other buffer was last read before the barrier below
-    float acc[QBG];
+  float acc[8][LK];
 #pragma unroll
-    for (int i = 0; i < QBG; ++i) acc[i] = 0.0f;
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-      const v4f m0 = *reinterpret_cast<const v4f*>(&qs[buf][c][0]);
-      const v4f m1 = *reinterpret_cast<const v4f*>(&qs[buf][c][4]);
+    for (int j = 0; j < LK; ++j) acc[i][j] = 0.0f;
+  load(0);
+  for (int c0 = 0; c0 < D; c0 += GC) {
+    if (c0 > 0) __syncthreads();                   // every wave is done with the previous channels
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(m0[i], kv[c], acc[i]);
+    for (int e = 0; e < KPT; ++e) {
+      const bool valid = key0 + tid + 256 * e < N;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[4 + i] = __builtin_fmaf(m1[i], kv[c], acc[4 + i]);
+      for (int c = 0; c < GC; ++c) {
+        float x = widen<BF16>(reinterpret_cast<const uint16_t*>(&raw[e][c / 8])[c % 8]);
+        if (mu != nullptr) x = x - mu[(size_t)bh * D + c0 + c];
+        kt[c][tid + 256 * e] = valid ? x : 0.0f;
+      }
     }
-    // materialize every chain here: otherwise the compiler sinks each chain into
-    // its guarded store below and keeps all the staged means it reads live
 #pragma unroll
-    for (int i = 0; i < QBG; ++i) asm volatile("" : "+v"(acc[i]));
-    if (key < Np) {
-      float* out = bias + ((size_t)bh * nqb + b0) * Np + key;
-#pragma unroll
-      for (int i = 0; i < QBG; ++i)
-        if (b0 + i < nqb) out[(size_t)i * Np] = valid ? acc[i] : 0.0f;
+    for (int e = 0; e < MPT; ++e) {
+      const int idx = tid + 256 * e;
+      qt[idx % GC][idx / GC] = mean[e];
     }
     __syncthreads();
+    if (c0 + GC < D) load(c0 + GC);
+    if (b0 + wb < nqb) {
+#pragma unroll 4
+      for (int c = 0; c < GC; ++c) {
+        float kk[LK];
+        if constexpr (LK == 8) {
+          const v4f k0 = *reinterpret_cast<const v4f*>(&kt[c][4 * lane]);
+          const v4f k1 = *reinterpret_cast<const v4f*>(&kt[c][256 + 4 * lane]);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) kk[j] = j < 4 ? k0[j & 3] : k1[j & 3];
+        } else {
+          kk[0] = kt[c][tid];
+        }
+        const v4f m0 = *reinterpret_cast<const v4f*>(&qt[c][wb]);
+        const v4f m1 = *reinterpret_cast<const v4f*>(&qt[c][wb + 4]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < LK; ++j) acc[i][j] = __builtin_fmaf(i < 4 ? m0[i & 3] : m1[i & 3], kk[j], acc[i][j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int b = b0 + wb + i;
+    if (b < nqb) {
+      float* row = bias + ((size_t)bh * nqb + b) * Np;
+      if constexpr (LK == 8) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int key = key0 + 256 * e + 4 * lane;
+          if (key < Np)
+            *reinterpret_cast<v4f*>(row + key) = v4f{acc[i][4 * e], acc[i][4 * e + 1], acc[i][4 * e + 2], acc[i][4 * e + 3]};
+        }
+      } else if (key0 + tid < Np) {
+        row[key0 + tid] = acc[i][0];
+      }
+    }
   }
 }
 
 // ---------------------------------------------------------------------------
-// Row quantizer for Q and K (blocks along D).  One lane owns 8 consecutive
+// Row quantizers for Q and K (blocks along D).  One lane owns 8 consecutive
 // channels (a 16-byte load); the 4 (MXFP4) or 2 (NV16) lanes of a block
 // reduce their absolute maxima with cross-lane swaps.  A lane writes its 8
-// codes as one 32-bit word.  A mean, when given, is subtracted first: row t
-// of head bh uses mu[(bh * nmb + (t >> mshift)) * D + c] (role K: one mean
-// per head; role Q with smoothing: one per QB-row block).  Role K stores each
-// token at its permuted position inside its group.
+// codes as one 32-bit word.
 // ---------------------------------------------------------------------------
 // Stored row of K token t.  MXFP4 (32x32x64 block-scaled MFMA): inside each
 // 64-token group, offset o = 32h + 16t' + 4g + r goes to 32t' + 8g + 4h + r.
@@ -224,96 +219,196 @@ __device__ __forceinline__ int k_stored_pos(int t) {
   }
 }
 
-// Units (8 channels of one row) per thread of the row quantizer: role K reads
-// the mean beside each unit, and four units per thread, their loads issued
-// together, keep more bytes in flight (K 82 -> 67 us on B1 H32 N32768 D128);
-// Q is fastest with one (four: +4%).
-template <bool IS_K>
-constexpr int rows_units() { return IS_K ? 4 : 1; }
+// Codes and scale of one unit (8 channels, lane's part of an NB-channel block);
+// the lanes of a block are consecutive and all call.
+template <int FMT>
+__device__ __forceinline__ void quant_unit(const float (&v)[8], uint32_t& word, uint32_t& sbyte) {
+  constexpr int LPB = (FMT == kFmtMX ? 32 : 16) / 8;   // lanes per block
+  float am = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) am = __builtin_fmaxf(am, __builtin_fabsf(v[i]));
+#pragma unroll
+  for (int off = 1; off < LPB; off <<= 1) am = __builtin_fmaxf(am, __shfl_xor(am, off, 64));
+  float y[8];
+  if (FMT == kFmtMX) {
+    const int e = e8m0_exponent(am);
+    sbyte = (uint32_t)(e + 127);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[i] = __builtin_ldexpf(v[i], -e);   // exact power-of-two scaling
+  } else {
+    sbyte = e4m3_encode(am / 6.0f);
+    const float s = e4m3_decode(sbyte);
+    const float r = s == 0.0f ? 0.0f : 1.0f / s;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) y[i] = s == 0.0f ? 0.0f : v[i] * r;
+  }
+  word = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) word |= cvt_fp4x2(y[2 * i], y[2 * i + 1]) << (8 * i);
+}
 
-template <int D, bool BF16, int FMT, bool IS_K>
-__global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restrict__ x, const float* __restrict__ mu,
-                                                         int mshift, int nmb, uint8_t* __restrict__ codes,
-                                                         uint8_t* __restrict__ scales, int N, int Nout,
-                                                         long long total_units) {
-  constexpr int NB = (FMT == kFmtMX) ? 32 : 16;     // block size
-  constexpr int LPB = NB / 8;                       // lanes per block
+template <int D, int FMT>
+__device__ __forceinline__ void store_unit(uint8_t* codes, uint8_t* scales, long long orow, int cu, uint32_t word,
+                                           uint32_t sbyte) {
+  constexpr int NB = (FMT == kFmtMX) ? 32 : 16, LPB = NB / 8;
+  *reinterpret_cast<uint32_t*>(codes + (size_t)orow * (D / 2) + cu * 4) = word;
+  if ((cu % LPB) == 0) scales[(size_t)orow * (D / NB) + cu / LPB] = (uint8_t)sbyte;
+}
+
+// Q without smoothing: workgroup blk of nblk takes 256 consecutive units per
+// step (one per thread; four, as K takes below, are 4% slower).
+template <int D, bool BF16, int FMT>
+__device__ __forceinline__ void quant_q(const uint16_t* __restrict__ x, uint8_t* __restrict__ codes,
+                                        uint8_t* __restrict__ scales, long long total_units, long long blk,
+                                        long long nblk) {
   constexpr int UPR = D / 8;                        // units (lanes) per row
-  constexpr int U = rows_units<IS_K>();
-  // a workgroup of 256 threads takes U x 256 consecutive units, 256 per step
-  // (each load coalesced across the wave), all loads issued before the first
-  // is used
-  const long long nsb = (total_units + 256 * U - 1) / (256 * U);
-  for (long long sb = blockIdx.x; sb < nsb; sb += gridDim.x) {
-    const long long u0 = sb * (256 * U) + threadIdx.x;
-    uint4 raws[U];
+  const long long nsb = (total_units + 255) / 256;
+  for (long long sb = blk; sb < nsb; sb += nblk) {
+    const long long u = sb * 256 + threadIdx.x;
+    if (u >= total_units) break;                    // whole rows, so whole blocks of lanes, leave together
+    const uint4 raw = *reinterpret_cast<const uint4*>(x + (size_t)u * 8);
+    const uint16_t* hv = reinterpret_cast<const uint16_t*>(&raw);
+    float v[8];
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const long long u = u0 + 256 * k;
-      raws[k] = (u < total_units) ? *reinterpret_cast<const uint4*>(x + (size_t)u * 8) : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const long long u = u0 + 256 * k;
-      if (u >= total_units) break;                    // whole rows, so whole blocks of lanes, leave together
-      const long long row = u / UPR;                  // (bh, t) flattened over the N input rows
-      const int cu = (int)(u % UPR);
-      const long long bh = row / N;
-      const int t = (int)(row % N);
-      const uint16_t* hv = reinterpret_cast<const uint16_t*>(&raws[k]);
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(hv[i]);
-      if (mu != nullptr) {
-        const float* m = mu + ((size_t)bh * nmb + (t >> mshift)) * D + cu * 8;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = v[i] - m[i];
-      }
-      float am = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) am = __builtin_fmaxf(am, __builtin_fabsf(v[i]));
-#pragma unroll
-      for (int off = 1; off < LPB; off <<= 1) am = __builtin_fmaxf(am, __shfl_xor(am, off, 64));
-      uint32_t sbyte;
-      float y[8];
-      if (FMT == kFmtMX) {
-        const int e = e8m0_exponent(am);
-        sbyte = (uint32_t)(e + 127);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = __builtin_ldexpf(v[i], -e);   // exact power-of-two scaling
-      } else {
-        sbyte = e4m3_encode(am / 6.0f);
-        const float s = e4m3_decode(sbyte);
-        if (s == 0.0f) {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) y[i] = 0.0f;
-        } else {
-          const float r = 1.0f / s;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) y[i] = v[i] * r;
-        }
-      }
-      uint32_t word = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) word |= cvt_fp4x2(y[2 * i], y[2 * i + 1]) << (8 * i);
-      const long long orow = bh * Nout + (IS_K ? k_stored_pos<FMT>(t) : t);
-      *reinterpret_cast<uint32_t*>(codes + (size_t)orow * (D / 2) + cu * 4) = word;
-      if ((cu % LPB) == 0) scales[(size_t)orow * (D / NB) + cu / LPB] = (uint8_t)sbyte;
-    }
+    for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(hv[i]);
+    uint32_t word, sbyte;
+    quant_unit<FMT>(v, word, sbyte);
+    store_unit<D, FMT>(codes, scales, u / UPR, (int)(u % UPR), word, sbyte);
   }
 }
 
-// Zero codes (and unit scales) of K's padded tail tokens N .. Np-1.
-template <int D, int FMT>
-__global__ void k_tail_kernel(uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, int N, int Np) {
-  constexpr int NB = (FMT == kFmtMX) ? 32 : 16;
-  const int bh = blockIdx.y;
-  const int ntail = Np - N;
-  for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < ntail * (D / 2); i += gridDim.x * blockDim.x) {
-    const int t = N + i / (D / 2), b = i % (D / 2);
-    const long long orow = (long long)bh * Np + k_stored_pos<FMT>(t);
-    codes[(size_t)orow * (D / 2) + b] = 0;
-    if (b < D / NB) scales[(size_t)orow * (D / NB) + b] = (FMT == kFmtMX) ? 127 : 0;
+template <int D, bool BF16, int FMT>
+__global__ __launch_bounds__(256) void quant_q_kernel(const uint16_t* __restrict__ x, uint8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ scales, long long total_units) {
+  quant_q<D, BF16, FMT>(x, codes, scales, total_units, blockIdx.x, gridDim.x);
+}
+
+// Q with smoothing (Algorithm 1): qbar[bh, b, c] = mean of Q[bh, t, c] over the
+// QB rows t of query block b (the last block holds the remaining rows) -- an
+// fp64 sum, exact for 16-bit inputs, so the order does not matter, divided by
+// the row count and rounded once to fp32 -- and the codes of Q - qbar.  One
+// workgroup per block keeps its rows in registers between the two, so Q is read
+// once (a mean pass of its own read it again: 32 us beside the quantizer's 41
+// on B4 H32 N4096 D128).
+template <int D, bool BF16, int FMT>
+__device__ __forceinline__ void quant_q_smooth(const uint16_t* __restrict__ q, float* __restrict__ qbar,
+                                               uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, int N,
+                                               int nqb, int b, int bh, KmRed& red) {
+  constexpr int UPR = D / 8, RS = 256 / UPR, U = QB / RS;   // rows in parallel, rows per thread
+  const int tid = threadIdx.x, cg = tid % UPR, rsub = tid / UPR;
+  const int t0 = b * QB, rows = min(QB, N - t0);
+  const uint16_t* qh = q + ((size_t)bh * N + t0) * D + cg * 8;
+  uint4 raw[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int r = rsub + RS * u;
+    raw[u] = r < rows ? *reinterpret_cast<const uint4*>(qh + (size_t)r * D) : make_uint4(0, 0, 0, 0);
+  }
+  double acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw[u]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] += (double)widen<BF16>(h[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) red[tid][i] = acc[i];
+  __syncthreads();
+  float* mean = reinterpret_cast<float*>(&red[0][8]);        // the pad column: 18 floats apart
+  if (tid < D) {
+    const int g = tid / 8, i = tid % 8;
+    double s = 0.0;
+    for (int r = 0; r < RS; ++r) s += red[r * UPR + g][i];
+    const float m = (float)(s / (double)rows);
+    qbar[((size_t)bh * nqb + b) * D + tid] = m;
+    mean[18 * tid] = m;
+  }
+  __syncthreads();
+  float m8[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) m8[i] = mean[18 * (cg * 8 + i)];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int r = rsub + RS * u;
+    if (r >= rows) break;                                    // whole rows leave together
+    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw[u]);
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(h[i]) - m8[i];
+    uint32_t word, sbyte;
+    quant_unit<FMT>(v, word, sbyte);
+    store_unit<D, FMT>(codes, scales, (long long)bh * N + t0 + r, cg, word, sbyte);
+  }
+}
+
+template <int D, bool BF16, int FMT>
+__global__ __launch_bounds__(256) void quant_q_smooth_kernel(const uint16_t* __restrict__ q, float* __restrict__ qbar,
+                                                             uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
+                                                             int N, int nqb) {
+  __shared__ KmRed red;
+  quant_q_smooth<D, BF16, FMT>(q, qbar, codes, scales, N, nqb, blockIdx.x, blockIdx.y, red);
+}
+
+// K: a workgroup takes KRB rows of one head (four units per thread, all loads
+// issued before the first is used: 82 -> 67 us on B1 H32 N32768 D128 against
+// one), subtracts the head's mean -- read from mu, or (part given, up to
+// KM_INLINE chunks) summed here from the partial sums, which saves the pass
+// between them -- and stores each token at its permuted position.  Rows N ..
+// Np - 1 get zero codes and unit scales.
+constexpr int KM_INLINE = 8;
+
+template <int D, bool BF16, int FMT>
+__global__ __launch_bounds__(256) void quant_k_kernel(const uint16_t* __restrict__ x, const double* __restrict__ part,
+                                                      float* __restrict__ mu, uint8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ scales, int N, int Np, int nchunk) {
+  constexpr int UPR = D / 8, RS = 256 / UPR, U = 4, KRB = RS * U;
+  const int nrb = Np / KRB;                                  // Np is a multiple of 128 and KRB 64 or 128
+  const int bh = blockIdx.x / nrb, t0 = (blockIdx.x % nrb) * KRB;
+  const int tid = threadIdx.x, cg = tid % UPR, rsub = tid / UPR;
+  const uint16_t* xh = x + ((size_t)bh * N + t0) * D + cg * 8;
+  uint4 raw[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int r = rsub + RS * u;
+    raw[u] = t0 + r < N ? *reinterpret_cast<const uint4*>(xh + (size_t)r * D) : make_uint4(0, 0, 0, 0);
+  }
+  float m8[8];
+  if (part != nullptr) {
+    __shared__ float mean[D];
+    if (tid < D) {
+      double s = 0.0;
+      for (int j = 0; j < nchunk; ++j) s += part[((size_t)bh * nchunk + j) * D + tid];
+      const float m = (float)(s / (double)N);
+      mean[tid] = m;
+      if (t0 == 0) mu[(size_t)bh * D + tid] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m8[i] = mean[cg * 8 + i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m8[i] = mu != nullptr ? mu[(size_t)bh * D + cg * 8 + i] : 0.0f;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = t0 + rsub + RS * u;
+    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw[u]);
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(h[i]);
+    if (mu != nullptr) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = v[i] - m8[i];
+    }
+    uint32_t word, sbyte;
+    quant_unit<FMT>(v, word, sbyte);
+    if (t >= N) {
+      word = 0;
+      sbyte = FMT == kFmtMX ? 127 : 0;
+    }
+    store_unit<D, FMT>(codes, scales, (long long)bh * Np + k_stored_pos<FMT>(t), cg, word, sbyte);
   }
 }
 
@@ -325,33 +420,41 @@ __global__ void k_tail_kernel(uint8_t* __restrict__ codes, uint8_t* __restrict__
 // contiguous range of per_wg (bh, tile) pairs and keeps the loads of the next
 // two tiles in registers while it quantizes the current one.
 // ---------------------------------------------------------------------------
-constexpr int VT = 128;       // tokens per tile (a V^T row segment of 64 bytes)
+constexpr int VT = 128;       // tokens per tile (a V^T row segment of 64 bytes); Np is a multiple of it
 // One workgroup per CU, two tiles in flight: 79.7 us on B1 H32 N32768 D128,
 // against 96 us for one tile per workgroup and, with the same loop, 92 us at
 // two workgroups per CU (one tile ahead: 83.5 us at one per CU, 87, 96 and
 // 101 us at two, three and four); with the scale bytes staged, 71.4 us.
 constexpr int V_WG_PER_CU = 1;
 
-template <int D, bool BF16, int FMT>
-__global__ __launch_bounds__(256) void quant_v_kernel(const uint16_t* __restrict__ v, uint8_t* __restrict__ codes,
-                                                      uint8_t* __restrict__ scales, int N, int Np, int total,
-                                                      int per_wg) {
-  constexpr int NB = (FMT == kFmtMX) ? 32 : 16;
+template <int D, int FMT>
+struct VLds {
   // all lanes of a wave read one row (consecutive channels): no padding needed
-  __shared__ uint16_t tile[VT][D];
+  uint16_t tile[VT][D];
   // The scale bytes of up to ST_TILES consecutive tiles of one head, per
   // V^T row: one 128-byte segment of the row, stored whole (written one byte
   // per block as they come, a row's line would fill over the workgroup's
   // whole range and partly leave L2 before it is complete).  Rows are 132
   // bytes apart, so the byte writes of a wave's channels fall in different banks.
-  constexpr int SPT = VT / NB, ST_TILES = 128 / SPT, ST_ROW = 132;
-  __shared__ __attribute__((aligned(16))) uint8_t sst[D * ST_ROW];
+  static constexpr int SPT = VT / (FMT == kFmtMX ? 32 : 16), ST_TILES = 128 / SPT, ST_ROW = 132;
+  __attribute__((aligned(16))) uint8_t sst[D * ST_ROW];
+};
+
+// workgroup blk of nblk
+template <int D, bool BF16, int FMT>
+__device__ __forceinline__ void quant_v(const uint16_t* __restrict__ v, uint8_t* __restrict__ codes,
+                                        uint8_t* __restrict__ scales, int N, int Np, int total, int per_wg, int blk,
+                                        int nblk, VLds<D, FMT>& lds) {
+  using T = VLds<D, FMT>;
+  constexpr int NB = (FMT == kFmtMX) ? 32 : 16, SPT = T::SPT, ST_TILES = T::ST_TILES, ST_ROW = T::ST_ROW;
+  auto& tile = lds.tile;
+  auto& sst = lds.sst;
   const int ntt = (Np + VT - 1) / VT;
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous
   // range of (bh, tile), so the two 64-byte halves of every 128-byte V^T line
   // are written through the same L2, mostly by one workgroup, one tile apart.
-  int w = blockIdx.x;
-  if ((gridDim.x & 7) == 0) w = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  int w = blk;
+  if ((nblk & 7) == 0) w = (blk & 7) * (nblk >> 3) + (blk >> 3);
   const int first = w * per_wg, last = min(total, first + per_wg);
   const int tid = threadIdx.x;
   constexpr int UPR = D / 8, LPT = VT * UPR / 256;   // 16-byte units per row, per thread
@@ -460,110 +563,221 @@ __global__ __launch_bounds__(256) void quant_v_kernel(const uint16_t* __restrict
   }
 }
 
+template <int D, bool BF16, int FMT>
+__global__ __launch_bounds__(256) void quant_v_kernel(const uint16_t* __restrict__ v, uint8_t* __restrict__ codes,
+                                                      uint8_t* __restrict__ scales, int N, int Np, int total,
+                                                      int per_wg) {
+  __shared__ VLds<D, FMT> lds;
+  quant_v<D, BF16, FMT>(v, codes, scales, N, Np, total, per_wg, blockIdx.x, gridDim.x, lds);
+}
+
+// ---------------------------------------------------------------------------
+// Everything that does not depend on the K mean in one launch: the first nv
+// workgroups quantize V, the next nkm form the K mean's partial sums, the rest
+// quantize Q.  For calls whose passes are too short to fill the GPU one by one.
+// ---------------------------------------------------------------------------
+struct PrepArgs {
+  const uint16_t *q, *k, *v;
+  uint8_t *qc, *qs, *vc, *vs;
+  float* qbar;
+  double* part;
+  long long q_units;
+  int N, Np, nchunk, nqb, v_total, v_per_wg, nv, nkm;
+};
+
+template <int D, bool BF16, int FMT, bool SQ>
+__global__ __launch_bounds__(256) void prep_kernel(const PrepArgs a) {
+  __shared__ union Lds {
+    VLds<D, FMT> v;
+    KmRed red;
+  } lds;
+  int b = blockIdx.x;
+  if (b < a.nv) {
+    quant_v<D, BF16, FMT>(a.v, a.vc, a.vs, a.N, a.Np, a.v_total, a.v_per_wg, b, a.nv, lds.v);
+    return;
+  }
+  b -= a.nv;
+  if (b < a.nkm) {
+    kmean_partial<D, BF16>(a.k, a.part, a.N, a.nchunk, b % a.nchunk, b / a.nchunk, lds.red);
+    return;
+  }
+  b -= a.nkm;
+  if constexpr (SQ) quant_q_smooth<D, BF16, FMT>(a.q, a.qbar, a.qc, a.qs, a.N, a.nqb, b % a.nqb, b / a.nqb, lds.red);
+  else quant_q<D, BF16, FMT>(a.q, a.qc, a.qs, a.q_units, b, gridDim.x - a.nv - a.nkm);
+}
+
 // ---------------------------------------------------------------------------
 // Host-side launchers (called by the C ABI in sage_abi.hip).
 // ---------------------------------------------------------------------------
 int kmean_chunks(int N) { return (N + KM_CHUNK - 1) / KM_CHUNK; }
+int qmean_blocks(int N) { return (N + QB - 1) / QB; }
 
-template <int D, bool BF16>
-static hipError_t launch_kmean_t(const void* k, double* part, float* mu, int BH, int N, hipStream_t st) {
+// f(ic<D>, ic<BF16>, ic<FMT>) for run-time values
+template <typename F>
+static hipError_t quant_dispatch(int D, bool bf16, int fmt, F&& f) {
+  if (D == 128) {
+    if (fmt == kFmtMX) return bf16 ? f(ic<128>{}, ic<1>{}, ic<kFmtMX>{}) : f(ic<128>{}, ic<0>{}, ic<kFmtMX>{});
+    return bf16 ? f(ic<128>{}, ic<1>{}, ic<kFmtNV16>{}) : f(ic<128>{}, ic<0>{}, ic<kFmtNV16>{});
+  }
+  if (fmt == kFmtMX) return bf16 ? f(ic<64>{}, ic<1>{}, ic<kFmtMX>{}) : f(ic<64>{}, ic<0>{}, ic<kFmtMX>{});
+  return bf16 ? f(ic<64>{}, ic<1>{}, ic<kFmtNV16>{}) : f(ic<64>{}, ic<0>{}, ic<kFmtNV16>{});
+}
+
+static hipError_t launch_kmean_final(const double* part, float* mu, int BH, int N, int D, hipStream_t st) {
   const int nchunk = kmean_chunks(N);
-  hipLaunchKernelGGL((kmean_partial_kernel<D, BF16>), dim3(nchunk, BH), dim3(KM_THREADS), 0, st,
-                     (const uint16_t*)k, part, N, nchunk);
-  hipLaunchKernelGGL((kmean_final_kernel<D>), dim3(BH), dim3(256), 0, st, (const double*)part, mu, N, nchunk);
+  if (D == 128) hipLaunchKernelGGL((kmean_final_kernel<128>), dim3(BH), dim3(256), 0, st, part, mu, N, nchunk);
+  else hipLaunchKernelGGL((kmean_final_kernel<64>), dim3(BH), dim3(256), 0, st, part, mu, N, nchunk);
   return hipGetLastError();
+}
+
+static hipError_t launch_kmean_partial(const void* k, double* part, int BH, int N, int D, bool bf16, hipStream_t st) {
+  const int nchunk = kmean_chunks(N);
+  return quant_dispatch(D, bf16, kFmtMX, [&](auto D_, auto B_, auto) {
+    hipLaunchKernelGGL((kmean_partial_kernel<decltype(D_)::value, decltype(B_)::value != 0>), dim3(nchunk, BH),
+                       dim3(KM_THREADS), 0, st, (const uint16_t*)k, part, N, nchunk);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_kmean(const void* k, double* part, float* mu, int BH, int N, int D, bool bf16, hipStream_t st) {
-  if (D == 128) return bf16 ? launch_kmean_t<128, true>(k, part, mu, BH, N, st) : launch_kmean_t<128, false>(k, part, mu, BH, N, st);
-  return bf16 ? launch_kmean_t<64, true>(k, part, mu, BH, N, st) : launch_kmean_t<64, false>(k, part, mu, BH, N, st);
+  const hipError_t e = launch_kmean_partial(k, part, BH, N, D, bf16, st);
+  return e != hipSuccess ? e : launch_kmean_final(part, mu, BH, N, D, st);
 }
 
-template <int D, bool BF16, int FMT, bool IS_K>
-static hipError_t launch_rows_t(const void* x, const float* mu, int mshift, int nmb, void* codes, void* scales, int BH,
-                                int N, int Nout, hipStream_t st) {
-  const long long units = (long long)BH * N * (D / 8);
-  constexpr int U = rows_units<IS_K>();
-  long long blocks = (units + 256 * U - 1) / (256 * U);
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL((quant_rows_kernel<D, BF16, FMT, IS_K>), dim3((unsigned)blocks), dim3(256), 0, st,
-                     (const uint16_t*)x, mu, mshift, nmb, (uint8_t*)codes, (uint8_t*)scales, N, Nout, units);
-  if (IS_K && Nout > N) {
-    hipLaunchKernelGGL((k_tail_kernel<D, FMT>), dim3(1, BH), dim3(256), 0, st, (uint8_t*)codes, (uint8_t*)scales, N, Nout);
+// K's codes and scales; mu null without smoothing.  part: the partial sums of
+// the mean (mu is then written here), or null when mu holds it already.
+static hipError_t launch_quant_k_rows(const void* x, const double* part, float* mu, void* codes, void* scales, int BH,
+                                      int N, int Np, int D, int fmt, bool bf16, hipStream_t st) {
+  const int nchunk = kmean_chunks(N);
+  if (part != nullptr && nchunk > KM_INLINE) {
+    const hipError_t e = launch_kmean_final(part, mu, BH, N, D, st);
+    if (e != hipSuccess) return e;
+    part = nullptr;
   }
-  return hipGetLastError();
+  return quant_dispatch(D, bf16, fmt, [&](auto D_, auto B_, auto F_) {
+    constexpr int DD = decltype(D_)::value, KRB = 4 * 256 / (DD / 8);
+    const long long blocks = (long long)(Np / KRB) * BH;
+    if (blocks > INT_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((quant_k_kernel<DD, decltype(B_)::value != 0, decltype(F_)::value>), dim3((unsigned)blocks),
+                       dim3(256), 0, st, (const uint16_t*)x, part, mu, (uint8_t*)codes, (uint8_t*)scales, N, Np, nchunk);
+    return hipGetLastError();
+  });
 }
 
-template <int D, int FMT, bool IS_K>
-static hipError_t launch_rows_d(const void* x, const float* mu, int mshift, int nmb, void* codes, void* scales, int BH,
-                                int N, int Nout, bool bf16, hipStream_t st) {
-  return bf16 ? launch_rows_t<D, true, FMT, IS_K>(x, mu, mshift, nmb, codes, scales, BH, N, Nout, st)
-              : launch_rows_t<D, false, FMT, IS_K>(x, mu, mshift, nmb, codes, scales, BH, N, Nout, st);
+// K with smoothing (mu and part given) or without (both null).
+hipError_t launch_quant_k(const void* k, double* part, float* mu, void* codes, void* scales, int BH, int N, int Np,
+                          int D, int fmt, bool bf16, hipStream_t st) {
+  if (mu != nullptr) {
+    const hipError_t e = launch_kmean_partial(k, part, BH, N, D, bf16, st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_quant_k_rows(k, mu ? part : nullptr, mu, codes, scales, BH, N, Np, D, fmt, bf16, st);
 }
 
-// mu: role K one mean per head (or null); role Q with smoothing one per QB-row block (or null).
-hipError_t launch_quant_rows(const void* x, const float* mu, void* codes, void* scales, int BH, int N, int Nout, int D,
-                             int fmt, bool is_k, bool bf16, hipStream_t st) {
-  const int mshift = is_k ? 30 : 7, nmb = is_k ? 1 : (N + QB - 1) / QB;
-  static_assert(QB == (1 << 7), "query smoothing blocks are 128 rows");
-#define SAGE_ROWS(DD, FF)                                                                                   \
-  return is_k ? launch_rows_d<DD, FF, true>(x, mu, mshift, nmb, codes, scales, BH, N, Nout, bf16, st)      \
-              : launch_rows_d<DD, FF, false>(x, mu, mshift, nmb, codes, scales, BH, N, Nout, bf16, st)
-  if (D == 128) { if (fmt == kFmtMX) { SAGE_ROWS(128, kFmtMX); } else { SAGE_ROWS(128, kFmtNV16); } }
-  else { if (fmt == kFmtMX) { SAGE_ROWS(64, kFmtMX); } else { SAGE_ROWS(64, kFmtNV16); } }
-#undef SAGE_ROWS
+// Q; qbar [BH, ceil(N/QB), D] receives the block means with smoothing, null without.
+hipError_t launch_quant_q(const void* q, float* qbar, void* codes, void* scales, int BH, int N, int D, int fmt,
+                          bool bf16, hipStream_t st) {
+  return quant_dispatch(D, bf16, fmt, [&](auto D_, auto B_, auto F_) {
+    constexpr int DD = decltype(D_)::value, FF = decltype(F_)::value;
+    constexpr bool BB = decltype(B_)::value != 0;
+    if (qbar != nullptr) {
+      hipLaunchKernelGGL((quant_q_smooth_kernel<DD, BB, FF>), dim3((unsigned)qmean_blocks(N), (unsigned)BH), dim3(256), 0,
+                         st, (const uint16_t*)q, qbar, (uint8_t*)codes, (uint8_t*)scales, N, qmean_blocks(N));
+    } else {
+      const long long units = (long long)BH * N * (DD / 8);
+      const long long blocks = std::min<long long>((units + 255) / 256, 65536);
+      hipLaunchKernelGGL((quant_q_kernel<DD, BB, FF>), dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)q,
+                         (uint8_t*)codes, (uint8_t*)scales, units);
+    }
+    return hipGetLastError();
+  });
 }
 
-int qmean_blocks(int N) { return (N + QB - 1) / QB; }
-
-hipError_t launch_qmean(const void* q, float* qbar, int BH, int N, int D, bool bf16, hipStream_t st) {
-  const dim3 grid((unsigned)qmean_blocks(N), (unsigned)BH);
-#define SAGE_QM(DD, BB) hipLaunchKernelGGL((qmean_kernel<DD, BB>), grid, dim3(KM_THREADS), 0, st, (const uint16_t*)q, \
-                                           qbar, N, qmean_blocks(N))
-  if (D == 128) { if (bf16) { SAGE_QM(128, true); } else { SAGE_QM(128, false); } }
-  else { if (bf16) { SAGE_QM(64, true); } else { SAGE_QM(64, false); } }
-#undef SAGE_QM
-  return hipGetLastError();
-}
-
-// bias [BH, nqb, Np] fp32; Np is a multiple of 128
+// bias [BH, nqb, Np] fp32; Np is a multiple of 128.  The 512-key tiles are taken
+// when they give every CU a workgroup and more than one wave of each has blocks.
 hipError_t launch_qk_bias(const void* k, const float* mu, const float* qbar, float* bias, int BH, int N, int Np, int D,
                           bool bf16, hipStream_t st) {
-  const dim3 grid((unsigned)((Np + QB_THREADS - 1) / QB_THREADS), (unsigned)BH);
   const int nqb = qmean_blocks(N);
-#define SAGE_QB(DD, BB) hipLaunchKernelGGL((qk_bias_kernel<DD, BB>), grid, dim3(QB_THREADS), 0, st, (const uint16_t*)k, \
-                                           mu, qbar, bias, N, Np, nqb)
-  if (D == 128) { if (bf16) { SAGE_QB(128, true); } else { SAGE_QB(128, false); } }
-  else { if (bf16) { SAGE_QB(64, true); } else { SAGE_QB(64, false); } }
-#undef SAGE_QB
-  return hipGetLastError();
+  const long long big = (long long)((Np + 511) / 512) * ((nqb + 31) / 32) * BH;
+  return quant_dispatch(D, bf16, kFmtMX, [&](auto D_, auto B_, auto) {
+    constexpr int DD = decltype(D_)::value;
+    constexpr bool BB = decltype(B_)::value != 0;
+    if (nqb > 8 && big >= 256) {
+      const int nkt = (Np + 511) / 512;
+      hipLaunchKernelGGL((qk_bias_kernel<DD, BB, 512, 4, 16>), dim3((unsigned)(nkt * ((nqb + 31) / 32)), (unsigned)BH),
+                         dim3(256), 0, st, (const uint16_t*)k, mu, qbar, bias, N, Np, nqb, nkt);
+    } else {
+      const int nkt = (Np + 255) / 256;
+      hipLaunchKernelGGL((qk_bias_kernel<DD, BB, 256, 1, 32>), dim3((unsigned)(nkt * ((nqb + 7) / 8)), (unsigned)BH),
+                         dim3(256), 0, st, (const uint16_t*)k, mu, qbar, bias, N, Np, nqb, nkt);
+    }
+    return hipGetLastError();
+  });
 }
 
-template <int D, bool BF16, int FMT>
-static hipError_t launch_v_t(const void* v, void* codes, void* scales, int BH, int N, int Np, hipStream_t st) {
-  // Np is a multiple of 128; a last half tile is handled by the tile-range guard
-  const long long total = (long long)((Np + VT - 1) / VT) * BH;
-  if (total == 0) return hipSuccess;
-  if (total > INT_MAX) return hipErrorInvalidValue;
+// tiles of the V quantizer, tiles per workgroup and workgroups (Np is a multiple of VT)
+static hipError_t v_grid(int BH, int Np, int* total, int* per_wg, int* grid) {
+  const long long t = (long long)(Np / VT) * BH;
+  if (t > INT_MAX) return hipErrorInvalidValue;
   int dev = 0, ncu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const long long slots = (long long)(ncu > 0 ? ncu : 1) * V_WG_PER_CU;
-  const int per_wg = (int)((total + slots - 1) / slots);
-  const int grid = (int)((total + per_wg - 1) / per_wg);
-  hipLaunchKernelGGL((quant_v_kernel<D, BF16, FMT>), dim3(grid), dim3(256), 0, st, (const uint16_t*)v,
-                     (uint8_t*)codes, (uint8_t*)scales, N, Np, (int)total, per_wg);
-  return hipGetLastError();
+  *total = (int)t;
+  *per_wg = (int)((t + slots - 1) / slots);
+  *grid = (int)((t + *per_wg - 1) / *per_wg);
+  return hipSuccess;
 }
 
 hipError_t launch_quant_v(const void* v, void* codes, void* scales, int BH, int N, int Np, int D, int fmt, bool bf16,
                           hipStream_t st) {
-#define SAGE_V(DD, FF) return bf16 ? launch_v_t<DD, true, FF>(v, codes, scales, BH, N, Np, st) \
-                                   : launch_v_t<DD, false, FF>(v, codes, scales, BH, N, Np, st)
-  if (D == 128) { if (fmt == kFmtMX) { SAGE_V(128, kFmtMX); } else { SAGE_V(128, kFmtNV16); } }
-  else { if (fmt == kFmtMX) { SAGE_V(64, kFmtMX); } else { SAGE_V(64, kFmtNV16); } }
-#undef SAGE_V
+  int total, per_wg, grid;
+  const hipError_t e = v_grid(BH, Np, &total, &per_wg, &grid);
+  if (e != hipSuccess) return e;
+  return quant_dispatch(D, bf16, fmt, [&](auto D_, auto B_, auto F_) {
+    hipLaunchKernelGGL((quant_v_kernel<decltype(D_)::value, decltype(B_)::value != 0, decltype(F_)::value>), dim3(grid),
+                       dim3(256), 0, st, (const uint16_t*)v, (uint8_t*)codes, (uint8_t*)scales, N, Np, total, per_wg);
+    return hipGetLastError();
+  });
+}
+
+// Up to this many elements (BH Np D) Q, V and K's partial sums share a launch
+// (four launches fewer): B1 H4 N4096 D128 61 -> 55 us a call, B2 H24 N1237 60 -> 51,
+// B1 H32 N4096 (2^24) 173 -> 170; above it the passes fill the GPU one by one and
+// the V part's LDS costs the others occupancy: B2 H32 N4096 326 -> 335.
+constexpr long long PREP_MAX_ELEMS = 1LL << 24;
+
+// Q, K and V of one call.  qbar null without smoothing Q; mu and part null
+// without smoothing K.
+hipError_t launch_quant_qkv(const void* q, const void* k, const void* v, void* qc, void* qs, float* qbar, void* kc,
+                            void* ks, double* part, float* mu, void* vc, void* vs, int BH, int N, int Np, int D, int fmt,
+                            bool bf16, hipStream_t st) {
+  const long long elems = (long long)BH * Np * D;
+  if (elems > PREP_MAX_ELEMS) {
+    hipError_t e = launch_quant_q(q, qbar, qc, qs, BH, N, D, fmt, bf16, st);
+    if (e == hipSuccess) e = launch_quant_k(k, part, mu, kc, ks, BH, N, Np, D, fmt, bf16, st);
+    if (e == hipSuccess) e = launch_quant_v(v, vc, vs, BH, N, Np, D, fmt, bf16, st);
+    return e;
+  }
+  PrepArgs a;
+  a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
+  a.qc = (uint8_t*)qc; a.qs = (uint8_t*)qs; a.vc = (uint8_t*)vc; a.vs = (uint8_t*)vs;
+  a.qbar = qbar; a.part = part; a.N = N; a.Np = Np; a.nchunk = kmean_chunks(N); a.nqb = qmean_blocks(N);
+  hipError_t e = v_grid(BH, Np, &a.v_total, &a.v_per_wg, &a.nv);
+  if (e != hipSuccess) return e;
+  a.nkm = mu != nullptr ? a.nchunk * BH : 0;
+  a.q_units = (long long)BH * N * (D / 8);
+  const long long nq = qbar != nullptr ? (long long)a.nqb * BH : (a.q_units + 255) / 256;
+  const dim3 grid((unsigned)(a.nv + a.nkm + nq));
+  e = quant_dispatch(D, bf16, fmt, [&](auto D_, auto B_, auto F_) {
+    constexpr int DD = decltype(D_)::value, FF = decltype(F_)::value;
+    constexpr bool BB = decltype(B_)::value != 0;
+    if (qbar != nullptr) hipLaunchKernelGGL((prep_kernel<DD, BB, FF, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((prep_kernel<DD, BB, FF, false>), grid, dim3(256), 0, st, a);
+    return hipGetLastError();
+  });
+  return e != hipSuccess ? e : launch_quant_k_rows(k, mu ? part : nullptr, mu, kc, ks, BH, N, Np, D, fmt, bf16, st);
 }
 
 }  // namespace sage

@@ -12,11 +12,15 @@
 namespace sage {
 hipError_t launch_kmean(const void* k, double* part, float* mu, int BH, int N, int D, bool bf16, hipStream_t st);
 int kmean_chunks(int N);
-hipError_t launch_quant_rows(const void* x, const float* mu, void* codes, void* scales, int BH, int N, int Nout, int D,
-                             int fmt, bool is_k, bool bf16, hipStream_t st);
+hipError_t launch_quant_q(const void* q, float* qbar, void* codes, void* scales, int BH, int N, int D, int fmt,
+                          bool bf16, hipStream_t st);
+hipError_t launch_quant_k(const void* k, double* part, float* mu, void* codes, void* scales, int BH, int N, int Np,
+                          int D, int fmt, bool bf16, hipStream_t st);
 hipError_t launch_quant_v(const void* v, void* codes, void* scales, int BH, int N, int Np, int D, int fmt, bool bf16,
                           hipStream_t st);
-hipError_t launch_qmean(const void* q, float* qbar, int BH, int N, int D, bool bf16, hipStream_t st);
+hipError_t launch_quant_qkv(const void* q, const void* k, const void* v, void* qc, void* qs, float* qbar, void* kc,
+                            void* ks, double* part, float* mu, void* vc, void* vs, int BH, int N, int Np, int D, int fmt,
+                            bool bf16, hipStream_t st);
 int qmean_blocks(int N);
 hipError_t launch_qk_bias(const void* k, const float* mu, const float* qbar, float* bias, int BH, int N, int Np, int D,
                           bool bf16, hipStream_t st);
@@ -124,25 +128,14 @@ int quant_impl(const void* x, int role, int B, int H, int N, int D, unsigned fmt
                float* kmean, void* ws, hipStream_t st) {
   const bool bf16 = (fmt & SAGE_IN_BF16) != 0;
   const int BH = B * H, f = fmt_of(fmt);
-  hipError_t e = hipSuccess;
-  if (role == SAGE_ROLE_Q) {
-    const bool smooth = (fmt & SAGE_SMOOTH_Q) != 0;     // kmean receives the block means
-    if (smooth) {
-      e = sage::launch_qmean(x, kmean, BH, N, D, bf16, st);
-      if (e != hipSuccess) return SAGE_ERR_HIP;
-    }
-    e = sage::launch_quant_rows(x, smooth ? kmean : nullptr, codes, scales, BH, N, N, D, f, false, bf16, st);
-  } else if (role == SAGE_ROLE_K) {
+  if (role == SAGE_ROLE_Q)      // with smoothing, kmean receives the block means
+    return hip_status(sage::launch_quant_q(x, (fmt & SAGE_SMOOTH_Q) ? kmean : nullptr, codes, scales, BH, N, D, f, bf16, st));
+  if (role == SAGE_ROLE_K) {
     const bool smooth = !(fmt & SAGE_NO_SMOOTH_K);
-    if (smooth) {
-      e = sage::launch_kmean(x, static_cast<double*>(ws), kmean, BH, N, D, bf16, st);
-      if (e != hipSuccess) return SAGE_ERR_HIP;
-    }
-    e = sage::launch_quant_rows(x, smooth ? kmean : nullptr, codes, scales, BH, N, pad128(N), D, f, true, bf16, st);
-  } else {
-    e = sage::launch_quant_v(x, codes, scales, BH, N, pad128(N), D, f, bf16, st);
+    return hip_status(sage::launch_quant_k(x, smooth ? static_cast<double*>(ws) : nullptr, smooth ? kmean : nullptr, codes,
+                                           scales, BH, N, pad128(N), D, f, bf16, st));
   }
-  return hip_status(e);
+  return hip_status(sage::launch_quant_v(x, codes, scales, BH, N, pad128(N), D, f, bf16, st));
 }
 
 int attn_args(const void* q, const void* k, const void* v, const void* o, int B, int H, int N, int D, int causal,
@@ -193,9 +186,10 @@ int attn_ws_impl(const void* q, const void* k, const void* v, void* o, int B, in
   const bool smooth_q = (fmt & SAGE_SMOOTH_Q) != 0, smooth_k = !(fmt & SAGE_NO_SMOOTH_K);
   float* qbar = smooth_q ? reinterpret_cast<float*>(base + w.qbar) : nullptr;
   float* bias = smooth_q ? reinterpret_cast<float*>(base + w.bias) : nullptr;
-  int rc = quant_impl(q, SAGE_ROLE_Q, B, H, N, D, fmt, base + w.qc, base + w.qs, qbar, nullptr, st);
-  if (rc == SAGE_OK) rc = quant_impl(k, SAGE_ROLE_K, B, H, N, D, fmt, base + w.kc, base + w.ks, mu, base + w.part, st);
-  if (rc == SAGE_OK) rc = quant_impl(v, SAGE_ROLE_V, B, H, N, D, fmt, base + w.vc, base + w.vs, nullptr, nullptr, st);
+  int rc = hip_status(sage::launch_quant_qkv(
+      q, k, v, base + w.qc, base + w.qs, qbar, base + w.kc, base + w.ks,
+      smooth_k ? reinterpret_cast<double*>(base + w.part) : nullptr, smooth_k ? mu : nullptr, base + w.vc, base + w.vs,
+      B * H, N, pad128(N), D, fmt_of(fmt), (fmt & SAGE_IN_BF16) != 0, st));
   if (rc == SAGE_OK && smooth_q)   // GEMV(qbar_i, K'^T) of every query block, over K' = K - mean(K)
     rc = hip_status(sage::launch_qk_bias(k, smooth_k ? mu : nullptr, qbar, bias, B * H, N, pad128(N), D,
                                          (fmt & SAGE_IN_BF16) != 0, st));
