@@ -25,11 +25,10 @@
 // f_j.  Each tile then rescales the accumulator once by
 // gamma_j = 2^{c2 (m_{j-1} - m_j) + f_{j-1} - f_j}.
 //
-// Data movement: KV tiles go from HBM straight into LDS with global loads
-// that write LDS (no staging registers).  LDS holds each tile in MFMA-operand
-// order -- one 1 KiB block per 64-lane operand read, lane l's 16 bytes at
-// 16 l -- so operand reads are linear and bank-conflict free.  Two LDS stages
-// and one barrier per tile: after the barrier of tile j every wave has finished
+// Data movement: KV tiles go from HBM straight into LDS with loads that write
+// LDS (no staging registers), row by row with swizzled 16-byte chunks or in
+// MFMA-operand order (see the load jobs); either way operand reads are free of
+// bank conflicts.  Two LDS stages and one barrier per tile: after the barrier of tile j every wave has finished
 // tile j - 1, and the loads of tile j + 1 go to that stage while tile j runs.
 //
 // What bounds it is instruction issue (exponentials, packs and plain VALU work
@@ -45,6 +44,12 @@
 namespace sage {
 
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// Swizzle of a tile row's NCH 16-byte chunks: 16 consecutive rows at one chunk fall on distinct bank groups.
+template <int NCH>
+__device__ __forceinline__ int fp4_swz(int row) {
+  return NCH == 8 ? (row >> 1) & 7 : NCH == 4 ? (row >> 2) & 3 : (row >> 3) & 1;
+}
 
 __device__ __forceinline__ v8i as_op(const v4i x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; }
 
@@ -90,19 +95,27 @@ constexpr int fp4_waves(int D, int BKV, int W, bool SQ) {
 // OUT: 0 = fp32, 1 = bf16, 2 = fp16.  SQ: smoothing Q -- S += qkb[bh, query
 // block, key] (Algorithm 1's GEMV of the block mean with K', one row of Np
 // floats per 128-query block, which is this workgroup's query tile).
-template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W>
-__global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_kernel(
+//
+// KG: KV groups.  With KG = 2 the workgroup's four waves are two groups of two:
+// 64 queries, each group walking every second KV tile through LDS stages of
+// its own, and the two results are merged through LDS at the end (each group's
+// O and l are brought to the larger running max and added, in fp32).  For calls
+// with too few 128-query tiles for the GPU; see fp4_kv_groups.
+template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W, int KG>
+__global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) void attn_fp4_mx_kernel(
     const uint8_t* __restrict__ qc, const uint8_t* __restrict__ qs, const uint8_t* __restrict__ kc,
     const uint8_t* __restrict__ ks, const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs,
     const float* __restrict__ qkb, void* __restrict__ o, int BH, int N, int Np, int nqt, float c2, float log6) {
   using T = Fp4Stage<D, BKV, SQ>;
   constexpr int NSUB = T::NSUB, NKS = T::NKS, NDB = T::NDB, NG = T::NG;
-  constexpr int AQW = 32 * W;
+  constexpr int QW = W / KG, AQW = 32 * QW;       // waves along the queries, queries per workgroup
   static_assert((W == 4 || W == 8) && (!SQ || W == 4), "4 or 8 waves; smoothing Q blocks are 128 queries");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2][T::BYTES];
+  static_assert(KG == 1 || (KG == 2 && W == 4), "one or two KV groups");
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * KG][T::BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % QW;   // wave of its KV group
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / QW;
   const int col = lane & 31, hi = lane >> 5;
   const int total = nqt * BH;
   int lin = blockIdx.x;
@@ -131,18 +144,36 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
   int ntiles = (N + BKV - 1) / BKV;
   if (CAUSAL) ntiles = min(ntiles, min(q0 + AQW - 1, N - 1) / BKV + 1);
 
-  // Load jobs: wave w loads K^ operand blocks b = w + 4i (key row 32t + col,
-  // bytes [16s + 16 NKS hi, +16) with t = b / NKS, s = b % NKS), V^T operand blocks
-  // b = w + 4i (dim row 32i + col, bytes [32w + 16hi, +16) of the tile, since
-  // NG = 4) and scale dword jobs jb = w + 4i: K^ scale dwords 64jb + lane,
-  // then V^T scale dwords 64(jb - NKSJ) + lane (dim row d / 2, half d & 1).
+  // Load jobs of 1 KiB: wave w of a KV group loads K^ jobs and V^T jobs b = w +
+  // QW i and scale dword jobs jb = w + QW i (K^ scale dwords 64jb + lane, then
+  // V^T scale dwords 64(jb - NKSJ) + lane, VW per dim row).
+  // ROWS (256-key tiles, four waves): a job is whole tile rows as they lie in memory (K^ rows
+  // of D/2 bytes, V^T rows of BKV/2), the 16-byte chunks swizzled against bank
+  // conflicts by the choice of the chunk each lane loads, so every line is
+  // requested once; operand reads then need an address per K-step.  Otherwise a
+  // job is one MFMA operand (32 rows x two 16-byte chunks, lane l's bytes at 16 l):
+  // a line is requested by up to four jobs, but one lane offset serves all
+  // operand reads, and the 128-key kernels have no registers left (D = 128, 8
+  // heads x 4096: 76 us a call with ROWS, 65 without; 256-key tiles, 4 heads
+  // x 4096 in two KV groups 47.7 -> 45.2, B4 H32 N4096 637 -> 618; 256-query
+  // workgroups, which fetch a tile half as often, 7745 -> 7773 on B1 H32 N32768).
   // Each load is a buffer resource over the head's tensor, a uniform offset --
   // tile, job and the tail redirect -- and one of five fixed lane offsets, so
   // a load costs no VALU and no 64-bit address arithmetic.
-  static_assert(W % NKS == 0 && W % NG == 0, "job layout");
-  constexpr int KJ = (T::NKB + W - 1) / W, VJ = (T::NVB + W - 1) / W, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + W - 1) / W;
-  const uint32_t ko0 = (uint32_t)((32 * (wave / NKS) + col) * (D / 2) + 16 * (wave % NKS) + 16 * NKS * hi);
-  const uint32_t vo0 = (uint32_t)((32 * (wave / NG) + col) * (Np / 2) + 32 * (wave % NG) + 16 * hi);
+  constexpr bool ROWS = BKV == 256 && W == 4;
+  static_assert(ROWS ? QW % 2 == 0 : QW % NKS == 0 && (QW % NG == 0 || NG % QW == 0), "job layout");
+  constexpr int KJ = (T::NKB + QW - 1) / QW, VJ = (T::NVB + QW - 1) / QW, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + QW - 1) / QW;
+  constexpr int KCH = D / 32, VCH = BKV / 32, VR = 64 / VCH;      // ROWS: chunks per row, V^T rows per job
+  uint32_t ko0, vo0, vo_back = 0;
+  if constexpr (ROWS) {
+    const int kcl = (lane % KCH) ^ fp4_swz<KCH>(lane / KCH), vcl = (lane % VCH) ^ fp4_swz<VCH>(wave * VR + lane / VCH);
+    ko0 = (uint32_t)(lane / KCH * (D / 2) + 16 * kcl);
+    vo0 = (uint32_t)(lane / VCH) * (uint32_t)(Np / 2) + 16 * vcl;
+    vo_back = vcl >= VCH / 2 ? 64u : 0u;                           // subtracted when the tile's upper half lies past Np
+  } else {
+    ko0 = (uint32_t)((32 * (wave / NKS) + col) * (D / 2) + 16 * (wave % NKS) + 16 * NKS * hi);
+    vo0 = (uint32_t)((32 * (wave / NG) + col) * (Np / 2) + 32 * (wave % NG) + 16 * hi);
+  }
   const uint32_t kso = (uint32_t)(4 * lane);
   constexpr int VW = T::VW;
   const uint32_t vso = (uint32_t)((lane / VW) * (Np / 32) + 4 * (lane % VW));
@@ -155,27 +186,32 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
   // the resource, a uniform byte offset and one fixed lane offset
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase, Np * (D / 2)), rv = make_rsrc(vbase, D * (Np / 2));
   const __amdgpu_buffer_rsrc_t rks = make_rsrc(ksbase, Np * (D / 32)), rvs = make_rsrc(vsbase, D * (Np / 32));
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(SQ ? qkb + ((size_t)bh * nqt + qt) * Np : nullptr, SQ ? Np * 4 : 0);
+  const __amdgpu_buffer_rsrc_t rb =
+      make_rsrc(SQ ? qkb + ((size_t)bh * ((N + 127) / 128) + q0 / 128) * Np : nullptr, SQ ? Np * 4 : 0);
   auto issue = [&](int j, int stage) {
     const int kb = j * BKV;
     const bool short_tail = BKV == 256 && kb + BKV > Np;   // keys [kb + 128, kb + 256) lie past Np
-    uint8_t* L = lds[stage];
+    uint8_t* L = lds[2 * kg + stage];
 #pragma unroll
     for (int i = 0; i < KJ; ++i) {
-      const int b = wave + W * i, t = b / NKS;
-      if (T::NKB % W != 0 && b >= T::NKB) break;
-      const uint32_t back = (short_tail && t >= NSUB / 2) ? 128u * (D / 2) : 0u;
-      buf_load16(rk, ko0, (uint32_t)kb * (D / 2) + (uint32_t)i * (32 * W / NKS) * (D / 2) - back, L + T::KC_OFF + b * 1024);
+      const int b = wave + QW * i;
+      if (T::NKB % QW != 0 && b >= T::NKB) break;
+      const uint32_t back = (short_tail && b >= T::NKB / 2) ? 128u * (D / 2) : 0u;
+      const uint32_t off = ROWS ? (uint32_t)b * 1024u : (uint32_t)i * (32 * QW / NKS) * (D / 2);
+      buf_load16(rk, ko0, (uint32_t)kb * (D / 2) + off - back, L + T::KC_OFF + b * 1024);
     }
+    const uint32_t vo = vo0 - (short_tail ? vo_back : 0u);
 #pragma unroll
     for (int i = 0; i < VJ; ++i) {
-      if (T::NVB % W != 0 && wave + W * i >= T::NVB) break;
-      const uint32_t back = (short_tail && (wave % NG) >= NG / 2) ? 64u : 0u;
-      buf_load16(rv, vo0, (uint32_t)kb / 2 + (uint32_t)i * (32 * W / NG) * (Np / 2) - back, L + T::VC_OFF + (wave + W * i) * 1024);
+      const int b = wave + QW * i;
+      if (T::NVB % QW != 0 && b >= T::NVB) break;
+      const uint32_t off = ROWS ? (uint32_t)(b * VR) * (uint32_t)(Np / 2)
+                                : (uint32_t)(QW * i / NG) * 32 * (Np / 2) + 32 * (QW * i % NG);
+      buf_load16(rv, vo, (uint32_t)kb / 2 + off, L + T::VC_OFF + b * 1024);
     }
 #pragma unroll
     for (int i = 0; i < SJ; ++i) {
-      const int jb = wave + W * i;
+      const int jb = wave + QW * i;
       if (jb < T::NKSJ) {
         const uint32_t back = (short_tail && 64 * jb * 4 >= T::KS_BYTES / 2) ? T::KS_BYTES / 2 : 0u;
         if (T::KS_BYTES % 256 == 0 || 256 * jb + 4 * lane < T::KS_BYTES)
@@ -191,19 +227,29 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
     }
   };
 
+  // operand addresses in the tile: K^ (key subtile t, K-step s) and V^T (channel block db, K-step g)
+  auto k_op = [&](int t, int s) {
+    return T::KC_OFF + (ROWS ? (32 * t + col) * (D / 2) + ((s + NKS * hi) ^ fp4_swz<KCH>(col)) * 16
+                             : (t * NKS + s) * 1024 + lane * 16);
+  };
+  auto v_op = [&](int db, int g) {
+    return T::VC_OFF + (ROWS ? (32 * db + col) * (BKV / 2) + ((2 * g + hi) ^ fp4_swz<VCH>(col)) * 16
+                             : (db * NG + g) * 1024 + lane * 16);
+  };
   v16f oacc[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db) oacc[db] = v16f{};
   float m = -INFINITY, mc_old = -INFINITY, f_old = 0.0f, lsum_acc = 0.0f;
 
-  issue(0, 0);
-  for (int j = 0; j < ntiles; ++j) {
-    const int stage = j & 1;
+  if (kg < ntiles) issue(kg, 0);
+  for (int jj = 0; jj < ntiles; jj += KG) {                // group kg takes tile j = jj + kg
+    const int j = jj + kg, stage = (jj / KG) & 1;
     wait_loads();                                          // this wave's loads of tile j have landed
-    __syncthreads();                                       // everyone's; every wave is past tile j - 1
-    if (j + 1 < ntiles) issue(j + 1, stage ^ 1);
-    const uint8_t* L = lds[stage];
+    __syncthreads();                                       // everyone's; every wave is past tile j - KG
+    if (j + KG < ntiles) issue(j + KG, stage ^ 1);
+    const uint8_t* L = lds[2 * kg + stage];
     const int kb = j * BKV;
+    if (KG > 1 && j >= ntiles) continue;
     if (CAUSAL && kb > qw + 31) continue;                  // the whole tile is above this wave's diagonal
 
     // S^T = K^ . Q^T for the tile.  K-step s takes channel block s + NKS hi in
@@ -220,7 +266,7 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
       v16f acc = v16f{};
       static_for<NKS>([&](auto S_) {
         constexpr int s = decltype(S_)::value;
-        const v4i a = *reinterpret_cast<const v4i*>(L + T::KC_OFF + (t * NKS + s) * 1024 + lane * 16);
+        const v4i a = *reinterpret_cast<const v4i*>(L + k_op(t, s));
         acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(qreg[s]), acc, 4, 4, s, (int)ksc, s,
                                                               (int)qsc);
       });
@@ -335,7 +381,7 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
       const int psb = sb < 0 ? 0 : sb;
 #pragma unroll
       for (int db = 0; db < NDB; ++db) {
-        const v4i a = *reinterpret_cast<const v4i*>(L + T::VC_OFF + (db * NG + g) * 1024 + lane * 16);
+        const v4i a = *reinterpret_cast<const v4i*>(L + v_op(db, g));
         oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(pw), oacc[db], 4, 4, 2 * (g & 1),
                                                                    (int)vsw[db][g >> 1], 0, psb);
       }
@@ -347,6 +393,37 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
     f_old = f;
   }
 
+  if constexpr (KG == 2) {
+    // the accumulators of state (m c2, f) are converted to state (mc, 0) by 2^{(m c2 - mc) + f};
+    // group 0 has at least one tile, a group 1 without any has m = -inf and adds zero
+    constexpr int WBYTES = (NDB * 4 + 1) * 1024;           // per wave: O, then (m c2, f, l)
+    static_assert(QW * WBYTES <= 2 * KG * T::BYTES, "the merge fits the tile stages");
+    uint8_t* const mrg = lds[0] + wave * WBYTES + lane * 16;
+    __syncthreads();                                       // every wave is done with the tiles
+    if (kg == 1) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<v4f*>(mrg + (db * 4 + g) * 1024) =
+              v4f{oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
+      *reinterpret_cast<v4f*>(mrg + NDB * 4 * 1024) = v4f{mc_old, f_old, lsum_acc, 0.0f};
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const v4f st = *reinterpret_cast<const v4f*>(mrg + NDB * 4 * 1024);
+    const float mc = smax(mc_old, st[0]);
+    const float g0 = __builtin_amdgcn_exp2f((mc_old - mc) + f_old), g1 = __builtin_amdgcn_exp2f((st[0] - mc) + st[1]);
+    lsum_acc = lsum_acc * g0 + st[2] * g1;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const v4f x = *reinterpret_cast<const v4f*>(mrg + (db * 4 + g) * 1024);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) oacc[db][4 * g + r] = oacc[db][4 * g + r] * g0 + x[r] * g1;
+      }
+  }
   const float ltot = lsum_acc + __shfl_xor(lsum_acc, 32, 64);
   const float inv = 1.0f / ltot;
   if (qi < N) {
@@ -371,32 +448,48 @@ __global__ __launch_bounds__(64 * W, fp4_waves(D, BKV, W, SQ)) void attn_fp4_mx_
   }
 }
 
-template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W>
+template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W, int KG>
 static hipError_t launch_fp4_t(const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  const int nqt = (N + 32 * W - 1) / (32 * W);
-  hipLaunchKernelGGL((attn_fp4_mx_kernel<D, BKV, CAUSAL, OUT, SQ, W>), dim3((unsigned)(nqt * BH)), dim3(64 * W), 0, st,
+  constexpr int AQW = 32 * W / KG;
+  const int nqt = (N + AQW - 1) / AQW;
+  hipLaunchKernelGGL((attn_fp4_mx_kernel<D, BKV, CAUSAL, OUT, SQ, W, KG>), dim3((unsigned)(nqt * BH)), dim3(64 * W), 0, st,
                      (const uint8_t*)qc, (const uint8_t*)qs, (const uint8_t*)kc, (const uint8_t*)ks, (const uint8_t*)vc,
                      (const uint8_t*)vs, qkb, o, BH, N, Np, nqt, c2, log6);
   return hipGetLastError();
 }
 
-template <int D, int BKV, bool CAUSAL, bool SQ, int W>
+template <int D, int BKV, bool CAUSAL, bool SQ, int W, int KG>
 static hipError_t launch_fp4_o(int out, const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  if (out == 0) return launch_fp4_t<D, BKV, CAUSAL, 0, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  if (out == 1) return launch_fp4_t<D, BKV, CAUSAL, 1, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-  return launch_fp4_t<D, BKV, CAUSAL, 2, SQ, W>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (out == 0) return launch_fp4_t<D, BKV, CAUSAL, 0, SQ, W, KG>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (out == 1) return launch_fp4_t<D, BKV, CAUSAL, 1, SQ, W, KG>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  return launch_fp4_t<D, BKV, CAUSAL, 2, SQ, W, KG>(qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+}
+
+// KV groups of a call: two where 128-query tiles are too few for the GPU and
+// there are at least two KV tiles to share.  With 256-key tiles at D = 128 the
+// two groups' stages take the LDS of a CU, so twice the workgroups must still
+// be one per CU: 4 heads x 4096 (128 tiles) 55.4 -> 45.2 us a call, 6 heads 59.9
+// -> 81.5.  The other stages fit twice or more: 128-key tiles, D = 128, heads x
+// 4096: 4 heads 57.8 -> 41, 8 heads 65 -> 62.7 (causal 64 -> 51), 12 heads 91.3 ->
+// 85.5, 16 heads 96.9 -> 102.9; D = 64, 8 heads 49 -> 42.5, 16 heads 72.5 -> 71.7.
+static int fp4_kv_groups(int BH, int N, int D, int bkv) {
+  const long long tiles = (long long)BH * ((N + 127) / 128);
+  return tiles <= (D == 128 && bkv == 256 ? 128 : 384) && N > bkv ? 2 : 1;
 }
 
 template <int D, int BKV, bool CAUSAL>
 static hipError_t launch_fp4_s(int out, const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-             : launch_fp4_o<D, BKV, CAUSAL, false, 4>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (fp4_kv_groups(BH, N, D, BKV) == 2)
+    return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4, 2>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
+               : launch_fp4_o<D, BKV, CAUSAL, false, 4, 2>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
+             : launch_fp4_o<D, BKV, CAUSAL, false, 4, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
 }
 
 // qkb: smoothing-Q bias [BH, ceil(N/128), Np] fp32, or null without smoothing Q.
@@ -406,10 +499,11 @@ hipError_t launch_attn_fp4_mx(const void* qc, const void* qs, const void* kc, co
 #define SAGE_A(DD, BB)                                                                                    \
   return causal ? launch_fp4_s<DD, BB, true>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st) \
                 : launch_fp4_s<DD, BB, false>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-  if (wg256) {
-    // 256-query workgroups: 256-key tiles, non-causal, without smoothing Q (checked by the caller)
-    if (D == 128) return launch_fp4_o<128, 256, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
-    return launch_fp4_o<64, 256, false, false, 8>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+  if (wg256 && fp4_kv_groups(BH, N, D, 256) == 1) {
+    // 256-query workgroups: 256-key tiles, non-causal, without smoothing Q (checked by the caller); calls
+    // split over KV groups run the same kernel with and without the flag, so both give the same bits
+    if (D == 128) return launch_fp4_o<128, 256, false, false, 8, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
+    return launch_fp4_o<64, 256, false, false, 8, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
   }
   if (D == 128) { if (bkv == 256) { SAGE_A(128, 256); } else if (bkv == 128) { SAGE_A(128, 128); } else { SAGE_A(128, 64); } }
   if (bkv == 256) { SAGE_A(64, 256); } else if (bkv == 128) { SAGE_A(64, 128); } else { SAGE_A(64, 64); }

@@ -302,3 +302,27 @@ def test_attn_wg256_bench_workload_same_bits():
     b = bd.sage_attn_fp4_fwd(qd, kd, vd, causal=False, fmt=bd.SAGE_BKV256 | bd.SAGE_WG256)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N", [129, 257, 300, 520])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bkv,causal,wg", [(64, False, 0), (64, True, 0), (128, False, 0), (128, True, 0), (256, False, 0),
+                                           (256, True, 0), (256, False, WG)])
+def test_attn_with_and_without_kv_groups(N, D, bkv, causal, wg):
+    """Calls with few query tiles split the KV tiles over two groups of waves and
+    merge them; calls with many do not.  Two heads alone take the first path
+    (where there are two tiles to share), 400 copies of them the second: both
+    meet the oracle's bar, and all copies are the same bits."""
+    torch = torch_dev()
+    say("attn kv groups N=%d D=%d bkv=%d causal=%d wg256=%d" % (N, D, bkv, causal, bool(wg)))
+    in_dtype = N % 2
+    q, k, v = wl.make_inputs(1, 2, N, D, in_dtype, seed=900 + N, k_bias_var=4.0, outlier_frac=0.02)
+    ref, tie, _ = oracle.attn(q, k, v, in_dtype, causal, oracle.FMT_MX, bkv)
+    qd, kd, vd = (to_dev(x, in_dtype) for x in (q, k, v))
+    few = bd.sage_attn_fp4_fwd(qd, kd, vd, causal=causal, fmt=bd.bkv_flag(bkv) | wg)
+    qd, kd, vd = (x.repeat(400, 1, 1, 1) for x in (qd, kd, vd))
+    many = bd.sage_attn_fp4_fwd(qd, kd, vd, causal=causal, fmt=bd.bkv_flag(bkv) | wg)
+    torch.cuda.synchronize()
+    check(few.cpu().numpy().reshape(-1, D), ref, tie, "two heads")
+    check(many[0].cpu().numpy().reshape(-1, D), ref, tie, "many heads")
+    assert torch.equal(many, many[:1].expand_as(many))
