@@ -39,13 +39,15 @@
 // 138 -> 132 us (the forward's share of that included).
 #include "sage_common.h"
 
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 namespace sage {
 
 constexpr int BW_Q = 128;    // query block (psi(Q), psi(dO), P and dS blocks)
 constexpr int BW_K = 128;    // key block
+// accumulators that read as floats (see sage_common.h): forward + backward B1 H32
+// N8192 D128 5225 -> 5160 us; at D = 64 no gain, and 1% lost on short calls
+template <int D> constexpr bool BW_ACC = D == 128;
 constexpr float kBwRoundMagic = 12582912.0f;   // 1.5 * 2^23
 
 template <bool BF16>
@@ -295,6 +297,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     bw_load_ld(lb, drow, L + T::LD_OFF, bh, Np, q0, wave, lane);
   };
 
+  const v16i acc0 = acc_start<BW_ACC<D>>();
   const int i0 = CAUSAL ? kb / BW_Q : 0;
   issue(i0, i0 & 1);
   for (int i = i0; i < nqb; ++i) {
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     float am = -INFINITY;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      v16i sacc = v16i{};
+      v16i sacc = acc0;
 #pragma unroll
       for (int s = 0; s < NKS; ++s)
         sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int e = 4 * g + r;
-          float x = __builtin_fmaf((float)sacc[e], ct, -l4[r]);
+          float x = __builtin_fmaf(acc_f32<BW_ACC<D>>(sacc[e]), ct, -l4[r]);
           if (need_mask) x = bw_mask<CAUSAL>(x, q0 + 32 * u + 4 * hi + 8 * g + r, key, N);
           arg[u][e] = x;
           am = __builtin_fmaxf(am, x);
@@ -349,13 +352,13 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     const float fv = sP * gs[(size_t)bh * nqb + i];
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      v16i dvi = v16i{};
+      v16i dvi = acc0;
 #pragma unroll
       for (int u = 0; u < NU; ++u)
         dvi = __builtin_amdgcn_mfma_i32_32x32x32_i8(
             *reinterpret_cast<const v4i*>(L + T::GT_OFF + (db * 4 + u) * 1024 + lane * 16), pc[u], dvi, 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dva[db][e] = __builtin_fmaf((float)dvi[e], fv, dva[db][e]);
+      for (int e = 0; e < 16; ++e) dva[db][e] = __builtin_fmaf(acc_f32<BW_ACC<D>>(dvi[e]), fv, dva[db][e]);
     }
   }
 
@@ -480,6 +483,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     if (tid < BW_Q) drs[((size_t)lbh * nkb + kblk) * Np + i * BW_Q + tid] = rsv;
     if (tid == 0) dss[pair] = sdsv;
   };
+  const v16i acc0 = acc_start<BW_ACC<D>>();
   const int i0 = CAUSAL ? kb / BW_Q : 0;
   bw_load_ld(lb, drow, lds + (i0 & 1) * T::A_BYTES + T::LD_OFF, bh, Np, i0 * BW_Q, wave, lane);
   issue_A(i0, i0 & 1);
@@ -505,7 +509,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
 #pragma unroll
       for (int uu = 0; uu < 2; ++uu) {
         const int u = 2 * qh + uu;
-        v16i sacc = v16i{};
+        v16i sacc = acc0;
 #pragma unroll
         for (int s = 0; s < NKS; ++s)
           sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(
@@ -522,7 +526,7 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int e = 4 * g + r;
-            float x = __builtin_fmaf((float)sacc[e], ct, -l4[r]);
+            float x = __builtin_fmaf(acc_f32<BW_ACC<D>>(sacc[e]), ct, -l4[r]);
             if constexpr (MASK) x = bw_mask<CAUSAL>(x, q0 + 32 * u + 4 * hi + 8 * g + r, key, N);
             const float p = __builtin_amdgcn_exp2f(x);
             const float y = p * (dp[e] - d4[r]);
@@ -586,13 +590,13 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const int db = qh * NH + h;
-      v16i dki = v16i{};
+      v16i dki = acc0;
 #pragma unroll
       for (int u = 0; u < NU; ++u)
         dki = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i*>(ldsT + (db * 4 + u) * 1024 + lane * 16),
                                                     cs[u], dki, 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dka[h][e] = __builtin_fmaf((float)dki[e], fk, dka[h][e]);
+      for (int e = 0; e < 16; ++e) dka[h][e] = __builtin_fmaf(acc_f32<BW_ACC<D>>(dki[e]), fk, dka[h][e]);
     }
     // the block's staged codes and row sums; they are stored after the next
     // block's first barrier, so the wait in front of it does not wait for them
@@ -686,6 +690,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
 
   int nkb = (N + BW_K - 1) / BW_K;
   if (CAUSAL) nkb = min(nkb, min(q0 + BW_Q - 1, N - 1) / BW_K + 1);
+  const v16i acc0 = acc_start<BW_ACC<D>>();
   issue(0, 0);
   for (int j = 0; j < nkb; ++j) {
     const int kb = j * BW_K, buf = j & 1;
@@ -698,7 +703,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     const bool need_mask = (q0 + BW_Q > N) || (kb + BW_K > N) || (CAUSAL && kb + BW_K - 1 > q0);
     // S^T (exact int32) and dP^T (fp32) of one 32-key subtile
     auto products = [&](int t, v16i& sacc, v16f& dp) {
-      sacc = v16i{};
+      sacc = acc0;
 #pragma unroll
       for (int s = 0; s < NKS; ++s)
         sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(
@@ -724,7 +729,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
         if constexpr (t + 1 < NT) products(t + 1, sacc[(t + 1) & 1], dp[(t + 1) & 1]);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          float arg = __builtin_fmaf((float)sacc[t & 1][e], ct, -lbq);
+          float arg = __builtin_fmaf(acc_f32<BW_ACC<D>>(sacc[t & 1][e]), ct, -lbq);
           if constexpr (MASK) arg = bw_mask<CAUSAL>(arg, qi, kb + 32 * t + 8 * (e >> 2) + 4 * hi + (e & 3), N);
           const float p = __builtin_amdgcn_exp2f(arg);
           const float x = p * (dp[t & 1][e] - dq_row);
@@ -759,7 +764,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     const float rr = (rs + __shfl_xor(rs, 32, 64)) * rsd;   // rowsum(dS) of this lane's query, / sqrt(D)
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      v16i dqi = v16i{};
+      v16i dqi = acc0;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
         dqi = __builtin_amdgcn_mfma_i32_32x32x32_i8(
@@ -770,7 +775,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int e = 4 * g + r;
-          float x = __builtin_fmaf((float)dqi[e], fq, dqa[db][e]);
+          float x = __builtin_fmaf(acc_f32<BW_ACC<D>>(dqi[e]), fq, dqa[db][e]);
           if (kmean != nullptr) x = __builtin_fmaf(rr, km[r], x);
           dqa[db][e] = x;
         }
@@ -851,6 +856,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
   if (CAUSAL) nkb = min(nkb, min(q0 + BW_Q - 1, N - 1) / BW_K + 1);
   v4i dcur[NT], dnext[NT];
   float rcur = 0.0f, rnext = 0.0f;
+  const v16i acc0 = acc_start<BW_ACC<D>>();
   issue(0, 0);
   load_ds(0, dcur, rcur);
   for (int j = 0; j < nkb; ++j) {
@@ -868,7 +874,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
     const float rr = rcur * rsd;
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      v16i dqi = v16i{};
+      v16i dqi = acc0;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
         dqi = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i*>(L + (db * NT + t) * 1024 + lane * 16),
@@ -879,7 +885,7 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int e = 4 * g + r;
-          float x = __builtin_fmaf((float)dqi[e], fq, dqa[db][e]);
+          float x = __builtin_fmaf(acc_f32<BW_ACC<D>>(dqi[e]), fq, dqa[db][e]);
           if (kmean != nullptr) x = __builtin_fmaf(rr, km[r], x);
           dqa[db][e] = x;
         }

@@ -8,6 +8,7 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -150,5 +151,26 @@ __device__ __forceinline__ float fmax3(float a, float b, float c) { return __bui
 // their operands (v_maximum3_f32, v_minimum3_f32).
 __device__ __forceinline__ float smax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 __device__ __forceinline__ float smin(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+
+// int32 MFMA accumulators that read as floats.  Started from the bits of M =
+// 1.5 * 2^23 instead of 0, an accumulator whose sum is below 2^22 in magnitude
+// (127 * 127 * 128 is) holds the bits of the float M + sum, so sum as a float is
+// one exact subtraction.  fp32 add, multiply and fma issue in half the cycles of
+// other VALU instructions here (v_cvt_f32_i32 5.6, v_add_f32 3.5 at four waves
+// per SIMD and the same clock).  The 16 registers are kept, not rebuilt per use.
+// With ON = false both are the plain forms.
+template <bool ON>
+__device__ __forceinline__ v16i acc_start() {
+  if constexpr (!ON) return v16i{};
+  v16i m;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) m[i] = 0x4B400000;
+  asm volatile("" : "+v"(m));
+  return m;
+}
+template <bool ON>
+__device__ __forceinline__ float acc_f32(int bits) {
+  return ON ? __int_as_float(bits) - 12582912.0f : (float)bits;
+}
 
 }  // namespace sage
