@@ -137,41 +137,6 @@ __device__ __forceinline__ float wave_max(float x) {
   return __builtin_fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// ---------------------------------------------------------------------------
-// D_q = sum_d dO[q,d] O[q,d] (fp32) and Lb_q = L_q log2(e), for q < N; rows
-// [N, Np) get 0.  D/8 lanes per row, 8 elements each.
-// ---------------------------------------------------------------------------
-template <int D, bool BF16>
-__global__ __launch_bounds__(256) void i8_bwd_prep_kernel(const uint16_t* __restrict__ dout, const float* __restrict__ o,
-                                                          const float* __restrict__ lse, float* __restrict__ drow,
-                                                          float* __restrict__ lb, int N, int Np, long long rows,
-                                                          float log2e) {
-  constexpr int LPR = D / 8;
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long row = t / LPR;                   // (bh, q) over Np rows per head
-  const int part = (int)(t % LPR);
-  if (row >= rows) return;                         // whole rows: LPR divides the block size
-  const long long bh = row / Np;
-  const int q = (int)(row % Np);
-  float s = 0.0f;
-  if (q < N) {
-    const size_t e = ((size_t)bh * N + q) * D + part * 8;
-    const uint4 g = *reinterpret_cast<const uint4*>(dout + e);
-    const uint16_t* gh = reinterpret_cast<const uint16_t*>(&g);
-    const float4 o0 = *reinterpret_cast<const float4*>(o + e);
-    const float4 o1 = *reinterpret_cast<const float4*>(o + e + 4);
-    const float ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s = __builtin_fmaf(widen<BF16>(gh[i]), ov[i], s);
-  }
-#pragma unroll
-  for (int off = LPR / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (part == 0) {
-    drow[row] = s;
-    lb[row] = q < N ? lse[(size_t)bh * N + q] * log2e : 0.0f;
-  }
-}
-
 __device__ __forceinline__ void bw_wait_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 // vmcnt(n) for the counts used below (n < 16: the low field of the immediate)
 template <int N>
@@ -904,23 +869,6 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
         *reinterpret_cast<float4*>(dq + idx) = make_float4(dqa[db][4 * g], dqa[db][4 * g + 1], dqa[db][4 * g + 2], dqa[db][4 * g + 3]);
       }
   }
-}
-
-hipError_t launch_i8_bwd_prep(const void* dout, const float* o, const float* lse, float* drow, float* lb, int BH,
-                              int N, int Np, int D, bool bf16, hipStream_t st) {
-  const long long rows = (long long)BH * Np;
-  const long long threads = rows * (D / 8);
-  const dim3 grid((unsigned)((threads + 255) / 256)), block(256);
-  const float log2e = 1.44269504088896340736f;
-  const uint16_t* g = static_cast<const uint16_t*>(dout);
-  if (D == 128) {
-    if (bf16) hipLaunchKernelGGL((i8_bwd_prep_kernel<128, true>), grid, block, 0, st, g, o, lse, drow, lb, N, Np, rows, log2e);
-    else hipLaunchKernelGGL((i8_bwd_prep_kernel<128, false>), grid, block, 0, st, g, o, lse, drow, lb, N, Np, rows, log2e);
-  } else {
-    if (bf16) hipLaunchKernelGGL((i8_bwd_prep_kernel<64, true>), grid, block, 0, st, g, o, lse, drow, lb, N, Np, rows, log2e);
-    else hipLaunchKernelGGL((i8_bwd_prep_kernel<64, false>), grid, block, 0, st, g, o, lse, drow, lb, N, Np, rows, log2e);
-  }
-  return hipGetLastError();
 }
 
 template <int D, bool CAUSAL, bool BF16>

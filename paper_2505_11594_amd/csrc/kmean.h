@@ -1,0 +1,72 @@
+// Partial sums of smoothing K's channel mean, shared by the FP4 and the INT8 quantizers.
+#pragma once
+#include "sage_common.h"
+
+namespace sage {
+
+// ---------------------------------------------------------------------------
+// Smoothing K, pass 1: per-chunk fp64 column sums.  Block (chunk, bh) sums
+// tokens [chunk * KM_CHUNK, ...) of K[bh] for every channel.  Every value is a
+// 16-bit float, so the fp64 partial sums are exact for the token counts used
+// here and the final mean does not depend on the summation order.
+// ---------------------------------------------------------------------------
+constexpr int KM_CHUNK = 512;
+constexpr int KM_THREADS = 256;
+
+typedef double KmRed[KM_THREADS][9];         // padded against bank conflicts
+
+template <int D, bool BF16>
+__device__ __forceinline__ void kmean_partial(const uint16_t* __restrict__ k, double* __restrict__ part, int N,
+                                              int nchunk, int chunk, int bh, KmRed& red) {
+  constexpr int CG = D / 8;                  // 8-channel groups per row (16 bytes)
+  constexpr int RS = KM_THREADS / CG;        // rows handled in parallel
+  const int tid = threadIdx.x;
+  const int cg = tid % CG, rsub = tid / CG;
+  const int t0 = chunk * KM_CHUNK;
+  const int t1 = min(N, t0 + KM_CHUNK);
+  const uint16_t* kb = k + (size_t)bh * N * D;
+  double acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+  for (int t = t0 + rsub; t < t1; t += RS) {
+    uint4 raw = *reinterpret_cast<const uint4*>(kb + (size_t)t * D + cg * 8);
+    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] += (double)widen<BF16>(h[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) red[tid][i] = acc[i];
+  __syncthreads();
+  if (tid < D) {
+    const int c = tid, g = c / 8, i = c % 8;
+    double s = 0.0;
+    for (int r = 0; r < RS; ++r) s += red[r * CG + g][i];
+    part[((size_t)bh * nchunk + chunk) * D + c] = s;
+  }
+}
+
+// Partial sums of up to this many chunks are added by K's quantizer itself
+// (each of its workgroups reads them all), more by a pass of their own.
+constexpr int KM_INLINE = 8;
+
+// mean[c] = fl32(sum of the head's partial sums / N), by the first D threads;
+// `store`: also into mu[bh].  Ends with a barrier.
+template <int D>
+__device__ __forceinline__ void kmean_inline(const double* __restrict__ part, float* __restrict__ mu, int N, int nchunk,
+                                             int bh, bool store, float (&mean)[D]) {
+  const int tid = threadIdx.x;
+  if (tid < D) {
+    double s = 0.0;
+    for (int j = 0; j < nchunk; ++j) s += part[((size_t)bh * nchunk + j) * D + tid];
+    const float m = (float)(s / (double)N);
+    mean[tid] = m;
+    if (store) mu[(size_t)bh * D + tid] = m;
+  }
+  __syncthreads();
+}
+
+int kmean_chunks(int N);
+hipError_t launch_kmean_partial(const void* k, double* part, int BH, int N, int D, bool bf16, hipStream_t st);
+hipError_t launch_kmean_final(const double* part, float* mu, int BH, int N, int D, hipStream_t st);
+
+}  // namespace sage

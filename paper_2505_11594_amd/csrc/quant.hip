@@ -16,50 +16,10 @@
 #include <algorithm>
 #include <climits>
 
+#include "kmean.h"
 #include "sage_common.h"
 
 namespace sage {
-
-// ---------------------------------------------------------------------------
-// Smoothing K, pass 1: per-chunk fp64 column sums.  Block (chunk, bh) sums
-// tokens [chunk * KM_CHUNK, ...) of K[bh] for every channel.  Every value is a
-// 16-bit float, so the fp64 partial sums are exact for the token counts used
-// here and the final mean does not depend on the summation order.
-// ---------------------------------------------------------------------------
-constexpr int KM_CHUNK = 512;
-constexpr int KM_THREADS = 256;
-
-typedef double KmRed[KM_THREADS][9];         // padded against bank conflicts
-
-template <int D, bool BF16>
-__device__ __forceinline__ void kmean_partial(const uint16_t* __restrict__ k, double* __restrict__ part, int N,
-                                              int nchunk, int chunk, int bh, KmRed& red) {
-  constexpr int CG = D / 8;                  // 8-channel groups per row (16 bytes)
-  constexpr int RS = KM_THREADS / CG;        // rows handled in parallel
-  const int tid = threadIdx.x;
-  const int cg = tid % CG, rsub = tid / CG;
-  const int t0 = chunk * KM_CHUNK;
-  const int t1 = min(N, t0 + KM_CHUNK);
-  const uint16_t* kb = k + (size_t)bh * N * D;
-  double acc[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-  for (int t = t0 + rsub; t < t1; t += RS) {
-    uint4 raw = *reinterpret_cast<const uint4*>(kb + (size_t)t * D + cg * 8);
-    const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] += (double)widen<BF16>(h[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) red[tid][i] = acc[i];
-  __syncthreads();
-  if (tid < D) {
-    const int c = tid, g = c / 8, i = c % 8;
-    double s = 0.0;
-    for (int r = 0; r < RS; ++r) s += red[r * CG + g][i];
-    part[((size_t)bh * nchunk + chunk) * D + c] = s;
-  }
-}
 
 template <int D, bool BF16>
 __global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_t* __restrict__ k,
@@ -357,8 +317,6 @@ __global__ __launch_bounds__(256) void quant_q_smooth_kernel(const uint16_t* __r
 // KM_INLINE chunks) summed here from the partial sums, which saves the pass
 // between them -- and stores each token at its permuted position.  Rows N ..
 // Np - 1 get zero codes and unit scales.
-constexpr int KM_INLINE = 8;
-
 template <int D, bool BF16, int FMT>
 __global__ __launch_bounds__(256) void quant_k_kernel(const uint16_t* __restrict__ x, const double* __restrict__ part,
                                                       float* __restrict__ mu, uint8_t* __restrict__ codes,
@@ -377,14 +335,7 @@ __global__ __launch_bounds__(256) void quant_k_kernel(const uint16_t* __restrict
   float m8[8];
   if (part != nullptr) {
     __shared__ float mean[D];
-    if (tid < D) {
-      double s = 0.0;
-      for (int j = 0; j < nchunk; ++j) s += part[((size_t)bh * nchunk + j) * D + tid];
-      const float m = (float)(s / (double)N);
-      mean[tid] = m;
-      if (t0 == 0) mu[(size_t)bh * D + tid] = m;
-    }
-    __syncthreads();
+    kmean_inline<D>(part, mu, N, nchunk, bh, t0 == 0, mean);
 #pragma unroll
     for (int i = 0; i < 8; ++i) m8[i] = mean[cg * 8 + i];
   } else {
@@ -623,25 +574,20 @@ static hipError_t quant_dispatch(int D, bool bf16, int fmt, F&& f) {
   return bf16 ? f(ic<64>{}, ic<1>{}, ic<kFmtNV16>{}) : f(ic<64>{}, ic<0>{}, ic<kFmtNV16>{});
 }
 
-static hipError_t launch_kmean_final(const double* part, float* mu, int BH, int N, int D, hipStream_t st) {
+hipError_t launch_kmean_final(const double* part, float* mu, int BH, int N, int D, hipStream_t st) {
   const int nchunk = kmean_chunks(N);
   if (D == 128) hipLaunchKernelGGL((kmean_final_kernel<128>), dim3(BH), dim3(256), 0, st, part, mu, N, nchunk);
   else hipLaunchKernelGGL((kmean_final_kernel<64>), dim3(BH), dim3(256), 0, st, part, mu, N, nchunk);
   return hipGetLastError();
 }
 
-static hipError_t launch_kmean_partial(const void* k, double* part, int BH, int N, int D, bool bf16, hipStream_t st) {
+hipError_t launch_kmean_partial(const void* k, double* part, int BH, int N, int D, bool bf16, hipStream_t st) {
   const int nchunk = kmean_chunks(N);
   return quant_dispatch(D, bf16, kFmtMX, [&](auto D_, auto B_, auto) {
     hipLaunchKernelGGL((kmean_partial_kernel<decltype(D_)::value, decltype(B_)::value != 0>), dim3(nchunk, BH),
                        dim3(KM_THREADS), 0, st, (const uint16_t*)k, part, N, nchunk);
     return hipGetLastError();
   });
-}
-
-hipError_t launch_kmean(const void* k, double* part, float* mu, int BH, int N, int D, bool bf16, hipStream_t st) {
-  const hipError_t e = launch_kmean_partial(k, part, BH, N, D, bf16, st);
-  return e != hipSuccess ? e : launch_kmean_final(part, mu, BH, N, D, st);
 }
 
 // K's codes and scales; mu null without smoothing.  part: the partial sums of

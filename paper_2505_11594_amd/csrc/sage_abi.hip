@@ -10,7 +10,6 @@
 #include "sage_mi355x.h"
 
 namespace sage {
-hipError_t launch_kmean(const void* k, double* part, float* mu, int BH, int N, int D, bool bf16, hipStream_t st);
 int kmean_chunks(int N);
 hipError_t launch_quant_q(const void* q, float* qbar, void* codes, void* scales, int BH, int N, int D, int fmt,
                           bool bf16, hipStream_t st);
@@ -33,13 +32,21 @@ hipError_t launch_attn_nv16(const void* qc, const void* qs, const void* kc, cons
 size_t nv16_expand_bytes(int BH, int Np, int D);
 hipError_t launch_attn_bf16(const void* q, const void* k, const void* v, void* o, int BH, int N, int D, bool causal,
                             bool out_f32, float c2, hipStream_t st);
-hipError_t launch_quant_i8(const void* x, const float* mu, void* codes, float* scales, int BH, int N, int Nout,
-                           int D, int R, int role, bool bf16, hipStream_t st);
+hipError_t launch_quant_i8_q(const void* q, void* codes, float* scales, int BH, int N, int D, bool bf16, hipStream_t st);
+hipError_t launch_quant_i8_k(const void* k, double* part, float* mu, void* codes, float* scales, int BH, int N, int Np,
+                             int D, int R, bool bf16, hipStream_t st);
+hipError_t launch_quant_i8_v(const void* v, void* codes, float* scales, int BH, int N, int Np, int D, int R, bool bf16,
+                             hipStream_t st);
+hipError_t launch_quant_i8_qkv(const void* q, const void* k, const void* v, void* qc, float* qs, void* kc, float* ks,
+                               void* vc, float* vs, double* part, float* mu, int BH, int N, int Np, int D, int R,
+                               bool bf16, hipStream_t st);
+hipError_t launch_quant_i8_bwd(const void* q, const void* k, const void* dout, const float* o, const float* lse, void* qc,
+                               float* qs, void* qt, void* kc, float* ks, void* kt, void* gt, float* gs, float* drow,
+                               float* lb, double* part, float* mu, int BH, int N, int Np, int D, bool bf16,
+                               hipStream_t st);
 hipError_t launch_attn_int8(const void* qc, const float* qs, const void* kc, const float* ks, const void* vc,
                             const float* vs, void* o, float* lse, int BH, int N, int Np, int D, int bkv, bool causal,
                             int out, float c2, float log127, hipStream_t st);
-hipError_t launch_i8_bwd_prep(const void* dout, const float* o, const float* lse, float* drow, float* lb, int BH,
-                              int N, int Np, int D, bool bf16, hipStream_t st);
 hipError_t launch_attn_int8_bwd(const void* qc, const float* qs, const void* qt, const void* kc, const float* ks,
                                 const void* kt, const void* v, const void* dout, const void* gt, const float* gs,
                                 const float* drow, const float* lb, const float* kmean, float* dq, float* dk, float* dv,
@@ -256,21 +263,13 @@ int quant_i8_impl(const void* x, int role, int B, int H, int N, int D, unsigned 
                   float* kmean, void* ws, hipStream_t st) {
   const bool bf16 = (flags & SAGE_IN_BF16) != 0;
   const int BH = B * H;
-  hipError_t e = hipSuccess;
-  if (role == SAGE_ROLE_Q) {
-    e = sage::launch_quant_i8(x, nullptr, codes, scales, BH, N, N, D, kI8Bq, 0, bf16, st);
-  } else if (role == SAGE_ROLE_K) {
+  if (role == SAGE_ROLE_Q) return hip_status(sage::launch_quant_i8_q(x, codes, scales, BH, N, D, bf16, st));
+  if (role == SAGE_ROLE_K) {
     const bool smooth = !(flags & SAGE_NO_SMOOTH_K);
-    if (smooth) {
-      e = sage::launch_kmean(x, static_cast<double*>(ws), kmean, BH, N, D, bf16, st);
-      if (e != hipSuccess) return SAGE_ERR_HIP;
-    }
-    e = sage::launch_quant_i8(x, smooth ? kmean : nullptr, codes, scales, BH, N, pad128(N), D, i8_bkv(flags), 1,
-                              bf16, st);
-  } else {
-    e = sage::launch_quant_i8(x, nullptr, codes, scales, BH, N, pad128(N), D, i8_bkv(flags), 2, bf16, st);
+    return hip_status(sage::launch_quant_i8_k(x, smooth ? static_cast<double*>(ws) : nullptr, smooth ? kmean : nullptr,
+                                              codes, scales, BH, N, pad128(N), D, i8_bkv(flags), bf16, st));
   }
-  return hip_status(e);
+  return hip_status(sage::launch_quant_i8_v(x, codes, scales, BH, N, pad128(N), D, i8_bkv(flags), bf16, st));
 }
 
 inline float log2_of_127() { return (float)std::log2(127.0); }
@@ -290,9 +289,11 @@ int attn_i8_ws_impl(const void* q, const void* k, const void* v, void* o, float*
   float* ks = reinterpret_cast<float*>(base + w.ks);
   float* vs = reinterpret_cast<float*>(base + w.vs);
   float* mu = reinterpret_cast<float*>(base + w.mu);
-  int rc = quant_i8_impl(q, SAGE_ROLE_Q, B, H, N, D, flags, base + w.qc, qs, nullptr, nullptr, st);
-  if (rc == SAGE_OK) rc = quant_i8_impl(k, SAGE_ROLE_K, B, H, N, D, flags, base + w.kc, ks, mu, base + w.part, st);
-  if (rc == SAGE_OK) rc = quant_i8_impl(v, SAGE_ROLE_V, B, H, N, D, flags, base + w.vc, vs, nullptr, nullptr, st);
+  const bool smooth = !(flags & SAGE_NO_SMOOTH_K);
+  int rc = hip_status(sage::launch_quant_i8_qkv(q, k, v, base + w.qc, qs, base + w.kc, ks, base + w.vc, vs,
+                                                smooth ? reinterpret_cast<double*>(base + w.part) : nullptr,
+                                                smooth ? mu : nullptr, B * H, N, pad128(N), D, i8_bkv(flags),
+                                                (flags & SAGE_IN_BF16) != 0, st));
   if (rc == SAGE_OK)
     rc = attn_i8_prequant_impl(base + w.qc, qs, base + w.kc, ks, base + w.vc, vs, o, lse, B, H, N, D, causal, flags,
                                st);
@@ -372,15 +373,12 @@ int attn_i8_bwd_ws_impl(const void* q, const void* k, const void* v, const float
   float* mu = reinterpret_cast<float*>(base + w.mu);
   float* drow = reinterpret_cast<float*>(base + w.drow);
   float* lb = reinterpret_cast<float*>(base + w.lb);
-  // psi of Q (row-major and transposed), K' (both), dO (transposed): blocks of 128 rows
-  hipError_t e = sage::launch_quant_i8(q, nullptr, base + w.qc, qs, BH, N, N, D, 128, 0, bf16, st);
-  if (e == hipSuccess) e = sage::launch_quant_i8(q, nullptr, base + w.qt, qs, BH, N, Np, D, 128, 2, bf16, st);
-  if (e == hipSuccess && smooth) e = sage::launch_kmean(k, reinterpret_cast<double*>(base + w.part), mu, BH, N, D, bf16, st);
-  const float* mup = smooth ? mu : nullptr;
-  if (e == hipSuccess) e = sage::launch_quant_i8(k, mup, base + w.kc, ks, BH, N, Np, D, 128, 1, bf16, st);
-  if (e == hipSuccess) e = sage::launch_quant_i8(k, mup, base + w.kt, ks, BH, N, Np, D, 128, 3, bf16, st);
-  if (e == hipSuccess) e = sage::launch_quant_i8(dout, nullptr, base + w.gt, gs, BH, N, Np, D, 128, 2, bf16, st);
-  if (e == hipSuccess) e = sage::launch_i8_bwd_prep(dout, o, lse, drow, lb, BH, N, Np, D, bf16, st);
+  // psi of Q (row-major and transposed), K' (both), dO (transposed): blocks of 128 rows; D and L log2(e)
+  float* const mup = smooth ? mu : nullptr;
+  hipError_t e = sage::launch_quant_i8_bwd(q, k, dout, o, lse, base + w.qc, qs, base + w.qt, base + w.kc, ks, base + w.kt,
+                                           base + w.gt, gs, drow, lb,
+                                           smooth ? reinterpret_cast<double*>(base + w.part) : nullptr, mup, BH, N, Np, D,
+                                           bf16, st);
   if (e == hipSuccess)
     e = sage::launch_attn_int8_bwd(base + w.qc, qs, base + w.qt, base + w.kc, ks, base + w.kt, v, dout, base + w.gt, gs,
                                    drow, lb, mup, dq, dk, dv, base + w.ds, G, BH, N, Np, D, causal != 0, bf16,
