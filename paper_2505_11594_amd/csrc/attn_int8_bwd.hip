@@ -343,26 +343,32 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
 // dK.  dK^T = Q^T dS^ per query block: S = Q^ K^T and dP = dO V^T of each
 // 32-query subtile, P = exp2(S c_t - Lb), dS = P (dP - D); dS of the whole
 // block stays in registers while its maximum is reduced across the waves,
-// then psi of dS and the product.  Eight waves, two per 32-key group: wave
-// (kg, qh) forms S, dP and dS of subtiles 2qh and 2qh + 1 for its keys, the
-// waves swap their dS^ codes through LDS, and each wave then runs the product
-// over all four subtiles for half of the channel blocks -- the int32 block
-// products stay whole, and each wave holds half the fp32 accumulators, which
-// lets two waves share a SIMD.  The query block's Q^ and dO (double-buffered)
-// and Q^T (single: loaded after the block's first barrier, waited for before
-// its second) are staged in LDS.  qt: Q^T int8 [BH, D, Np] permuted per 32
-// rows.
+// then psi of dS and the product, whose B operands are the wave's own codes.
+// Four waves of 32 keys (QH = 1); the query block's Q^ and dO are staged in one
+// LDS buffer (the next block's loads are issued after the block's second
+// barrier, when every wave has read it) and Q^T in another (loaded after the
+// first, waited for before the second), so that two workgroups share a CU and
+// overlap each other's phases: the MFMA and the softmax halves of a block hardly
+// overlap inside one workgroup.  One workgroup of eight waves per CU, with the
+// operands double-buffered and the stored codes staged in LDS, took 2535 us on
+// B1 H32 N8192 D128, this 1988.
+// QH = 2, for grids that leave CUs idle: eight waves, two per key group; wave
+// (kg, qh) forms dS of subtiles 2qh and 2qh + 1, the waves swap their codes
+// through LDS, and each runs the product over all four subtiles for half of the
+// channel blocks (the int32 block products stay whole, so both give the same
+// bits).  B2 H12 N1000 D64 causal (192 workgroups): 29 us, with QH = 1 36.
+// qt: Q^T int8 [BH, D, Np] permuted per 32 rows.
 // ---------------------------------------------------------------------------
-constexpr int BW_DK_WAVES = 8;
-
-template <int D>
+template <int D, int QH>
 struct BwDkLds {
+  static constexpr int W = 4 * QH;
   static constexpr int NKS = D / 32, NKS16 = D / 16, NDB = D / 32;
   static constexpr int NQA = 4 * NKS, NGA = 4 * NKS16, NT = NDB * 4;
-  static constexpr int QA_OFF = 0, GA_OFF = NQA * 1024, LD_OFF = GA_OFF + NGA * 1024, A_BYTES = LD_OFF + 1024;
-  static constexpr int T_BYTES = NT * 1024;
-  static constexpr int AJ = (NQA + NGA) / BW_DK_WAVES, TJ = NT / BW_DK_WAVES;   // loads per wave
-  static_assert((NQA + NGA) % BW_DK_WAVES == 0 && NT % BW_DK_WAVES == 0, "even split over the waves");
+  static constexpr int QA_OFF = 0, GA_OFF = NQA * 1024, LD_OFF = GA_OFF + NGA * 1024, T_OFF = LD_OFF + 1024;
+  static constexpr int RED2_OFF = T_OFF + NT * 1024, CX_OFF = RED2_OFF + 4 * BW_Q * 4;
+  static constexpr int RED_OFF = CX_OFF + (QH == 2 ? 16 * 1024 : 0), BYTES = RED_OFF + 2 * W * 4;
+  static constexpr int AJ = (NQA + NGA) / W, TJ = NT / W;   // loads per wave
+  static_assert((NQA + NGA) % W == 0 && NT % W == 0, "even split over the waves");
 };
 
 // STORE_DS: also write, for every (query block, KV block) pair, the dS^ codes
@@ -371,35 +377,31 @@ struct BwDkLds {
 // query 32w + l%32 and the 16 keys at positions [16 (l/32), +16) of subtile t,
 // position 16h + 4g + r holding key 8g + 4h + r), s_dS of the pair, and the
 // pair's row sums of the unquantized dS (one per query, [KV block][query]).
-// The codes go through LDS (a byte transpose inside each quad of lanes, then
-// dword writes in place) and leave with whole 16-byte vector stores; the row
-// sums are reduced across lanes in registers.  Heads are
+// The codes are stored from registers after a byte transpose inside each quad
+// of lanes (a wave's store is four runs of 64 bytes); the row sums are reduced
+// across lanes in registers, across the waves in LDS.  Heads are
 // bh0 + blockIdx.y; the stored arrays are indexed by blockIdx.y.
-template <int D, bool CAUSAL, bool BF16, bool STORE_DS>
-__global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
+template <int D, bool CAUSAL, bool BF16, bool STORE_DS, int QH>
+__global__ __launch_bounds__(256 * QH, 2 / QH) void attn_i8_bwd_dk_kernel(
     const int8_t* __restrict__ qc, const float* __restrict__ qs, const int8_t* __restrict__ qt,
     const int8_t* __restrict__ kc, const float* __restrict__ ks, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ drow, const float* __restrict__ lb,
     float* __restrict__ dk, int8_t* __restrict__ dsc, float* __restrict__ dss, float* __restrict__ drs, int N, int Np,
     int nqb, int bh0, float c2, float rsd) {
-  using T = BwDkLds<D>;
-  constexpr int NKS = T::NKS, NKS16 = T::NKS16, NDB = T::NDB, NU = BW_Q / 32, NH = NDB / 2;
-  constexpr int T_OFF = 2 * T::A_BYTES, CX_OFF = T_OFF + T::T_BYTES, DSL_OFF = CX_OFF + 4 * NU * 1024;
-  constexpr int RED2_OFF = DSL_OFF + (STORE_DS ? 16 * 1024 : 0), RED_OFF = RED2_OFF + (STORE_DS ? 4 * BW_Q * 4 : 0);
-  __shared__ __attribute__((aligned(16))) uint8_t lds[RED_OFF + 2 * BW_DK_WAVES * 4];
-  uint8_t* const ldsT = lds + T_OFF;
-  uint8_t* const cx = lds + CX_OFF;                 // dS^ codes: (key group, subtile) blocks
-  uint8_t* const dsl = lds + DSL_OFF;
-  float* const red2 = reinterpret_cast<float*>(lds + RED2_OFF);
-  float* const red = reinterpret_cast<float*>(lds + RED_OFF);   // [2][BW_DK_WAVES] wave maxima
+  using T = BwDkLds<D, QH>;
+  constexpr int NKS = T::NKS, NKS16 = T::NKS16, W = T::W, NU = BW_Q / 32;
+  constexpr int NUW = NU / QH, NDBW = T::NDB / QH;                   // subtiles and channel blocks per wave
+  __shared__ __attribute__((aligned(16))) uint8_t lds[T::BYTES];
+  float* const red2 = reinterpret_cast<float*>(lds + T::RED2_OFF);   // [4][BW_Q] row sums per key group
+  float* const red = reinterpret_cast<float*>(lds + T::RED_OFF);     // [2][W] wave maxima
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave & 3, qh = wave >> 2;          // key group; query half (subtiles 2qh, 2qh + 1); channel half
+  const int kg = QH == 1 ? wave : wave % 4, qh = QH == 1 ? 0 : wave / 4;   // key group; query and channel half
   const int col = lane & 31, hi = lane >> 5;
   const int kblk = blockIdx.x, lbh = blockIdx.y, bh = bh0 + lbh;
   const int nkb = Np / BW_K;
   const int kb = kblk * BW_K, key = kb + 32 * kg + col;
-  const float sK = ks[(size_t)bh * (Np / BW_K) + kblk];
+  const float sK = ks[(size_t)bh * nkb + kblk];
 
   // B operands of this lane's key: K^ (channels [32s + 16hi, +16)) and V
   // (16-bit, channels [16s + 8hi, +8))
@@ -413,77 +415,70 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     for (int s = 0; s < NKS16; ++s)
       vreg[s] = key < N ? *reinterpret_cast<const v4i*>(vr + 16 * s + 8 * hi) : v4i{0, 0, 0, 0};
   }
-  v16f dka[NH];                                      // channel blocks qh NH + h
+  v16f dka[NDBW];                                    // channel blocks qh NDBW + h
 #pragma unroll
-  for (int h = 0; h < NH; ++h) dka[h] = v16f{};
+  for (int h = 0; h < NDBW; ++h) dka[h] = v16f{};
 
-  auto issue_A = [&](int i, int buf) {
+  auto issue_A = [&](int i) {
     const int q0 = i * BW_Q;
-    uint8_t* L = lds + buf * T::A_BYTES;
     const __amdgpu_buffer_rsrc_t rq = bw_rows_rsrc<D, 1>(qc, bh, N, q0), rg = bw_rows_rsrc<D, 2>(dout, bh, N, q0);
 #pragma unroll
     for (int k = 0; k < T::AJ; ++k) {
-      const int b = wave + BW_DK_WAVES * k, g = b - T::NQA;
-      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::QA_OFF + b * 1024);
-      else buf_load16(rg, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), L + T::GA_OFF + g * 1024);
+      const int b = wave + W * k, g = b - T::NQA;
+      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), lds + T::QA_OFF + b * 1024);
+      else buf_load16(rg, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), lds + T::GA_OFF + g * 1024);
     }
+    bw_load_ld(lb, drow, lds + T::LD_OFF, bh, Np, q0, wave, lane);
   };
   auto issue_T = [&](int i) {
     const __amdgpu_buffer_rsrc_t rt = bw_cols_rsrc<D>(qt, bh, Np, i * BW_Q);
 #pragma unroll
     for (int k = 0; k < T::TJ; ++k) {
-      const int t = wave + BW_DK_WAVES * k;
-      buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, t), ldsT + t * 1024);
+      const int t = wave + W * k;
+      buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, t), lds + T::T_OFF + t * 1024);
     }
   };
-
-  // the dS^ state of one block, from registers (see the end of the loop)
-  v4i dsv[16 / BW_DK_WAVES];
-  float rsv = 0.0f, sdsv = 0.0f;
-  auto store_ds = [&](int i) {
-    const size_t pair = ((size_t)lbh * nqb + i) * nkb + kblk;
-#pragma unroll
-    for (int b2 = 0; b2 < 16 / BW_DK_WAVES; ++b2)
-      *reinterpret_cast<v4i*>(dsc + (pair * 16 + wave * (16 / BW_DK_WAVES) + b2) * 1024 + lane * 16) = dsv[b2];
-    if (tid < BW_Q) drs[((size_t)lbh * nkb + kblk) * Np + i * BW_Q + tid] = rsv;
-    if (tid == 0) dss[pair] = sdsv;
+  // row sums and s_dS of block i, after the barrier that follows it
+  float sdS = 0.0f;
+  auto store_rs = [&](int i) {
+    if (tid < BW_Q)
+      drs[((size_t)lbh * nkb + kblk) * Np + i * BW_Q + tid] =
+          (red2[tid] + red2[BW_Q + tid]) + (red2[2 * BW_Q + tid] + red2[3 * BW_Q + tid]);
+    if (tid == 0) dss[((size_t)lbh * nqb + i) * nkb + kblk] = sdS;
   };
+
   const v16i acc0 = acc_start<BW_ACC<D>>();
   const int i0 = CAUSAL ? kb / BW_Q : 0;
-  bw_load_ld(lb, drow, lds + (i0 & 1) * T::A_BYTES + T::LD_OFF, bh, Np, i0 * BW_Q, wave, lane);
-  issue_A(i0, i0 & 1);
+  if (i0 < nqb) issue_A(i0);
   for (int i = i0; i < nqb; ++i) {
     const int q0 = i * BW_Q, a = i & 1;
     bw_wait_all();                                 // this wave's loads of block i have landed
     __syncthreads();                               // everyone's; every wave is done with block i - 1
-    if (STORE_DS && i > i0) store_ds(i - 1);
-    if (i + 1 < nqb) bw_load_ld(lb, drow, lds + (a ^ 1) * T::A_BYTES + T::LD_OFF, bh, Np, q0 + BW_Q, wave, lane);
     issue_T(i);
-    if (i + 1 < nqb) issue_A(i + 1, a ^ 1);
-    const uint8_t* L = lds + a * T::A_BYTES;
+    if (STORE_DS && i > i0) store_rs(i - 1);
     const float sQ = qs[(size_t)bh * nqb + i];
     const float ct = __builtin_fmaxf(sQ * sK * c2, 1.17549435e-38f);   // see the forward kernel
     const bool need_mask = (q0 + BW_Q > N) || (kb + BW_K > N) || (CAUSAL && q0 < kb + BW_K - 1);
 
-    // dS of this wave's two subtiles u = 2qh + uu: element v is query
-    // q0 + 32u + 8(v>>2) + 4hi + (v&3); the masking choice is made per block
-    float dS[2][16];
+    // dS of this wave's subtiles of the block: element v of subtile u is query q0 + 32u + 8(v>>2) + 4hi + (v&3); the masking
+    // choice is made per block
+    float dS[NUW][16];
     float dm = 0.0f;
     auto phase1 = [&](auto MASK_) {
       constexpr bool MASK = decltype(MASK_)::value != 0;
 #pragma unroll
-      for (int uu = 0; uu < 2; ++uu) {
-        const int u = 2 * qh + uu;
+      for (int uu = 0; uu < NUW; ++uu) {
+        const int u = NUW * qh + uu;
         v16i sacc = acc0;
 #pragma unroll
         for (int s = 0; s < NKS; ++s)
           sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-              *reinterpret_cast<const v4i*>(L + T::QA_OFF + (u * NKS + s) * 1024 + lane * 16), kreg[s], sacc, 0, 0, 0);
+              *reinterpret_cast<const v4i*>(lds + T::QA_OFF + (u * NKS + s) * 1024 + lane * 16), kreg[s], sacc, 0, 0, 0);
         v16f dp = v16f{};
 #pragma unroll
         for (int s = 0; s < NKS16; ++s)
-          dp = mfma16<BF16>(*reinterpret_cast<const v4i*>(L + T::GA_OFF + (u * NKS16 + s) * 1024 + lane * 16), vreg[s], dp);
-        const float* lbr = reinterpret_cast<const float*>(L + T::LD_OFF) + 32 * u + 4 * hi;
+          dp = mfma16<BF16>(*reinterpret_cast<const v4i*>(lds + T::GA_OFF + (u * NKS16 + s) * 1024 + lane * 16), vreg[s], dp);
+        const float* lbr = reinterpret_cast<const float*>(lds + T::LD_OFF) + 32 * u + 4 * hi;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const v4f l4 = *reinterpret_cast<const v4f*>(lbr + 8 * g);
@@ -504,30 +499,32 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
     if (need_mask) phase1(ic<1>{});
     else phase1(ic<0>{});
     dm = wave_max(dm);
-    if (lane == 0) red[a * BW_DK_WAVES + wave] = dm;
-    // the T loads of this block were issued before the next block's A loads
-    if (i + 1 < nqb) bw_wait_vm<T::AJ>();
-    else bw_wait_all();
+    if (lane == 0) red[W * a + wave] = dm;
+    bw_wait_all();                                 // this wave's loads of Q^T
     bw_lds_barrier();
+    if (i + 1 < nqb) issue_A(i + 1);
     dm = 0.0f;
 #pragma unroll
-    for (int w = 0; w < BW_DK_WAVES; ++w) dm = __builtin_fmaxf(dm, red[a * BW_DK_WAVES + w]);
-    const float sdS = dm / 127.0f, rdS = dm > 0.0f ? 1.0f / sdS : 0.0f;
+    for (int w = 0; w < W; ++w) dm = __builtin_fmaxf(dm, red[W * a + w]);
+    sdS = dm / 127.0f;
+    const float rdS = dm > 0.0f ? 1.0f / sdS : 0.0f;
 
+    v4i sc[NU];
+    uint8_t* const dst = reinterpret_cast<uint8_t*>(dsc) + (((size_t)lbh * nqb + i) * nkb + kblk) * 16384;
 #pragma unroll
-    for (int uu = 0; uu < 2; ++uu) {
-      const int u = 2 * qh + uu;
-      const v4i sc = bw_codes(dS[uu], rdS);
-      *reinterpret_cast<v4i*>(cx + (kg * NU + u) * 1024 + lane * 16) = sc;
+    for (int uu = 0; uu < NUW; ++uu) {
+      const int u = NUW * qh + uu;
+      sc[uu] = bw_codes(dS[uu], rdS);
+      if constexpr (QH == 2) *reinterpret_cast<v4i*>(lds + T::CX_OFF + (kg * NU + u) * 1024 + lane * 16) = sc[uu];
       if constexpr (STORE_DS) {
-        // codes: byte e = 4g + r of sc is query 32u + 8g + 4hi + r and key
-        // 32 kg + col; after the quad transpose this lane holds query
-        // 32u + 8g + 4hi + (col & 3) for keys 4 (col >> 2) + [0, 4)
+        // byte e = 4g + r of sc is query 32u + 8g + 4hi + r and key 32 kg + col;
+        // after the quad transpose this lane holds query 32u + 8g + 4hi + (col & 3)
+        // for keys 4 (col >> 2) + [0, 4)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const uint32_t t = quad_byte_transpose((uint32_t)sc[g], lane);
+          const uint32_t t = quad_byte_transpose((uint32_t)sc[uu][g], lane);
           const int m = col >> 2, lq = 8 * g + 4 * hi + (col & 3) + 32 * (m & 1);
-          *reinterpret_cast<uint32_t*>(dsl + (u * 4 + kg) * 1024 + lq * 16 + 4 * (m >> 1)) = t;
+          *reinterpret_cast<uint32_t*>(dst + (u * 4 + kg) * 1024 + lq * 16 + 4 * (m >> 1)) = t;
         }
         // row sums of dS over this wave's 32 keys: a butterfly over the 32
         // lanes that share hi (partners lane ^ 16, row rotation by 8, half-row
@@ -547,41 +544,36 @@ __global__ __launch_bounds__(64 * BW_DK_WAVES, 1) void attn_i8_bwd_dk_kernel(
         }
       }
     }
-    bw_lds_barrier();                              // every wave's codes (and, storing dS^, its staging) are in LDS
-    v4i cs[NU];
+    if constexpr (QH == 2) {
+      bw_lds_barrier();                            // every wave's codes are in LDS
 #pragma unroll
-    for (int u = 0; u < NU; ++u) cs[u] = *reinterpret_cast<const v4i*>(cx + (kg * NU + u) * 1024 + lane * 16);
+      for (int u = 0; u < NU; ++u) sc[u] = *reinterpret_cast<const v4i*>(lds + T::CX_OFF + (kg * NU + u) * 1024 + lane * 16);
+    }
     const float fk = (sdS * sQ) * rsd;
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const int db = qh * NH + h;
+    for (int h = 0; h < NDBW; ++h) {
+      const int db = qh * NDBW + h;
       v16i dki = acc0;
 #pragma unroll
       for (int u = 0; u < NU; ++u)
-        dki = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i*>(ldsT + (db * 4 + u) * 1024 + lane * 16),
-                                                    cs[u], dki, 0, 0, 0);
+        dki = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+            *reinterpret_cast<const v4i*>(lds + T::T_OFF + (db * 4 + u) * 1024 + lane * 16), sc[u], dki, 0, 0, 0);
 #pragma unroll
       for (int e = 0; e < 16; ++e) dka[h][e] = __builtin_fmaf(acc_f32<BW_ACC<D>>(dki[e]), fk, dka[h][e]);
     }
-    // the block's staged codes and row sums; they are stored after the next
-    // block's first barrier, so the wait in front of it does not wait for them
-    if constexpr (STORE_DS) {
-#pragma unroll
-      for (int b2 = 0; b2 < 16 / BW_DK_WAVES; ++b2)
-        dsv[b2] = *reinterpret_cast<const v4i*>(dsl + (wave * (16 / BW_DK_WAVES) + b2) * 1024 + lane * 16);
-      if (tid < BW_Q) rsv = (red2[tid] + red2[BW_Q + tid]) + (red2[2 * BW_Q + tid] + red2[3 * BW_Q + tid]);
-      sdsv = sdS;
-    }
   }
-  if (STORE_DS && i0 < nqb) store_ds(nqb - 1);
+  if constexpr (STORE_DS) {
+    __syncthreads();
+    if (i0 < nqb) store_rs(nqb - 1);
+  }
 
   // dK^T: lane holds key kb + 32 kg + col and channels 32db + 8g + 4hi + r
   if (key < N) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+    for (int h = 0; h < NDBW; ++h)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const size_t idx = ((size_t)bh * N + key) * D + 32 * (qh * NH + h) + 8 * g + 4 * hi;
+        const size_t idx = ((size_t)bh * N + key) * D + 32 * (qh * NDBW + h) + 8 * g + 4 * hi;
         *reinterpret_cast<float4*>(dk + idx) = make_float4(dka[h][4 * g], dka[h][4 * g + 1], dka[h][4 * g + 2], dka[h][4 * g + 3]);
       }
   }
@@ -871,6 +863,22 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
   }
 }
 
+// The dK kernel for g heads from h0 on; QH = 2 where its workgroups do not outnumber the CUs.
+template <int D, bool CAUSAL, bool BF16, bool STORE_DS>
+static hipError_t launch_dk(const int8_t* qc, const float* qs, const int8_t* qt, const int8_t* kc, const float* ks,
+                            const uint16_t* v, const uint16_t* dout, const float* drow, const float* lb, float* dk,
+                            int8_t* dsc, float* dss, float* drs, int h0, int g, int N, int Np, int nqb, float c2, float rsd,
+                            hipStream_t st) {
+  const dim3 grid((unsigned)(Np / BW_K), (unsigned)g);
+  if ((long long)grid.x * grid.y <= 256)
+    hipLaunchKernelGGL((attn_i8_bwd_dk_kernel<D, CAUSAL, BF16, STORE_DS, 2>), grid, dim3(512), 0, st, qc, qs, qt, kc, ks, v,
+                       dout, drow, lb, dk, dsc, dss, drs, N, Np, nqb, h0, c2, rsd);
+  else
+    hipLaunchKernelGGL((attn_i8_bwd_dk_kernel<D, CAUSAL, BF16, STORE_DS, 1>), grid, dim3(256), 0, st, qc, qs, qt, kc, ks, v,
+                       dout, drow, lb, dk, dsc, dss, drs, N, Np, nqb, h0, c2, rsd);
+  return hipGetLastError();
+}
+
 template <int D, bool CAUSAL, bool BF16>
 static hipError_t launch_bwd_t(const int8_t* qc, const float* qs, const int8_t* qt, const int8_t* kc, const float* ks,
                                const int8_t* kt, const uint16_t* v, const uint16_t* dout, const int8_t* gt,
@@ -883,10 +891,8 @@ static hipError_t launch_bwd_t(const int8_t* qc, const float* qs, const int8_t* 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (G <= 0) {                                    // no room to store dS^: dQ recomputes it
-    hipLaunchKernelGGL((attn_i8_bwd_dk_kernel<D, CAUSAL, BF16, false>), dim3((unsigned)nkb, (unsigned)BH),
-                       dim3(64 * BW_DK_WAVES), 0,
-                       st, qc, qs, qt, kc, ks, v, dout, drow, lb, dk, nullptr, nullptr, nullptr, N, Np, nqb, 0, c2, rsd);
-    e = hipGetLastError();
+    e = launch_dk<D, CAUSAL, BF16, false>(qc, qs, qt, kc, ks, v, dout, drow, lb, dk, nullptr, nullptr, nullptr, 0, BH, N, Np,
+                                          nqb, c2, rsd, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_i8_bwd_dq_kernel<D, CAUSAL, BF16>), dim3((unsigned)nqb, (unsigned)BH), dim3(256), 0, st,
                        qc, qs, kc, ks, kt, v, dout, drow, lb, kmean, dq, N, Np, nqb, c2, rsd);
@@ -894,10 +900,8 @@ static hipError_t launch_bwd_t(const int8_t* qc, const float* qs, const int8_t* 
   }
   for (int h0 = 0; h0 < BH; h0 += G) {             // groups of G heads share the stored dS^
     const int g = min(G, BH - h0);
-    hipLaunchKernelGGL((attn_i8_bwd_dk_kernel<D, CAUSAL, BF16, true>), dim3((unsigned)nkb, (unsigned)g),
-                       dim3(64 * BW_DK_WAVES), 0,
-                       st, qc, qs, qt, kc, ks, v, dout, drow, lb, dk, dsc, dss, drs, N, Np, nqb, h0, c2, rsd);
-    e = hipGetLastError();
+    e = launch_dk<D, CAUSAL, BF16, true>(qc, qs, qt, kc, ks, v, dout, drow, lb, dk, dsc, dss, drs, h0, g, N, Np, nqb, c2, rsd,
+                                         st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_i8_bwd_dq_ds_kernel<D, CAUSAL>), dim3((unsigned)nqb, (unsigned)g), dim3(256), 0, st, ks, kt,
                        dsc, dss, drs, kmean, dq, N, Np, nqb, h0, rsd);

@@ -166,3 +166,32 @@ def test_bwd_long_sequence_head_grouped_stored_ds():
         assert np.array_equal(x, y)
     *ref, tol = oracle.attn_int8_bwd(q, k, v, do, o, lse, 1, False, 128)
     check_grads(g1, ref, tol, "N=8192 head-grouped")
+
+
+@pytest.mark.parametrize("N", [1, 129, 300])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("stored", [False, True])
+def test_bwd_many_heads_same_bits(N, D, causal, stored):
+    """The dK kernel runs eight waves per key block where its grid leaves CUs
+    idle and four otherwise, and large calls quantize in separate launches: two
+    heads alone and 400 copies of them give the same bits, with the stored dS^
+    state and without."""
+    torch = torch_dev()
+    say("int8 bwd many heads N=%d D=%d causal=%d stored=%d" % (N, D, causal, stored))
+    g = torch.Generator(device="cuda").manual_seed(50 + N)
+    dt = torch.bfloat16 if N % 2 else torch.float16
+    q, k, v, dout = (torch.randn((1, 2, N, D), generator=g, device="cuda").to(dt) for _ in range(4))
+
+    def grads(q, k, v, dout):
+        o, lse = bd.sage_attn_int8_fwd(q, k, v, causal=causal)
+        B, H = q.shape[:2]
+        size = bd.attn_int8_bwd_workspace_size if stored else bd.attn_int8_bwd_min_workspace_size
+        ws = torch.empty(size(B, H, N, D), dtype=torch.uint8, device="cuda")
+        return (o, lse) + tuple(bd.sage_attn_int8_bwd(q, k, v, o, lse, dout, causal=causal, workspace=ws))
+
+    few = grads(q, k, v, dout)
+    many = grads(*(x.repeat(400, 1, 1, 1) for x in (q, k, v, dout)))
+    torch.cuda.synchronize()
+    for a, b in zip(few, many):
+        assert torch.equal(b, a.expand_as(b))
