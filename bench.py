@@ -410,7 +410,7 @@ def int8_backward(torch, bd, w, qd, kd, vd, o, L, steps):
     del ws, grads, dout
     return {"step_ms": t * 1e3, "tops": ops / t / 1e12, "ops": ops,
             # the recommended workspace stores dS^: dK writes it, dQ sums from it
-            "kernels": ["i8_bwd_prep_kernel<128,true>", "attn_i8_bwd_dv_kernel<128,false>",
+            "kernels": ["quant_i8_kernel", "quant_i8_k_kernel", "attn_i8_bwd_dv_kernel<128,false>",
                         "attn_i8_bwd_dk_kernel<128,false,true,true>", "attn_i8_bwd_dq_ds_kernel<128,false>"],
             "frac_of_mixed_peak": floor / t,
             "peak_note": "8/10 of the work at the int8 peak (5000 TOPS), 2/10 (dO V^T) at the bf16 peak (2500 TFLOP/s)"}
@@ -630,7 +630,7 @@ def main():
         e1.record()
         torch.cuda.synchronize()
         t_wg = e0.elapsed_time(e1) / 1e3 / args.steps
-        wg128 = {"kernel": "attn_fp4_mx256_kernel<%d,false,0,false,4>" % D, "kernel_ms": t_wg * 1e3,
+        wg128 = {"kernel": "attn_fp4_mx_kernel<%d,256,false,0,false,4,1>" % D, "kernel_ms": t_wg * 1e3,
                  "tops": ops / t_wg / 1e12, "frac_of_mxfp4_peak": ops / t_wg / 1e12 / PEAK_FP4_TFLOPS,
                  "traffic": traffic_from_counters("default")}
         log("attention kernel, 128-query workgroups %.3f ms = %.1f TFLOP/s" % (t_wg * 1e3, ops / t_wg / 1e12))
@@ -713,7 +713,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": attn_tflops, "peak": PEAK_FP4_TFLOPS, "unit": "TFLOP/s",
                      "frac": attn_tflops / PEAK_FP4_TFLOPS,
                      "traffic": traffic_from_counters("wg256" if wg else "default") if w.bkv == 256 else None,
-                     "kernel": ("attn_fp4_mx256_kernel<%d,false,0,false,%d>" % (D, 8 if wg else 4) if w.bkv == 256
+                     "kernel": ("attn_fp4_mx_kernel<%d,256,false,0,false,%d,1>" % (D, 8 if wg else 4) if w.bkv == 256
                                 else "attn_fp4_mx_kernel<%d,%d,false,0,false>" % (D, w.bkv)),
                      "kernel_ms": t_attn * 1e3,
                      "issue_ceilings": ceilings},
