@@ -28,15 +28,18 @@
 //    operand of dQ^T = K^T dS^T (A = K^T rows, permuted the same way).
 // Each workgroup stages the operands its four waves share -- a query block
 // (Q^, dO, L, D and a transposed Q^ or dO^) for dV and dK, a KV block (K^, V,
-// K^T) for dQ -- in LDS in MFMA-operand order with global loads that write
-// LDS, one block ahead of the block being computed.  Nothing inside a block
+// K^T) for dQ -- in LDS in MFMA-operand order with buffer loads that write
+// LDS, one block ahead of the block being computed (dK with one workgroup of
+// four waves for two of a CU: single-buffered, each operand's next loads issued
+// once every wave has read it).  Nothing inside a block
 // waits for those loads: each kernel keeps one LDS array (see sage_common.h),
 // its inner barriers order LDS only, dK stores a block's dS^ state after the
 // next block's first barrier, and dQ reads the row sums a block ahead.  With the
 // waits that each of these brought, one forward and backward of B1 H32 N8192
 // D128 took 5836 us, without them 5224 us; B2 H12 N1000 D64 causal 148 -> 138 us.
 // Buffer loads and maxima and row sums exchanged without LDS: 5224 -> 5146 and
-// 138 -> 132 us (the forward's share of that included).
+// 138 -> 132 us (the forward's share of that included).  With the quantizers in
+// fewer launches and dK as below: 4422 and 105 us.
 #include "sage_common.h"
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
