@@ -326,3 +326,37 @@ def test_attn_with_and_without_kv_groups(N, D, bkv, causal, wg):
     check(few.cpu().numpy().reshape(-1, D), ref, tie, "two heads")
     check(many[0].cpu().numpy().reshape(-1, D), ref, tie, "many heads")
     assert torch.equal(many, many[:1].expand_as(many))
+
+
+@pytest.mark.parametrize("N", [1, 513, 4096, 4097])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("op", ["mx", "nv16", "int8"])
+def test_attn_one_launch_quantizers_same_bits(N, D, op):
+    """A call quantizes Q, V and K's partial sums in one launch (up to 2^24
+    elements), and K's quantizer adds up to 8 chunks of 512 partial sums itself:
+    one chunk, two, 8 and 9 give the bits of the quantizers run role by role,
+    with and without smoothing K, and K's mean is the fp64 mean to fp32 rounding."""
+    torch = torch_dev()
+    say("one-launch quantizers N=%d D=%d %s" % (N, D, op))
+    g = torch.Generator(device="cuda").manual_seed(70 + N)
+    dt = torch.bfloat16 if D == 128 else torch.float16
+    x = [(torch.randn((1, 2, N, D), generator=g, device="cuda") + (i == 1)).to(dt) for i in range(3)]
+    roles = (bd.SAGE_ROLE_Q, bd.SAGE_ROLE_K, bd.SAGE_ROLE_V)
+    for sm in (0, bd.SAGE_NO_SMOOTH_K):
+        if op == "int8":
+            quant = [bd.sage_quant_int8(t, r, sm) for t, r in zip(x, roles)]
+            got = bd.sage_attn_int8_fwd(*x, flags=sm)
+            ref = bd.sage_attn_int8_fwd_prequant(*(t[:2] for t in quant), (1, 2, N, D), in_bf16=dt == torch.bfloat16)
+        else:
+            f = (bd.SAGE_FMT_MXFP4 if op == "mx" else bd.SAGE_FMT_NV16_E4M3) | bd.bkv_flag(128)
+            quant = [bd.sage_quant_fp4(t, r, f | sm) for t, r in zip(x, roles)]
+            got = (bd.sage_attn_fp4_fwd(*x, fmt=f | sm),)
+            ref = (bd.sage_attn_fp4_fwd_prequant(*(t[:2] for t in quant), (1, 2, N, D), fmt=f,
+                                                 in_bf16=dt == torch.bfloat16),)
+        torch.cuda.synchronize()
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b)
+        if not sm:
+            mean = x[1].double().mean(2)
+            # one rounding to fp32 (2^-24 of the value), and as much for the fp64 sums
+            assert ((quant[1][2].view(1, 2, D).double() - mean).abs() <= 2.0 ** -23 * mean.abs() + 1e-12).all()
