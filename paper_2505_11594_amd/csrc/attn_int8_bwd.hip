@@ -165,24 +165,29 @@ __device__ __forceinline__ void bw_lds_barrier() { asm volatile("s_waitcnt lgkmc
 // floats each).
 
 // Loads of 128-row blocks, as buffer loads (see sage_common.h): a resource
-// over the rows of the block that exist (rows past the end read zero; those
-// entries are masked), one fixed lane offset per operand, and a uniform offset
-// per operand block.
+// over the rows of the block that exist, and the whole offset in the lane
+// offset, which the range check covers, so rows past the end read zero (those
+// entries are masked).
 //
 // Row-major operand (E bytes per element), rows [r0, r0 + 128) of x [BH, rows, D]:
 // operand block b = wave + W i is (32-row group b / NS, K-step b % NS), lane
-// bytes [KB s + 16 hi, +16) of row 32u + col with KB = 32 bytes per K-step.
+// bytes [32 s + 16 hi, +16) of row 32u + col with NS = D E / 32.  Its lane
+// offset is the wave's (block b = wave) plus a constant per i.
 template <int D, int E>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t bw_rows_rsrc(const void* x, int bh, int rows, int r0) {
   const int n = min(rows - r0, 128);
   return make_rsrc(static_cast<const uint8_t*>(x) + ((size_t)bh * rows + r0) * (D * E), (uint32_t)n * (D * E));
 }
-template <int D, int E>
-__device__ __forceinline__ uint32_t bw_rows_voff(int col, int hi) { return (uint32_t)(col * D * E + 16 * hi); }
-template <int D, int E>
-__device__ __forceinline__ uint32_t bw_rows_soff(int b) {
+template <int D, int E, int W>
+__device__ __forceinline__ uint32_t bw_rows_voff(int wave, int col, int hi) {
   constexpr int NS = D * E / 32;
-  return (uint32_t)((b / NS) * 32 * D * E + (b % NS) * 32);
+  static_assert(NS % W == 0 || W % NS == 0, "blocks of one wave are a constant apart");
+  return (uint32_t)((32 * (wave / NS) + col) * (D * E) + 32 * (wave % NS) + 16 * hi);
+}
+template <int D, int E, int W>
+__device__ __forceinline__ void bw_rows_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int i, uint8_t* dst) {
+  constexpr int NS = D * E / 32;
+  buf_load16(r, voff + (uint32_t)((W * i / NS) * 32 * D * E + W * i % NS * 32), 0u, dst);
 }
 // Transposed operand, columns [c0, c0 + 128) of x [BH, D, Np] (int8): operand
 // block t is (channel block t / 4, 32-column group t % 4).
@@ -222,7 +227,7 @@ struct BwDvLds {
   static constexpr int NQA = 4 * NKS, NT = NDB * 4;
   static constexpr int QA_OFF = 0, GT_OFF = NQA * 1024, LD_OFF = GT_OFF + NT * 1024, BYTES = LD_OFF + 1024;
   static constexpr int J = (NQA + NT) / 4;
-  static_assert((NQA + NT) % 4 == 0, "even split over 4 waves");
+  static_assert(NQA % 4 == 0 && NT % 4 == 0, "even split over 4 waves");
 };
 
 template <int D, bool CAUSAL>
@@ -252,6 +257,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
 #pragma unroll
   for (int db = 0; db < NDB; ++db) dva[db] = v16f{};
 
+  const uint32_t vq = bw_rows_voff<D, 1, 4>(wave, col, hi);
   auto issue = [&](int i, int buf) {
     const int q0 = i * BW_Q;
     uint8_t* L = lds + buf * T::BYTES;
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k;
-      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::QA_OFF + b * 1024);
+      if (4 * k < T::NQA) bw_rows_load<D, 1, 4>(rq, vq, k, L + T::QA_OFF + b * 1024);
       else buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, b - T::NQA), L + T::GT_OFF + (b - T::NQA) * 1024);
     }
     bw_load_ld(lb, drow, L + T::LD_OFF, bh, Np, q0, wave, lane);
@@ -371,7 +377,7 @@ struct BwDkLds {
   static constexpr int RED2_OFF = T_OFF + NT * 1024, CX_OFF = RED2_OFF + 4 * BW_Q * 4;
   static constexpr int RED_OFF = CX_OFF + (QH == 2 ? 16 * 1024 : 0), BYTES = RED_OFF + 2 * W * 4;
   static constexpr int AJ = (NQA + NGA) / W, TJ = NT / W;   // loads per wave
-  static_assert((NQA + NGA) % W == 0 && NT % W == 0, "even split over the waves");
+  static_assert(NQA % W == 0 && NGA % W == 0 && NT % W == 0, "even split over the waves");
 };
 
 // STORE_DS: also write, for every (query block, KV block) pair, the dS^ codes
@@ -422,14 +428,15 @@ __global__ __launch_bounds__(256 * QH, 2 / QH) void attn_i8_bwd_dk_kernel(
 #pragma unroll
   for (int h = 0; h < NDBW; ++h) dka[h] = v16f{};
 
+  const uint32_t vq = bw_rows_voff<D, 1, W>(wave, col, hi), vg = bw_rows_voff<D, 2, W>(wave, col, hi);
   auto issue_A = [&](int i) {
     const int q0 = i * BW_Q;
     const __amdgpu_buffer_rsrc_t rq = bw_rows_rsrc<D, 1>(qc, bh, N, q0), rg = bw_rows_rsrc<D, 2>(dout, bh, N, q0);
 #pragma unroll
     for (int k = 0; k < T::AJ; ++k) {
       const int b = wave + W * k, g = b - T::NQA;
-      if (b < T::NQA) buf_load16(rq, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), lds + T::QA_OFF + b * 1024);
-      else buf_load16(rg, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), lds + T::GA_OFF + g * 1024);
+      if (W * k < T::NQA) bw_rows_load<D, 1, W>(rq, vq, k, lds + T::QA_OFF + b * 1024);
+      else bw_rows_load<D, 2, W>(rg, vg, k - T::NQA / W, lds + T::GA_OFF + g * 1024);
     }
     bw_load_ld(lb, drow, lds + T::LD_OFF, bh, Np, q0, wave, lane);
   };
@@ -592,7 +599,7 @@ struct BwQLds {
   static constexpr int NKA = NT * NKS, NVA = NT * NKS16, NKT = NDB * NT;
   static constexpr int KA_OFF = 0, VA_OFF = NKA * 1024, KT_OFF = VA_OFF + NVA * 1024, BYTES = KT_OFF + NKT * 1024;
   static constexpr int J = (NKA + NVA + NKT) / 4;
-  static_assert((NKA + NVA + NKT) % 4 == 0, "even split over 4 waves");
+  static_assert(NKA % 4 == 0 && NVA % 4 == 0 && NKT % 4 == 0, "even split over 4 waves");
 };
 
 // ---------------------------------------------------------------------------
@@ -634,6 +641,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
 
   // loads of KV block j: wave w takes operand blocks w, w + 4, ...; V rows
   // >= N read zero (those keys are masked)
+  const uint32_t vk = bw_rows_voff<D, 1, 4>(wave, col, hi), vv = bw_rows_voff<D, 2, 4>(wave, col, hi);
   auto issue = [&](int j, int buf) {
     const int kb = j * BW_K;
     uint8_t* L = lds + buf * T::BYTES;
@@ -642,8 +650,8 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
 #pragma unroll
     for (int k = 0; k < T::J; ++k) {
       const int b = wave + 4 * k, g = b - T::NKA, t = g - T::NVA;
-      if (b < T::NKA) buf_load16(rk, bw_rows_voff<D, 1>(col, hi), bw_rows_soff<D, 1>(b), L + T::KA_OFF + b * 1024);
-      else if (g < T::NVA) buf_load16(rv, bw_rows_voff<D, 2>(col, hi), bw_rows_soff<D, 2>(g), L + T::VA_OFF + g * 1024);
+      if (4 * k < T::NKA) bw_rows_load<D, 1, 4>(rk, vk, k, L + T::KA_OFF + b * 1024);
+      else if (4 * k < T::NKA + T::NVA) bw_rows_load<D, 2, 4>(rv, vv, k - T::NKA / 4, L + T::VA_OFF + g * 1024);
       else buf_load16(rt, bw_cols_voff(Np, col, hi), bw_cols_soff(Np, t), L + T::KT_OFF + t * 1024);
     }
   };

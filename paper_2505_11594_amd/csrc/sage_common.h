@@ -41,6 +41,9 @@ enum { kFmtMX = 0, kFmtNV16 = 1 };
 // A raw buffer resource over `bytes` bytes at `base` (reads past the end return
 // zero), and direct-to-LDS buffer loads from it: lane l's bytes land at
 // dst + size * l; the byte address is base + voff (per lane) + soff (uniform).
+// The check that gives zero past the end is relied on for voff alone (the
+// compiler's contract leaves soff out of it): a load whose offset may pass the
+// end carries all of that offset in voff, soff only moves inside the buffer.
 // Unlike global_load_lds, which the compiler also counts as an LDS access that
 // may finish out of order (each later LDS read then waits for all reads before
 // it), they leave the waits of operand reads counted.

@@ -195,3 +195,33 @@ def test_bwd_many_heads_same_bits(N, D, causal, stored):
     torch.cuda.synchronize()
     for a, b in zip(few, many):
         assert torch.equal(b, a.expand_as(b))
+
+
+@pytest.mark.parametrize("N", [1, 129, 257])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("stored", [False, True])
+def test_bwd_reads_nothing_behind_its_tensors(N, D, causal, stored):
+    """Inputs that are the front of larger tensors: the ragged last block's rows
+    past N of the last head lie behind them.  NaN there and in the workspace
+    beforehand gives the bits of zeros there."""
+    torch = torch_dev()
+    say("int8 bwd NaN behind its tensors N=%d D=%d causal=%d stored=%d" % (N, D, causal, stored))
+    g = torch.Generator(device="cuda").manual_seed(80 + N)
+    x = [torch.randn((1, 2, N, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    x += list(bd.sage_attn_int8_fwd(*x[:3], causal=causal))
+    size = bd.attn_int8_bwd_workspace_size if stored else bd.attn_int8_bwd_min_workspace_size
+
+    def grads(behind, ws_byte):
+        def front(t):
+            big = torch.full((t.numel() + 128 * D,), behind, dtype=t.dtype, device="cuda")
+            big[:t.numel()] = t.flatten()
+            return big[:t.numel()].view(t.shape)
+        q, k, v, dout, o, lse = (front(t) for t in x)
+        ws = torch.full((size(1, 2, N, D, bd.SAGE_IN_BF16),), ws_byte, dtype=torch.uint8, device="cuda")
+        return bd.sage_attn_int8_bwd(q, k, v, o, lse, dout, causal=causal, workspace=ws)
+
+    ref, got = grads(0.0, 0), grads(float("nan"), 255)
+    torch.cuda.synchronize()
+    for a, b in zip(ref, got):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
