@@ -39,14 +39,43 @@
 // computed ahead and three LDS stages, a call on B2 H32 N4096 D128 took 344
 // instead of 373 us with 128-key tiles and 387 instead of 408 with 64-key tiles,
 // B1 H24 N19200 D64 1766 instead of 1801 us.
-#include "fp4_tile.h"
 #include "sage_common.h"
 
 namespace sage {
 
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
+// Swizzle of a tile row's NCH 16-byte chunks: 16 consecutive rows at one chunk fall on distinct bank groups.
+template <int NCH>
+__device__ __forceinline__ int fp4_swz(int row) {
+  return NCH == 8 ? (row >> 1) & 7 : NCH == 4 ? (row >> 2) & 3 : (row >> 3) & 1;
+}
+
 __device__ __forceinline__ v8i as_op(const v4i x) { return v8i{x[0], x[1], x[2], x[3], 0, 0, 0, 0}; }
+
+// One LDS stage of a KV tile: K^ and V^T codes (in the order of the load jobs in
+// the kernel), their scales and, with smoothing Q, the tile's BKV entries of the
+// query block's GEMV bias.  Np is a multiple of 128: when the last 256-key tile
+// reaches past Np its upper 128 keys are loaded from its lower half (finite
+// values, masked as keys >= N), so that no load leaves its tensor.
+template <int D, int BKV, bool SQ>
+struct Fp4Stage {
+  static constexpr int NSUB = BKV / 32;        // 32-key subtiles (S^T rows)
+  static constexpr int NKS = D / 64;           // K-steps of S^T = K^ Q^T
+  static constexpr int NDB = D / 32;           // 32-dim blocks (O^T rows)
+  static constexpr int NG = BKV / 64;          // K-steps of O^T += V^T P^T
+  static constexpr int NKB = NSUB * NKS;       // K^ load jobs, 1 KiB each
+  static constexpr int NVB = NDB * NG;         // V^T load jobs, 1 KiB each
+  static constexpr int KC_OFF = 0;
+  static constexpr int VC_OFF = KC_OFF + NKB * 1024;
+  static constexpr int KS_OFF = VC_OFF + NVB * 1024;     // K^ scales: BKV rows x D/32 bytes
+  static constexpr int KS_BYTES = BKV * (D / 32);
+  static constexpr int VW = BKV == 256 ? 2 : 1;          // dwords of V^T scales per dim row (64 keys: half of one)
+  static constexpr int VS_OFF = KS_OFF + (KS_BYTES + 255) / 256 * 256;
+  static constexpr int BIAS_OFF = VS_OFF + D * 4 * VW;   // smoothing Q: fp32 bias of the tile's keys
+  static constexpr int BYTES = BIAS_OFF + (SQ ? BKV * 4 : 0);
+  static constexpr int NKSJ = (KS_BYTES / 4 + 63) / 64, NVSJ = D * VW / 64;   // dword-load jobs of 64 lanes
+};
 
 // Waves per SIMD that the register budget is set for: a tile's S takes BKV/2
 // registers, O D/2; with smoothing Q at D = 128 and 128 keys a third wave would
@@ -116,47 +145,89 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
   int ntiles = (N + BKV - 1) / BKV;
   if (CAUSAL) ntiles = min(ntiles, min(q0 + AQW - 1, N - 1) / BKV + 1);
 
-  // Tile loads (see fp4_tile.h).  Each is a buffer resource over the head's
-  // tensor, a uniform offset -- tile, job and the tail redirect -- and one of five
-  // fixed lane offsets, so a load costs no VALU and no 64-bit address arithmetic.
-  using J = Fp4Jobs<D, BKV, QW>;
-  constexpr bool ROWS = J::ROWS;
-  constexpr int KJ = J::KJ, VJ = J::VJ, SJ = J::SJ, KCH = J::KCH, VCH = J::VCH, VW = T::VW;
-  const uint32_t ko0 = J::k_lane(wave, lane), vo0 = J::v_lane(wave, lane, Np), vo_back = J::v_back(wave, lane);
-  const uint32_t kso = J::ks_lane(lane), vso = J::vs_lane(lane, Np), vso_back = J::vs_back(lane);
+  // Load jobs of 1 KiB: wave w of a KV group loads K^ jobs and V^T jobs b = w +
+  // QW i and scale dword jobs jb = w + QW i (K^ scale dwords 64jb + lane, then
+  // V^T scale dwords 64(jb - NKSJ) + lane, VW per dim row).
+  // ROWS (256-key tiles, four waves): a job is whole tile rows as they lie in memory (K^ rows
+  // of D/2 bytes, V^T rows of BKV/2), the 16-byte chunks swizzled against bank
+  // conflicts by the choice of the chunk each lane loads, so every line is
+  // requested once; operand reads then need an address per K-step.  Otherwise a
+  // job is one MFMA operand (32 rows x two 16-byte chunks, lane l's bytes at 16 l):
+  // a line is requested by up to four jobs, but one lane offset serves all
+  // operand reads, and the 128-key kernels have no registers left (D = 128, 8
+  // heads x 4096: 76 us a call with ROWS, 65 without; 256-key tiles, 4 heads
+  // x 4096 in two KV groups 47.7 -> 45.2, B4 H32 N4096 637 -> 618; 256-query
+  // workgroups, which fetch a tile half as often, 7745 -> 7773 on B1 H32 N32768).
+  // Each load is a buffer resource over the head's tensor, a uniform offset --
+  // tile, job and the tail redirect -- and one of five fixed lane offsets, so
+  // a load costs no VALU and no 64-bit address arithmetic.
+  constexpr bool ROWS = BKV == 256 && W == 4;
+  static_assert(ROWS ? QW % 2 == 0 : QW % NKS == 0 && (QW % NG == 0 || NG % QW == 0), "job layout");
+  constexpr int KJ = (T::NKB + QW - 1) / QW, VJ = (T::NVB + QW - 1) / QW, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + QW - 1) / QW;
+  constexpr int KCH = D / 32, VCH = BKV / 32, VR = 64 / VCH;      // ROWS: chunks per row, V^T rows per job
+  // Redirect of a 256-key tile whose upper half lies past Np: V^T by the lane offset, K^ by the uniform
+  // offset, or, where one job per wave starts below the 128 keys it goes back (K_LANE), by the lane offset too.
+  constexpr bool K_LANE = !ROWS && BKV == 256 && QW > T::NKB / 2;
+  static_assert(ROWS || BKV != 256 || (QW % NG == 0 && (!K_LANE || QW == T::NKB)), "a wave's jobs lie in one half of the tile");
+  uint32_t ko0, vo0, ko_back = 0, vo_back = 0;
+  if constexpr (ROWS) {
+    const int kcl = (lane % KCH) ^ fp4_swz<KCH>(lane / KCH), vcl = (lane % VCH) ^ fp4_swz<VCH>(wave * VR + lane / VCH);
+    ko0 = (uint32_t)(lane / KCH * (D / 2) + 16 * kcl);
+    vo0 = (uint32_t)(lane / VCH) * (uint32_t)(Np / 2) + 16 * vcl;
+    vo_back = vcl >= VCH / 2 ? 64u : 0u;
+  } else {
+    ko0 = (uint32_t)((32 * (wave / NKS) + col) * (D / 2) + 16 * (wave % NKS) + 16 * NKS * hi);
+    vo0 = (uint32_t)((32 * (wave / NG) + col) * (Np / 2) + 32 * (wave % NG) + 16 * hi);
+    if constexpr (K_LANE) ko_back = wave >= T::NKB / 2 ? 128u * (D / 2) : 0u;
+    if constexpr (BKV == 256) vo_back = wave % NG >= NG / 2 ? 64u : 0u;
+  }
+  const uint32_t kso = (uint32_t)(4 * lane);
+  constexpr int VW = T::VW;
+  const uint32_t vso = (uint32_t)((lane / VW) * (Np / 32) + 4 * (lane % VW));
+  const uint32_t vso_hi = (uint32_t)(4 * (lane % VW));   // the second dword: subtracted when it lies past Np
   const uint8_t* kbase = kc + (size_t)bh * Np * (D / 2);
   const uint8_t* vbase = vc + (size_t)bh * D * (Np / 2);
   const uint8_t* ksbase = ks + (size_t)bh * Np * (D / 32);
   const uint8_t* vsbase = vs + (size_t)bh * D * (Np / 32);
+  // buffer resources over this head's K^, V^T codes and scales: every load is
+  // the resource, a uniform byte offset and one fixed lane offset
   const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase, Np * (D / 2)), rv = make_rsrc(vbase, D * (Np / 2));
   const __amdgpu_buffer_rsrc_t rks = make_rsrc(ksbase, Np * (D / 32)), rvs = make_rsrc(vsbase, D * (Np / 32));
   const __amdgpu_buffer_rsrc_t rb =
       make_rsrc(SQ ? qkb + ((size_t)bh * ((N + 127) / 128) + q0 / 128) * Np : nullptr, SQ ? Np * 4 : 0);
   auto issue = [&](int j, int stage) {
     const int kb = j * BKV;
-    const bool tail = J::tail(kb, Np);
+    const bool short_tail = BKV == 256 && kb + BKV > Np;   // keys [kb + 128, kb + 256) lie past Np
     uint8_t* L = lds[2 * kg + stage];
-    const uint32_t ko = ko0 - (tail ? J::k_back(wave) : 0u);
+    const uint32_t ko = ko0 - (short_tail ? ko_back : 0u);
 #pragma unroll
     for (int i = 0; i < KJ; ++i) {
       const int b = wave + QW * i;
       if (T::NKB % QW != 0 && b >= T::NKB) break;
-      buf_load16(rk, ko, J::k_uni(kb, wave, i, tail), L + T::KC_OFF + b * 1024);
+      const uint32_t back = (!K_LANE && short_tail && b >= T::NKB / 2) ? 128u * (D / 2) : 0u;
+      const uint32_t off = ROWS ? (uint32_t)b * 1024u : (uint32_t)i * (32 * QW / NKS) * (D / 2);
+      buf_load16(rk, ko, (uint32_t)kb * (D / 2) + off - back, L + T::KC_OFF + b * 1024);
     }
-    const uint32_t vo = vo0 - (tail ? vo_back : 0u), vsl = vso - (tail ? vso_back : 0u);
+    const uint32_t vo = vo0 - (short_tail ? vo_back : 0u);
 #pragma unroll
     for (int i = 0; i < VJ; ++i) {
       const int b = wave + QW * i;
       if (T::NVB % QW != 0 && b >= T::NVB) break;
-      buf_load16(rv, vo, J::v_uni(kb, wave, i, Np), L + T::VC_OFF + b * 1024);
+      const uint32_t off = ROWS ? (uint32_t)(b * VR) * (uint32_t)(Np / 2)
+                                : (uint32_t)(QW * i / NG) * 32 * (Np / 2) + 32 * (QW * i % NG);
+      buf_load16(rv, vo, (uint32_t)kb / 2 + off, L + T::VC_OFF + b * 1024);
     }
 #pragma unroll
     for (int i = 0; i < SJ; ++i) {
       const int jb = wave + QW * i;
       if (jb < T::NKSJ) {
-        if (J::ks_on(jb, lane)) buf_load4(rks, kso, J::ks_uni(kb, jb, tail), L + T::KS_OFF + jb * 256);
-      } else if (jb < J::NSJ) {
-        buf_load4(rvs, vsl, J::vs_uni(kb, jb, Np), L + T::VS_OFF + (jb - T::NKSJ) * 256);
+        const uint32_t back = (short_tail && 64 * jb * 4 >= T::KS_BYTES / 2) ? T::KS_BYTES / 2 : 0u;
+        if (T::KS_BYTES % 256 == 0 || 256 * jb + 4 * lane < T::KS_BYTES)
+          buf_load4(rks, kso, (uint32_t)kb * (D / 32) + 256u * jb - back, L + T::KS_OFF + jb * 256);
+      } else if (jb < NSJ) {
+        // 64-key tiles: the aligned dword that holds the tile's two scale bytes
+        buf_load4(rvs, vso - (short_tail ? vso_hi : 0u), ((uint32_t)kb / 32 & ~3u) + (uint32_t)(jb - T::NKSJ) * (2 / VW) * Np,
+              L + T::VS_OFF + (jb - T::NKSJ) * 256);
       }
     }
     if constexpr (SQ) {

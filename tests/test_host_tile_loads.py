@@ -1,52 +1,62 @@
-"""Every KV tile load of the FP4 kernel stays inside its head's tensor: the offsets
-of csrc/fp4_tile.h, which the kernel uses as they are, walked on the host for
-every wave, lane, job and tile."""
+"""Every KV tile load of the FP4 kernel stays inside its head's tensor: the
+kernel's own load code, compiled for the host with a buffer load that checks its
+range, and run for every wave, lane, job and tile."""
 import os
+import re
 import subprocess
 
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-SRC = r"""
+PRE = r"""
+#include <algorithm>
+#include <cstdint>
 #include <cstdio>
 #include <initializer_list>
-#include "fp4_tile.h"
-using namespace sage;
+using std::min;
 static long long loads = 0, bad = 0;
-static void in(const char* what, int N, int kb, uint32_t lane, uint32_t uni, uint32_t size, unsigned long long bytes) {
+struct Rsrc { unsigned long long bytes; };
+typedef Rsrc __amdgpu_buffer_rsrc_t;
+static Rsrc make_rsrc(const void*, uint32_t bytes) { return {bytes}; }
+static uint8_t lds[8][1 << 17];
+static uint8_t* stage_end;
+static void load(Rsrc r, uint32_t voff, uint32_t soff, int size, int lane, uint8_t* dst) {
   ++loads;
-  if ((unsigned long long)lane + uni + size > bytes && bad++ < 5)
-    printf("%s N=%d kb=%d: %u + %u + %u > %llu\n", what, N, kb, lane, uni, size, bytes);
-}
-template <int D, int BKV, int LW> static void walk(int N, int step) {
-  using J = Fp4Jobs<D, BKV, LW>;
-  using T = typename J::T;
-  const unsigned long long Np = (N + 127) / 128 * 128;
-  const int last = (N + BKV - 1) / BKV - 1;
-  for (int j = 0; j <= last; j = j == last ? j + 1 : (j + step < last ? j + step : last)) {
-    const int kb = j * BKV;
-    const bool tail = J::tail(kb, (int)Np);
-    for (int w = 0; w < LW; ++w)
-      for (int l = 0; l < 64; ++l) {
-        for (int i = 0; i < J::KJ && w + LW * i < T::NKB; ++i)
-          in("K", N, kb, J::k_lane(w, l) - (tail ? J::k_back(w) : 0), J::k_uni(kb, w, i, tail), 16, Np * D / 2);
-        for (int i = 0; i < J::VJ && w + LW * i < T::NVB; ++i)
-          in("V", N, kb, J::v_lane(w, l, (int)Np) - (tail ? J::v_back(w, l) : 0), J::v_uni(kb, w, i, (int)Np), 16, Np * D / 2);
-        for (int i = 0; i < J::SJ; ++i) {
-          const int jb = w + LW * i;
-          if (jb < T::NKSJ) {
-            if (J::ks_on(jb, l)) in("K scales", N, kb, J::ks_lane(l), J::ks_uni(kb, jb, tail), 4, Np * D / 32);
-          } else if (jb < J::NSJ) {
-            in("V scales", N, kb, J::vs_lane(l, (int)Np) - (tail ? J::vs_back(l) : 0), J::vs_uni(kb, jb, (int)Np), 4, Np * D / 32);
-          }
-        }
-      }
+  if ((unsigned long long)voff + soff + size > r.bytes || dst + size * (lane + 1) > stage_end) {
+    if (bad++ < 5) printf("%u + %u + %d > %llu\n", voff, soff, size, r.bytes);
   }
 }
+#define buf_load16(r, v, s, d) load(r, v, s, 16, lane, d)
+#define buf_load4(r, v, s, d) load(r, v, s, 4, lane, d)
+"""
+FN = r"""
+template <int D, int BKV, bool SQ, int W, int KG>
+static void walk(int N, int step) {
+  using T = Fp4Stage<D, BKV, SQ>;
+  constexpr int NKS = T::NKS, NG = T::NG, QW = W / KG;
+  const int Np = (N + 127) / 128 * 128, ntiles = (N + BKV - 1) / BKV;
+  const long long bh = 0;
+  const uint8_t *kc = nullptr, *vc = nullptr, *ks = nullptr, *vs = nullptr;
+  const float* qkb = nullptr;
+  const int q0 = 0;
+  for (int kg = 0; kg < KG; ++kg)
+    for (int wave = 0; wave < QW; ++wave)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int col = lane & 31, hi = lane >> 5;
+        (void)NG; (void)col; (void)hi;
+        @KERNEL@
+        for (int j = 0; j < ntiles; j = j == ntiles - 1 ? ntiles : min(j + step, ntiles - 1))
+          for (int st = 0; st < 2; ++st) {
+            stage_end = lds[2 * kg + st] + T::BYTES;
+            issue(j, st);
+          }
+      }
+}
 template <int D> static void all(int N, int step) {
-  walk<D, 64, 4>(N, step); walk<D, 128, 4>(N, step); walk<D, 256, 4>(N, step); walk<D, 256, 8>(N, step);
-  walk<D, 64, 2>(N, step); walk<D, 128, 2>(N, step); walk<D, 256, 2>(N, step);
+  walk<D, 64, false, 4, 1>(N, step); walk<D, 128, false, 4, 1>(N, step); walk<D, 256, false, 4, 1>(N, step);
+  walk<D, 64, true, 4, 2>(N, step); walk<D, 128, true, 4, 2>(N, step); walk<D, 256, true, 4, 2>(N, step);
+  walk<D, 256, false, 8, 1>(N, step);
 }
 int main() {
   for (int N : {1, 64, 65, 128, 129, 255, 256, 257, 384, 385, 640, 1000, 1237}) { all<64>(N, 1); all<128>(N, 1); }
@@ -58,18 +68,23 @@ int main() {
 """
 
 
-@pytest.mark.parametrize("planted", [False, True])
+@pytest.mark.parametrize("planted", ["", "V", "K"])
 def test_fp4_tile_loads_stay_inside_their_tensors(tmp_path, planted):
     """... and the walk finds a tail that is not redirected (planted in a copy)."""
-    csrc = os.path.join(ROOT, "paper_2505_11594_amd", "csrc")
-    hdr = open(os.path.join(csrc, "fp4_tile.h")).read()
-    if planted:
-        assert hdr.count("return BKV == 256 && v_chunk") == 1
-        hdr = hdr.replace("return BKV == 256 && v_chunk", "return ROWS && v_chunk")
-    (tmp_path / "fp4_tile.h").write_text(hdr)
-    (tmp_path / "t.cpp").write_text(SRC)
+    src = open(os.path.join(ROOT, "paper_2505_11594_amd", "csrc", "attn_fp4.hip")).read()
+    swz = src[src.index("template <int NCH>"):src.index("__device__ __forceinline__ v8i as_op")]
+    stage = src[src.index("template <int D, int BKV, bool SQ>\nstruct Fp4Stage"):src.index("// Waves per SIMD that the register")]
+    code = src[src.index("  constexpr bool ROWS = "):src.index("  // operand addresses in the tile")]
+    if planted == "V":
+        assert code.count("if constexpr (BKV == 256) vo_back = ") == 1
+        code = code.replace("if constexpr (BKV == 256) vo_back = ", "if constexpr (false) vo_back = ")
+    if planted == "K":
+        assert code.count("constexpr bool K_LANE = ") == 1
+        code = code.replace("constexpr bool K_LANE = ", "constexpr bool K_LANE = false && ")
+    text = PRE + swz + stage + FN.replace("@KERNEL@", code)
+    (tmp_path / "t.cpp").write_text(re.sub(r"__device__|__forceinline__", "", text))
     exe = str(tmp_path / "t")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-o", exe, str(tmp_path / "t.cpp")], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wno-unknown-pragmas", "-o", exe, str(tmp_path / "t.cpp")], check=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     print(r.stdout)
-    assert (r.returncode != 0) == planted, r.stdout
+    assert (r.returncode != 0) == bool(planted), r.stdout
