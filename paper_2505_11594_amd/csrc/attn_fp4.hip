@@ -165,11 +165,12 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
   static_assert(ROWS ? QW % 2 == 0 : QW % NKS == 0 && (QW % NG == 0 || NG % QW == 0), "job layout");
   constexpr int KJ = (T::NKB + QW - 1) / QW, VJ = (T::NVB + QW - 1) / QW, NSJ = T::NKSJ + T::NVSJ, SJ = (NSJ + QW - 1) / QW;
   constexpr int KCH = D / 32, VCH = BKV / 32, VR = 64 / VCH;      // ROWS: chunks per row, V^T rows per job
-  // Redirect of a 256-key tile whose upper half lies past Np: V^T by the lane offset, K^ by the uniform
-  // offset, or, where one job per wave starts below the 128 keys it goes back (K_LANE), by the lane offset too.
-  constexpr bool K_LANE = !ROWS && BKV == 256 && QW > T::NKB / 2;
-  static_assert(ROWS || BKV != 256 || (QW % NG == 0 && (!K_LANE || QW == T::NKB)), "a wave's jobs lie in one half of the tile");
-  uint32_t ko0, vo0, ko_back = 0, vo_back = 0;
+  // Redirect of a 256-key tile whose upper half lies past Np.  ROWS: V^T by the lane offset, K^ by the uniform
+  // one.  Else a wave's V^T jobs (and K^ job, where it has one) lie in one half of the tile: the lane offset is
+  // that of the lower half and the uniform offset adds the way up, which the short tile leaves out.
+  constexpr bool K_WAVE = !ROWS && BKV == 256 && QW == T::NKB;
+  static_assert(ROWS || BKV != 256 || (QW % NG == 0 && (K_WAVE || QW == T::NKB / 2)), "a wave's jobs lie in one half of the tile");
+  uint32_t ko0, vo0, vo_back = 0, k_up = 0, v_up = 0;
   if constexpr (ROWS) {
     const int kcl = (lane % KCH) ^ fp4_swz<KCH>(lane / KCH), vcl = (lane % VCH) ^ fp4_swz<VCH>(wave * VR + lane / VCH);
     ko0 = (uint32_t)(lane / KCH * (D / 2) + 16 * kcl);
@@ -178,8 +179,10 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
   } else {
     ko0 = (uint32_t)((32 * (wave / NKS) + col) * (D / 2) + 16 * (wave % NKS) + 16 * NKS * hi);
     vo0 = (uint32_t)((32 * (wave / NG) + col) * (Np / 2) + 32 * (wave % NG) + 16 * hi);
-    if constexpr (K_LANE) ko_back = wave >= T::NKB / 2 ? 128u * (D / 2) : 0u;
-    if constexpr (BKV == 256) vo_back = wave % NG >= NG / 2 ? 64u : 0u;
+    if constexpr (K_WAVE) k_up = wave >= T::NKB / 2 ? 128u * (D / 2) : 0u;
+    if constexpr (BKV == 256) v_up = wave % NG >= NG / 2 ? 64u : 0u;
+    ko0 -= k_up;
+    vo0 -= v_up;
   }
   const uint32_t kso = (uint32_t)(4 * lane);
   constexpr int VW = T::VW;
@@ -199,14 +202,14 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
     const int kb = j * BKV;
     const bool short_tail = BKV == 256 && kb + BKV > Np;   // keys [kb + 128, kb + 256) lie past Np
     uint8_t* L = lds[2 * kg + stage];
-    const uint32_t ko = ko0 - (short_tail ? ko_back : 0u);
 #pragma unroll
     for (int i = 0; i < KJ; ++i) {
       const int b = wave + QW * i;
       if (T::NKB % QW != 0 && b >= T::NKB) break;
-      const uint32_t back = (!K_LANE && short_tail && b >= T::NKB / 2) ? 128u * (D / 2) : 0u;
+      const uint32_t back = (short_tail && b >= T::NKB / 2) ? 128u * (D / 2) : 0u;
       const uint32_t off = ROWS ? (uint32_t)b * 1024u : (uint32_t)i * (32 * QW / NKS) * (D / 2);
-      buf_load16(rk, ko, (uint32_t)kb * (D / 2) + off - back, L + T::KC_OFF + b * 1024);
+      if constexpr (K_WAVE) buf_load16(rk, ko0, (uint32_t)kb * (D / 2) + off + (short_tail ? 0u : k_up), L + T::KC_OFF + b * 1024);
+      else buf_load16(rk, ko0, (uint32_t)kb * (D / 2) + off - back, L + T::KC_OFF + b * 1024);
     }
     const uint32_t vo = vo0 - (short_tail ? vo_back : 0u);
 #pragma unroll
@@ -215,7 +218,8 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
       if (T::NVB % QW != 0 && b >= T::NVB) break;
       const uint32_t off = ROWS ? (uint32_t)(b * VR) * (uint32_t)(Np / 2)
                                 : (uint32_t)(QW * i / NG) * 32 * (Np / 2) + 32 * (QW * i % NG);
-      buf_load16(rv, vo, (uint32_t)kb / 2 + off, L + T::VC_OFF + b * 1024);
+      if constexpr (BKV == 256 && !ROWS) buf_load16(rv, vo0, (uint32_t)kb / 2 + off + (short_tail ? 0u : v_up), L + T::VC_OFF + b * 1024);
+      else buf_load16(rv, vo, (uint32_t)kb / 2 + off, L + T::VC_OFF + b * 1024);
     }
 #pragma unroll
     for (int i = 0; i < SJ; ++i) {

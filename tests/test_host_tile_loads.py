@@ -76,11 +76,11 @@ def test_fp4_tile_loads_stay_inside_their_tensors(tmp_path, planted):
     stage = src[src.index("template <int D, int BKV, bool SQ>\nstruct Fp4Stage"):src.index("// Waves per SIMD that the register")]
     code = src[src.index("  constexpr bool ROWS = "):src.index("  // operand addresses in the tile")]
     if planted == "V":
-        assert code.count("if constexpr (BKV == 256) vo_back = ") == 1
-        code = code.replace("if constexpr (BKV == 256) vo_back = ", "if constexpr (false) vo_back = ")
+        assert code.count("if constexpr (BKV == 256) v_up = ") == 1
+        code = code.replace("if constexpr (BKV == 256) v_up = ", "if constexpr (false) v_up = ")
     if planted == "K":
-        assert code.count("constexpr bool K_LANE = ") == 1
-        code = code.replace("constexpr bool K_LANE = ", "constexpr bool K_LANE = false && ")
+        assert code.count("if constexpr (K_WAVE) k_up = ") == 1
+        code = code.replace("if constexpr (K_WAVE) k_up = ", "if constexpr (false) k_up = ")
     text = PRE + swz + stage + FN.replace("@KERNEL@", code)
     (tmp_path / "t.cpp").write_text(re.sub(r"__device__|__forceinline__", "", text))
     exe = str(tmp_path / "t")
