@@ -11,9 +11,11 @@ because the quantization decisions must round exactly like the definition.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -28,7 +30,7 @@ PROBES_SOURCES = ["probes.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result",
@@ -36,10 +38,14 @@ FLAGS = [
 ]
 
 
-def _compile(lib: str, sources, verbose: bool) -> str:
-    srcs = [os.path.join(CSRC, s) for s in sources]
-    tmp = lib + ".tmp%d" % os.getpid()
-    cmd = [HIPCC] + FLAGS + ["-o", tmp] + srcs
+# MFMA results in VGPRs: where LDS allows one workgroup per CU only (two KV groups
+# of 256-key tiles), the compiler counts on 512 registers, puts the scores into
+# AGPRs and moves each one back before its use (32 -> 28 us on 4 heads x 4096, D =
+# 128).  The other FP4 kernels use no AGPR either way.
+SOURCE_FLAGS = {"attn_fp4.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
+
+def _run(cmd, verbose: bool) -> None:
     r = subprocess.run(cmd, capture_output=True, text=True)
     # the host pass does not know the device-only feature name; that warning is harmless
     msgs = [l for l in (r.stdout + r.stderr).splitlines() if "not a recognized feature" not in l]
@@ -47,6 +53,15 @@ def _compile(lib: str, sources, verbose: bool) -> str:
         raise RuntimeError("hipcc failed:\n" + "\n".join(msgs))
     if verbose and msgs:
         print("\n".join(msgs), file=sys.stderr)
+
+
+def _compile(lib: str, sources, verbose: bool) -> str:
+    tmp = lib + ".tmp%d" % os.getpid()
+    with tempfile.TemporaryDirectory() as d, concurrent.futures.ThreadPoolExecutor(4) as pool:
+        objs = [os.path.join(d, s + ".o") for s in sources]
+        list(pool.map(lambda so: _run([HIPCC] + FLAGS + SOURCE_FLAGS.get(so[0], []) +
+                                      ["-c", "-o", so[1], os.path.join(CSRC, so[0])], verbose), zip(sources, objs)))
+        _run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", tmp] + objs, verbose)
     os.replace(tmp, lib)
     return lib
 

@@ -30,6 +30,7 @@
 // MFMA-operand order (see the load jobs); either way operand reads are free of
 // bank conflicts.  Two LDS stages and one barrier per tile: after the barrier of tile j every wave has finished
 // tile j - 1, and the loads of tile j + 1 go to that stage while tile j runs.
+// (Calls with few query tiles take two tiles a step: see KG below.)
 //
 // What bounds it is instruction issue (exponentials, packs and plain VALU work
 // nearly in series with the MFMAs), so the tile's S is computed at its top and
@@ -86,6 +87,19 @@ constexpr int fp4_waves(int D, int BKV, int W, bool SQ) {
   return D == 128 ? 3 : 4;
 }
 
+// LDS of the kernel with two KV groups (KG = 2, below): four stages, then per wave
+// three dwords a lane (tile maximum, row sum, block exponents) and the codes of
+// P, NG x 16 bytes a lane.  Where that alone keeps a second workgroup off the CU
+// (160 KiB), the codes go over the tile's K^ codes instead, behind a barrier.
+template <int D, int BKV, bool SQ>
+struct Fp4Xchg {
+  using T = Fp4Stage<D, BKV, SQ>;
+  static constexpr int XS_OFF = 4 * T::BYTES, XP_OFF = XS_OFF + 4 * 768, OWN = 4 * T::NG * 1024;
+  static constexpr bool IN_K = XP_OFF <= 81920 && XP_OFF + OWN > 81920;
+  static constexpr int BYTES = IN_K ? XP_OFF : XP_OFF + OWN;
+  static_assert(2 * T::NG <= T::NKB && BYTES <= 163840, "the codes of two waves fit K^'s, and all fits a CU");
+};
+
 // W waves per workgroup (32 queries each).  W = 4 is the default.  W = 8
 // (flag SAGE_WG256; non-causal, without smoothing Q, whose GEMV bias rows
 // belong to 128-query blocks) shares each K^/V^T tile in LDS between 256
@@ -97,22 +111,27 @@ constexpr int fp4_waves(int D, int BKV, int W, bool SQ) {
 // block, key] (Algorithm 1's GEMV of the block mean with K', one row of Np
 // floats per 128-query block, which is this workgroup's query tile).
 //
-// KG: KV groups.  With KG = 2 the workgroup's four waves are two groups of two:
-// 64 queries, each group walking every second KV tile through LDS stages of
-// its own, and the two results are merged through LDS at the end (each group's
-// O and l are brought to the larger running max and added, in fp32).  For calls
-// with too few 128-query tiles for the GPU; see fp4_kv_groups.
+// KG: KV groups.  With KG = 2 the workgroup's four waves are two groups of two,
+// 64 queries, that take two KV tiles a step: group kg forms S and P of tile
+// jj + kg -- P's codes and block scales depend on the tile's own maximum only --
+// and leaves the codes, that maximum and the row sum in LDS; then every wave
+// runs the softmax state and P.V over both tiles in turn for the channel blocks
+// of its half kg.  Every sum keeps the order of KG = 1, so both give the same
+// bits, and a head's result does not depend on how many heads share the call.
+// For calls with too few 128-query tiles for the GPU; see fp4_kv_groups.
 template <int D, int BKV, bool CAUSAL, int OUT, bool SQ, int W, int KG>
 __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) void attn_fp4_mx_kernel(
     const uint8_t* __restrict__ qc, const uint8_t* __restrict__ qs, const uint8_t* __restrict__ kc,
     const uint8_t* __restrict__ ks, const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs,
     const float* __restrict__ qkb, void* __restrict__ o, int BH, int N, int Np, int nqt, float c2, float log6) {
   using T = Fp4Stage<D, BKV, SQ>;
-  constexpr int NSUB = T::NSUB, NKS = T::NKS, NDB = T::NDB, NG = T::NG;
+  constexpr int NSUB = T::NSUB, NKS = T::NKS, NG = T::NG;
+  constexpr int NDB = T::NDB / KG;                // channel blocks of this wave
   constexpr int QW = W / KG, AQW = 32 * QW;       // waves along the queries, queries per workgroup
   static_assert((W == 4 || W == 8) && (!SQ || W == 4), "4 or 8 waves; smoothing Q blocks are 128 queries");
   static_assert(KG == 1 || (KG == 2 && W == 4), "one or two KV groups");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * KG][T::BYTES];
+  using X = Fp4Xchg<D, BKV, SQ>;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[KG == 1 ? 2 * T::BYTES : X::BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % QW;   // wave of its KV group
@@ -201,7 +220,7 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
   auto issue = [&](int j, int stage) {
     const int kb = j * BKV;
     const bool short_tail = BKV == 256 && kb + BKV > Np;   // keys [kb + 128, kb + 256) lie past Np
-    uint8_t* L = lds[2 * kg + stage];
+    uint8_t* L = lds + (2 * kg + stage) * T::BYTES;
 #pragma unroll
     for (int i = 0; i < KJ; ++i) {
       const int b = wave + QW * i;
@@ -259,10 +278,64 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
     wait_loads();                                          // this wave's loads of tile j have landed
     __syncthreads();                                       // everyone's; every wave is past tile j - KG
     if (j + KG < ntiles) issue(j + KG, stage ^ 1);
-    const uint8_t* L = lds[2 * kg + stage];
-    const int kb = j * BKV;
-    if (KG > 1 && j >= ntiles) continue;
-    if (CAUSAL && kb > qw + 31) continue;                  // the whole tile is above this wave's diagonal
+    const uint8_t* L = lds + (2 * kg + stage) * T::BYTES;
+    const int kb = j * BKV;                                // KG = 2: a group without a tile computes what no one reads
+    // the whole tile is above this wave's diagonal (KG = 2: never, 64 queries end inside the last tile)
+    if (KG == 1 && CAUSAL && kb > qw + 31) continue;
+
+    // P.V of block g of the tile in Lt: pw the codes of its 32 keys, psb its scale byte
+    uint32_t vsw[NDB][VW];
+    auto pv = [&](auto G_, const uint8_t* Lt, const v4i pw, int psb) {
+      constexpr int g = decltype(G_)::value;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const v4i a = *reinterpret_cast<const v4i*>(Lt + v_op(kg * NDB + db, g));
+        oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(pw), oacc[db], 4, 4, 2 * (g & 1),
+                                                                   (int)vsw[db][g >> 1], 0, psb);
+      }
+    };
+    // the softmax state over a tile with row maximum tm (c2 tm = tc): O is
+    // rescaled, the tile's V^T scales are read, and the factor of l returned
+    int kfold, kf127;
+    auto advance = [&](const uint8_t* Lt, int kbt, float tm, float tc) {
+      const float m_new = smax(m, tm);
+      const float mc = m_new * c2;
+      const float delta = tc - mc;
+      const float kf = __builtin_floorf(delta);              // c2 (t - m_new) <= 0 split into k and f in [0, 1)
+      const float f = delta - kf;
+      const float gam = __builtin_amdgcn_exp2f((mc_old - mc) + (f_old - f));
+      kfold = (int)__builtin_fmaxf(kf, -300.0f);
+      kf127 = kfold + 127;                                   // P's scale byte is e + kfold + 127, clamped at 0
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[db][v] *= gam;
+      // V^T scale bytes of this lane's dim rows, block 2g + hi of the tile in byte 2(g & 1) of dword g >> 1
+      // (read as v2u, not uint2: see sage_common.h; as uint2 this read waited for
+      // the whole prefetch of tile j + 1: B4 H32 N4096 D128 681 -> 643 us a call)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const uint8_t* vp = Lt + T::VS_OFF + (32 * (kg * NDB + db) + col) * 4 * VW;
+        if constexpr (VW == 2) {
+          const v2u w2 = *reinterpret_cast<const v2u*>(vp);
+          vsw[db][0] = w2[0] >> (8 * hi);
+          vsw[db][1] = w2[1] >> (8 * hi);
+        } else {
+          vsw[db][0] = *reinterpret_cast<const uint32_t*>(vp) >> (8 * ((BKV == 64 ? (kbt / 32) & 3 : 0) + hi));
+        }
+      }
+      m = m_new;
+      mc_old = mc;
+      f_old = f;
+      return gam;
+    };
+    // KG = 2: where the wave of query group `wave` and KV group k leaves P's codes of block g
+    auto xp = [&](int k, int g) {
+      return (X::IN_K ? lds + (2 * k + stage) * T::BYTES + T::KC_OFF + (wave * NG + g) * 1024
+                      : lds + X::XP_OFF + ((k * QW + wave) * NG + g) * 1024) + lane * 16;
+    };
+    float* const xs = reinterpret_cast<float*>(lds + X::XS_OFF) + lane;
+    const int wx = kg * QW + wave;
 
     // S^T = K^ . Q^T for the tile.  K-step s takes channel block s + NKS hi in
     // lane half hi (blocks s and s + NKS), so each lane's K and Q scale bytes
@@ -297,6 +370,7 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
         }
       }
     }
+    if constexpr (KG == 2 && X::IN_K) lds_barrier();         // K^'s codes have been read
     const bool need_mask = (kb + BKV > N) || (CAUSAL && kb + BKV - 1 > qw);
     if (need_mask) {
       // element (u, v) is key kb + 32 hi + c with c = 64 (u >> 1) + 16 (u & 1) + v;
@@ -330,37 +404,12 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
     // row max over the two lane halves that share a query
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tl), __float_as_uint(tl), false, false);
     const float t = smax(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-    const float m_new = smax(m, t);
     const float tc = t * c2;
-    const float mc = m_new * c2;
-    const float delta = tc - mc;
-    const float kf = __builtin_floorf(delta);              // c2 (t - m_new) <= 0 split into k and f in [0, 1)
-    const float f = delta - kf;
-    const float gam = __builtin_amdgcn_exp2f((mc_old - mc) + (f_old - f));
-    const int kfold = (int)__builtin_fmaxf(kf, -300.0f);
-    const int kf127 = kfold + 127;                         // P's scale byte is e + kfold + 127, clamped at 0
+    float gam = 0.0f;
+    if constexpr (KG == 1) gam = advance(L, kb, t, tc);
     const float bias = log6 - tc;                          // P~2 = 2^{fma(S, c2, log2 6 - t c2)}
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) oacc[db][v] *= gam;
-
-    // V^T scale bytes of this lane's dim rows, block 2g + hi of the tile in byte 2(g & 1) of dword g >> 1
-    // (read as v2u, not uint2: see sage_common.h; as uint2 this read waited for
-    // the whole prefetch of tile j + 1: B4 H32 N4096 D128 681 -> 643 us a call)
-    uint32_t vsw[NDB][VW];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-      const uint8_t* vp = L + T::VS_OFF + (32 * db + col) * 4 * VW;
-      if constexpr (VW == 2) {
-        const v2u w2 = *reinterpret_cast<const v2u*>(vp);
-        vsw[db][0] = w2[0] >> (8 * hi);
-        vsw[db][1] = w2[1] >> (8 * hi);
-      } else {
-        vsw[db][0] = *reinterpret_cast<const uint32_t*>(vp) >> (8 * ((BKV == 64 ? (kb / 32) & 3 : 0) + hi));
-      }
-    }
     float ps[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t ew = 0;                                       // KG = 2: the block exponents, a byte each
     static_for<NG>([&](auto G_) {
       constexpr int g = decltype(G_)::value;
       // smallest e with 6 2^e >= blockmax(P~2) = 6 2^{c2 (bm - t)}; a fully
@@ -389,53 +438,42 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
         }
       }
       const v4i pw = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      const int sb = e + kf127;
-      const int psb = sb < 0 ? 0 : sb;
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const v4i a = *reinterpret_cast<const v4i*>(L + v_op(db, g));
-        oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_op(a), as_op(pw), oacc[db], 4, 4, 2 * (g & 1),
-                                                                   (int)vsw[db][g >> 1], 0, psb);
+      if constexpr (KG == 1) {
+        const int sb = e + kf127;
+        pv(G_, L, pw, sb < 0 ? 0 : sb);
+      } else {
+        *reinterpret_cast<v4i*>(xp(kg, g)) = pw;
+        ew |= ((uint32_t)e & 255u) << (8 * g);
       }
     });
     const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
-    lsum_acc = lsum_acc * gam + __builtin_ldexpf(psum, kfold);
-    m = m_new;
-    mc_old = mc;
-    f_old = f;
+    if constexpr (KG == 1) {
+      lsum_acc = lsum_acc * gam + __builtin_ldexpf(psum, kfold);
+    } else {
+      xs[wx * 192] = t;
+      xs[wx * 192 + 64] = psum;
+      xs[wx * 192 + 128] = __uint_as_float(ew);
+    }
+    if constexpr (KG == 2) {
+      lds_barrier();                                       // both tiles' P
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (k == 1 && jj + 1 >= ntiles) break;
+        const int wk = k * QW + wave;
+        const uint8_t* Lk = lds + (2 * k + stage) * T::BYTES;
+        const float tk = xs[wk * 192], pk = xs[wk * 192 + 64];
+        const uint32_t ek = __float_as_uint(xs[wk * 192 + 128]);
+        const float gam = advance(Lk, (jj + k) * BKV, tk, tk * c2);
+        static_for<NG>([&](auto G_) {
+          constexpr int g = decltype(G_)::value;
+          const int sb = ((int)(ek << (24 - 8 * g)) >> 24) + kf127;
+          pv(G_, Lk, *reinterpret_cast<const v4i*>(xp(k, g)), sb < 0 ? 0 : sb);
+        });
+        lsum_acc = lsum_acc * gam + __builtin_ldexpf(pk, kfold);
+      }
+    }
   }
 
-  if constexpr (KG == 2) {
-    // the accumulators of state (m c2, f) are converted to state (mc, 0) by 2^{(m c2 - mc) + f};
-    // group 0 has at least one tile, a group 1 without any has m = -inf and adds zero
-    constexpr int WBYTES = (NDB * 4 + 1) * 1024;           // per wave: O, then (m c2, f, l)
-    static_assert(QW * WBYTES <= 2 * KG * T::BYTES, "the merge fits the tile stages");
-    uint8_t* const mrg = lds[0] + wave * WBYTES + lane * 16;
-    __syncthreads();                                       // every wave is done with the tiles
-    if (kg == 1) {
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<v4f*>(mrg + (db * 4 + g) * 1024) =
-              v4f{oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
-      *reinterpret_cast<v4f*>(mrg + NDB * 4 * 1024) = v4f{mc_old, f_old, lsum_acc, 0.0f};
-    }
-    __syncthreads();
-    if (kg == 1) return;
-    const v4f st = *reinterpret_cast<const v4f*>(mrg + NDB * 4 * 1024);
-    const float mc = smax(mc_old, st[0]);
-    const float g0 = __builtin_amdgcn_exp2f((mc_old - mc) + f_old), g1 = __builtin_amdgcn_exp2f((st[0] - mc) + st[1]);
-    lsum_acc = lsum_acc * g0 + st[2] * g1;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const v4f x = *reinterpret_cast<const v4f*>(mrg + (db * 4 + g) * 1024);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) oacc[db][4 * g + r] = oacc[db][4 * g + r] * g0 + x[r] * g1;
-      }
-  }
   const float ltot = lsum_acc + __shfl_xor(lsum_acc, 32, 64);
   const float inv = 1.0f / ltot;
   if (qi < N) {
@@ -444,7 +482,7 @@ __global__ __launch_bounds__(64 * W, KG == 1 ? fp4_waves(D, BKV, W, SQ) : 2) voi
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int d0 = 32 * db + 8 * g + 4 * hi;
+        const int d0 = 32 * (kg * NDB + db) + 8 * g + 4 * hi;
         const size_t idx = ((size_t)bh * N + qi) * D + d0;
         const float a0 = oacc[db][4 * g] * inv, a1 = oacc[db][4 * g + 1] * inv;
         const float a2 = oacc[db][4 * g + 2] * inv, a3 = oacc[db][4 * g + 3] * inv;
@@ -482,22 +520,28 @@ static hipError_t launch_fp4_o(int out, const void* qc, const void* qs, const vo
 }
 
 // KV groups of a call: two where 128-query tiles are too few for the GPU and
-// there are at least two KV tiles to share.  With 256-key tiles at D = 128 the
-// two groups' stages take the LDS of a CU, so twice the workgroups must still
-// be one per CU: 4 heads x 4096 (128 tiles) 55.4 -> 45.2 us a call, 6 heads 59.9
-// -> 81.5.  The other stages fit twice or more: 128-key tiles, D = 128, heads x
-// 4096: 4 heads 57.8 -> 41, 8 heads 65 -> 62.7 (causal 64 -> 51), 12 heads 91.3 ->
-// 85.5, 16 heads 96.9 -> 102.9; D = 64, 8 heads 49 -> 42.5, 16 heads 72.5 -> 71.7.
-static int fp4_kv_groups(int BH, int N, int D, int bkv) {
+// there are at least two KV tiles to share (both give the same bits).  Attention
+// alone, N = 4096, one group -> two, in us, by number of 128-query tiles:
+//               128           256           384           512
+//   D 128, 256 keys  40.2 -> 27.9  42.2 -> 54.2  66 -> 80     (two groups: one workgroup per CU)
+//   D 128, 128 keys  43.3 -> 30.7  45.3 -> 46.1  68.4 -> 67   73 -> 85
+//     causal         43.5 -> 31.1  44.5 -> 32.9  67.1 -> 53.5 68 -> 54 (N = 16384: 210 -> 236)
+//   D 128, 64 keys   55.9 -> 38.2  58.6 -> 52.0  80.8 -> 72.8 86 -> 96
+//   D 64, 256 keys   32.5 -> 21.8  33.4 -> 34.2  53.8 -> 49.2 55 -> 63
+//   D 64, 128 keys   36.1 -> 25.1  36.9 -> 36.6  57.6 -> 49.9 58 -> 64
+//   D 64, 64 keys    46.0 -> 31.8  46.8 -> 45.3  72.4 -> 62.2 71 -> 74
+// (N = 16384, D 128, 128 keys: 256 tiles 163 -> 170, 384 250 -> 254.)
+static int fp4_kv_groups(int BH, int N, int D, int bkv, bool causal) {
   const long long tiles = (long long)BH * ((N + 127) / 128);
-  return tiles <= (D == 128 && bkv == 256 ? 128 : 384) && N > bkv ? 2 : 1;
+  const int most = D == 128 && (bkv == 256 || (bkv == 128 && !causal)) ? 128 : 384;
+  return tiles <= most && N > bkv ? 2 : 1;
 }
 
 template <int D, int BKV, bool CAUSAL>
 static hipError_t launch_fp4_s(int out, const void* qc, const void* qs, const void* kc, const void* ks, const void* vc,
                                const void* vs, const float* qkb, void* o, int BH, int N, int Np, float c2, float log6,
                                hipStream_t st) {
-  if (fp4_kv_groups(BH, N, D, BKV) == 2)
+  if (fp4_kv_groups(BH, N, D, BKV, CAUSAL) == 2)
     return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4, 2>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
                : launch_fp4_o<D, BKV, CAUSAL, false, 4, 2>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
   return qkb ? launch_fp4_o<D, BKV, CAUSAL, true, 4, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
@@ -511,9 +555,9 @@ hipError_t launch_attn_fp4_mx(const void* qc, const void* qs, const void* kc, co
 #define SAGE_A(DD, BB)                                                                                    \
   return causal ? launch_fp4_s<DD, BB, true>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st) \
                 : launch_fp4_s<DD, BB, false>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st)
-  if (wg256 && fp4_kv_groups(BH, N, D, 256) == 1) {
+  if (wg256 && fp4_kv_groups(BH, N, D, 256, false) == 1) {
     // 256-query workgroups: 256-key tiles, non-causal, without smoothing Q (checked by the caller); calls
-    // split over KV groups run the same kernel with and without the flag, so both give the same bits
+    // with too few tiles for the GPU take two KV groups with the flag too
     if (D == 128) return launch_fp4_o<128, 256, false, false, 8, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
     return launch_fp4_o<64, 256, false, false, 8, 1>(out, qc, qs, kc, ks, vc, vs, qkb, o, BH, N, Np, c2, log6, st);
   }

@@ -148,12 +148,6 @@ __device__ __forceinline__ void bw_wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
 
-// Workgroup barrier that orders ordinary LDS accesses only: loads in flight,
-// direct-to-LDS ones included, stay in flight (__syncthreads and the workgroup
-// fences also wait for every one of them, so the next block's prefetch would be
-// waited for at the barriers inside a block).
-__device__ __forceinline__ void bw_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // The dV and dK kernels: a workgroup owns 128 keys (4 waves x 32) of one
 // (b,h) and walks the query blocks; S = Q^ K^T puts a key in each lane's
 // column and 16 queries in its rows.  LDS holds the query block's operands in
@@ -310,7 +304,7 @@ __global__ __launch_bounds__(256, 2) void attn_i8_bwd_dv_kernel(
     }
     am = wave_max(am);
     if (lane == 0) red[4 * a + wave] = am;
-    bw_lds_barrier();
+    lds_barrier();
     am = __builtin_fmaxf(__builtin_fmaxf(red[4 * a], red[4 * a + 1]), __builtin_fmaxf(red[4 * a + 2], red[4 * a + 3]));
     const float pm = __builtin_amdgcn_exp2f(am);   // max P of the block (0 when it is fully masked)
     const float sP = pm / 127.0f, rP = pm > 0.0f ? 1.0f / sP : 0.0f;
@@ -511,7 +505,7 @@ __global__ __launch_bounds__(256 * QH, 2 / QH) void attn_i8_bwd_dk_kernel(
     dm = wave_max(dm);
     if (lane == 0) red[W * a + wave] = dm;
     bw_wait_all();                                 // this wave's loads of Q^T
-    bw_lds_barrier();
+    lds_barrier();
     if (i + 1 < nqb) issue_A(i + 1);
     dm = 0.0f;
 #pragma unroll
@@ -555,7 +549,7 @@ __global__ __launch_bounds__(256 * QH, 2 / QH) void attn_i8_bwd_dk_kernel(
       }
     }
     if constexpr (QH == 2) {
-      bw_lds_barrier();                            // every wave's codes are in LDS
+      lds_barrier();                            // every wave's codes are in LDS
 #pragma unroll
       for (int u = 0; u < NU; ++u) sc[u] = *reinterpret_cast<const v4i*>(lds + T::CX_OFF + (kg * NU + u) * 1024 + lane * 16);
     }
@@ -719,7 +713,7 @@ __global__ __launch_bounds__(256, 1) void attn_i8_bwd_dq_kernel(
     else phase1(ic<0>{});
     dm = wave_max(dm);
     if (lane == 0) red[4 * buf + wave] = dm;
-    bw_lds_barrier();
+    lds_barrier();
     dm = __builtin_fmaxf(__builtin_fmaxf(red[4 * buf], red[4 * buf + 1]),
                          __builtin_fmaxf(red[4 * buf + 2], red[4 * buf + 3]));
     const float sdS = dm / 127.0f, rdS = dm > 0.0f ? 1.0f / sdS : 0.0f;

@@ -59,6 +59,12 @@ __device__ __forceinline__ void buf_load4(__amdgpu_buffer_rsrc_t r, uint32_t vof
                                            (uint32_t)__builtin_amdgcn_readfirstlane((int)soff), 0, 0);
 }
 
+// Workgroup barrier that orders ordinary LDS accesses only: loads in flight,
+// direct-to-LDS ones included, stay in flight (__syncthreads and the workgroup
+// fences also wait for every one of them, so the next block's prefetch would be
+// waited for at the barriers inside a block).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ---- 16-bit input widening (exact) ----------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 __device__ __forceinline__ float fp16_to_f32(uint16_t h) {

@@ -309,10 +309,10 @@ def test_attn_wg256_bench_workload_same_bits():
 @pytest.mark.parametrize("bkv,causal,wg", [(64, False, 0), (64, True, 0), (128, False, 0), (128, True, 0), (256, False, 0),
                                            (256, True, 0), (256, False, WG)])
 def test_attn_with_and_without_kv_groups(N, D, bkv, causal, wg):
-    """Calls with few query tiles split the KV tiles over two groups of waves and
-    merge them; calls with many do not.  Two heads alone take the first path
-    (where there are two tiles to share), 400 copies of them the second: both
-    meet the oracle's bar, and all copies are the same bits."""
+    """Calls with few query tiles share the KV tiles between two groups of waves;
+    calls with many do not.  Two heads alone take the first path (where there are
+    two tiles to share), 400 copies of them the second: both meet the oracle's
+    bar, and all copies are the same bits."""
     torch = torch_dev()
     say("attn kv groups N=%d D=%d bkv=%d causal=%d wg256=%d" % (N, D, bkv, causal, bool(wg)))
     in_dtype = N % 2
@@ -326,6 +326,33 @@ def test_attn_with_and_without_kv_groups(N, D, bkv, causal, wg):
     check(few.cpu().numpy().reshape(-1, D), ref, tie, "two heads")
     check(many[0].cpu().numpy().reshape(-1, D), ref, tie, "many heads")
     assert torch.equal(many, many[:1].expand_as(many))
+
+
+@pytest.mark.parametrize("N", [129, 300, 520, 1100])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bkv", [64, 128, 256])
+@pytest.mark.parametrize("mode", ["plain", "causal", "wg256", "smooth_q", "smooth_q_causal"])
+def test_attn_bits_of_a_head_do_not_depend_on_the_number_of_heads(N, D, bkv, mode):
+    """Two heads alone (two KV groups where there are two tiles to share, 64
+    queries a workgroup) and 400 copies of them (one group, 128 or 256 queries)
+    give the same bits, an odd number of tiles included; with smoothing Q, whose
+    bias both paths add, also against the oracle.  16-bit outputs at N % 8 == 0."""
+    torch = torch_dev()
+    if mode == "wg256" and bkv != 256:
+        pytest.skip("256-query workgroups take 256-key tiles")
+    causal, sq = mode.endswith("causal"), mode.startswith("smooth_q")
+    say("attn few and many heads N=%d D=%d bkv=%d %s" % (N, D, bkv, mode))
+    in_dtype = N % 2
+    q, k, v = wl.make_inputs(1, 2, N, D, in_dtype, seed=930 + N, k_bias_var=4.0, outlier_frac=0.02)
+    fmt = bd.bkv_flag(bkv) | (bd.SAGE_WG256 if mode == "wg256" else 0) | (bd.SAGE_SMOOTH_Q if sq else 0)
+    x = [to_dev(t, in_dtype) for t in (q, k, v)]
+    few = bd.sage_attn_fp4_fwd(*x, causal=causal, fmt=fmt, out_f32=N % 8 != 0)
+    many = bd.sage_attn_fp4_fwd(*(t.repeat(400, 1, 1, 1) for t in x), causal=causal, fmt=fmt, out_f32=N % 8 != 0)
+    torch.cuda.synchronize()
+    assert torch.equal(many, few.expand_as(many))
+    if sq and N == 300:
+        ref, tie, _ = oracle.attn(q, k, v, in_dtype, causal, oracle.FMT_MX, bkv, flags=oracle.SMOOTH_Q)
+        check(many[399].cpu().numpy().reshape(-1, D), ref, tie, "many heads, smoothing Q")
 
 
 @pytest.mark.parametrize("N", [1, 513, 4096, 4097])

@@ -19,7 +19,7 @@ static long long loads = 0, bad = 0;
 struct Rsrc { unsigned long long bytes; };
 typedef Rsrc __amdgpu_buffer_rsrc_t;
 static Rsrc make_rsrc(const void*, uint32_t bytes) { return {bytes}; }
-static uint8_t lds[8][1 << 17];
+static uint8_t lds[1 << 18];
 static uint8_t* stage_end;
 static void load(Rsrc r, uint32_t voff, uint32_t soff, int size, int lane, uint8_t* dst) {
   ++loads;
@@ -48,7 +48,7 @@ static void walk(int N, int step) {
         @KERNEL@
         for (int j = 0; j < ntiles; j = j == ntiles - 1 ? ntiles : min(j + step, ntiles - 1))
           for (int st = 0; st < 2; ++st) {
-            stage_end = lds[2 * kg + st] + T::BYTES;
+            stage_end = lds + (2 * kg + st + 1) * T::BYTES;
             issue(j, st);
           }
       }
