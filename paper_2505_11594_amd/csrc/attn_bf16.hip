@@ -165,14 +165,16 @@ __global__ __launch_bounds__(64 * BW, 2) void attn_bf16_kernel(const uint16_t* _
     }
     if ((kb + BK > N) || (CAUSAL && kb + BK - 1 > qw)) {
       // element (t, v) is key kb + 4 hi + c with c = 32t + 8 (v >> 2) + (v & 3), kept iff
-      // c < rem: the sign bit of c - rem turns -inf into the bound +inf for kept keys
+      // c < rem: the sign of c - rem selects its bits or those of -inf (a minimum with
+      // -inf would let the NaN of a masked key through)
       const int rem = (CAUSAL ? min(N, qi + 1) : N) - kb - 4 * hi;
 #pragma unroll
       for (int t = 0; t < NSUB; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int c = 32 * t + 8 * (e >> 2) + (e & 3);
-          sacc[t][e] = smin(sacc[t][e], __uint_as_float(0xFF800000u ^ ((uint32_t)(c - rem) & 0x80000000u)));
+          const uint32_t keep = (uint32_t)((c - rem) >> 31);
+          sacc[t][e] = __uint_as_float((__float_as_uint(sacc[t][e]) & keep) | (0xFF800000u & ~keep));
         }
     }
     float x = sacc[0][0];

@@ -70,3 +70,27 @@ def test_bf16_16bit_output_and_rejects_fp16():
     q16 = to_dev(q, 0)
     with pytest.raises(bd.SageError):
         bd.sage_attn_bf16_fwd(q16, q16, q16)
+
+
+@pytest.mark.parametrize("N", [40, 64, 129, 300])
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_masked_keys_may_hold_nan_and_inf(N, D):
+    """Causal: NaN or infinity in K at token n leaves the queries before n their
+    bits (their score of n is masked, whatever it is); and rows behind the last
+    head's K and V, which its last tile covers, leave all of them theirs."""
+    torch = torch_dev()
+    q, k, v = (to_dev(x, 1) for x in wl.make_inputs(1, 2, N, D, 1, seed=340 + N, k_bias_var=1.0))
+    ref = {c: bd.sage_attn_bf16_fwd(q, k, v, causal=c) for c in (False, True)}
+    n = N - 7
+    for bad in (float("nan"), float("inf")):
+        kb = k.clone()
+        kb[:, :, n:] = bad
+        o = bd.sage_attn_bf16_fwd(q, kb, v, causal=True)
+        big = [torch.full((x.numel() + 64 * D,), bad, dtype=x.dtype, device="cuda") for x in (k, v)]
+        for b, x in zip(big, (k, v)):
+            b[:x.numel()] = x.flatten()
+        front = [b[:k.numel()].view(k.shape) for b in big]
+        torch.cuda.synchronize()
+        assert torch.isfinite(ref[True]).all() and torch.equal(o[:, :, :n], ref[True][:, :, :n])
+        for c in (False, True):
+            assert torch.equal(bd.sage_attn_bf16_fwd(q, *front, causal=c), ref[c])
