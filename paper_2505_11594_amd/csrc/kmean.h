@@ -56,8 +56,12 @@ __device__ __forceinline__ void kmean_inline(const double* __restrict__ part, fl
                                              int bh, bool store, float (&mean)[D]) {
   const int tid = threadIdx.x;
   if (tid < D) {
-    double s = 0.0;
-    for (int j = 0; j < nchunk; ++j) s += part[((size_t)bh * nchunk + j) * D + tid];
+    double p[KM_INLINE], s = 0.0;                // all loads in flight before the first sum (nchunk <= KM_INLINE)
+#pragma unroll
+    for (int j = 0; j < KM_INLINE; ++j) p[j] = part[((size_t)bh * nchunk + min(j, nchunk - 1)) * D + tid];
+#pragma unroll
+    for (int j = 0; j < KM_INLINE; ++j)
+      if (j < nchunk) s += p[j];
     const float m = (float)(s / (double)N);
     mean[tid] = m;
     if (store) mu[(size_t)bh * D + tid] = m;

@@ -325,34 +325,31 @@ __global__ __launch_bounds__(256) void quant_k_kernel(const uint16_t* __restrict
   const int nrb = Np / KRB;                                  // Np is a multiple of 128 and KRB 64 or 128
   const int bh = blockIdx.x / nrb, t0 = (blockIdx.x % nrb) * KRB;
   const int tid = threadIdx.x, cg = tid % UPR, rsub = tid / UPR;
-  const uint16_t* xh = x + ((size_t)bh * N + t0) * D + cg * 8;
+  const uint16_t* xh = x + (size_t)bh * N * D + cg * 8;
   uint4 raw[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = rsub + RS * u;
-    raw[u] = t0 + r < N ? *reinterpret_cast<const uint4*>(xh + (size_t)r * D) : make_uint4(0, 0, 0, 0);
-  }
-  float m8[8];
+  for (int u = 0; u < U; ++u)                                // rows past N: any row, overwritten below
+    raw[u] = *reinterpret_cast<const uint4*>(xh + (size_t)min(t0 + rsub + RS * u, N - 1) * D);
+  v4f ma = {}, mb = {};
   if (part != nullptr) {
-    __shared__ float mean[D];
+    __shared__ __attribute__((aligned(16))) float mean[D];
     kmean_inline<D>(part, mu, N, nchunk, bh, t0 == 0, mean);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m8[i] = mean[cg * 8 + i];
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m8[i] = mu != nullptr ? mu[(size_t)bh * D + cg * 8 + i] : 0.0f;
+    ma = *reinterpret_cast<const v4f*>(mean + cg * 8);
+    mb = *reinterpret_cast<const v4f*>(mean + cg * 8 + 4);
+  } else if (mu != nullptr) {
+    typedef v4f __attribute__((aligned(4))) v4f_a4;          // the caller's mean is 4-byte aligned
+    const v4f_a4* mp = reinterpret_cast<const v4f_a4*>(mu + (size_t)bh * D + cg * 8);
+    ma = mp[0];
+    mb = mp[1];
   }
+  const float m8[8] = {ma[0], ma[1], ma[2], ma[3], mb[0], mb[1], mb[2], mb[3]};
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int t = t0 + rsub + RS * u;
     const uint16_t* h = reinterpret_cast<const uint16_t*>(&raw[u]);
     float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(h[i]);
-    if (mu != nullptr) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = v[i] - m8[i];
-    }
+    for (int i = 0; i < 8; ++i) v[i] = widen<BF16>(h[i]) - m8[i];   // without smoothing m8 is 0: exact
     uint32_t word, sbyte;
     quant_unit<FMT>(v, word, sbyte);
     if (t >= N) {
