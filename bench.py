@@ -411,7 +411,7 @@ def int8_backward(torch, bd, w, qd, kd, vd, o, L, steps):
     return {"step_ms": t * 1e3, "tops": ops / t / 1e12, "ops": ops,
             # the recommended workspace stores dS^: dK writes it, dQ sums from it
             "kernels": ["quant_i8_kernel", "quant_i8_k_kernel", "attn_i8_bwd_dv_kernel<128,false>",
-                        "attn_i8_bwd_dk_kernel<128,false,true,true>", "attn_i8_bwd_dq_ds_kernel<128,false>"],
+                        "attn_i8_bwd_dk_kernel<128,false,true,true,1>", "attn_i8_bwd_dq_ds_kernel<128,false>"],
             "frac_of_mixed_peak": floor / t,
             "peak_note": "8/10 of the work at the int8 peak (5000 TOPS), 2/10 (dO V^T) at the bf16 peak (2500 TFLOP/s)"}
 
@@ -487,7 +487,7 @@ def main():
     qd, kd, vd = to_dev(q), to_dev(k), to_dev(v)
     tile = bd.bkv_flag(w.bkv)
     # 256-query workgroups where the kernel has them (256-key tiles, non-causal, no smoothing Q): each K^/V^T
-    # tile in LDS then serves 8 waves, which halves the HBM fetches at the same or slightly lower time
+    # tile in LDS then serves 8 waves, which halves the HBM fetches for 0 to 4% more time
     wg = w.bkv == 256 and not w.causal
     shape = tile | (bd.SAGE_WG256 if wg else 0)
     fmt = bd.SAGE_FMT_MXFP4 | shape | (bd.SAGE_IN_BF16 if w.in_dtype == wl.IN_BF16 else 0) | bd.SAGE_OUT_F32
@@ -594,8 +594,7 @@ def main():
     def attn_only():
         bd.sage_attn_fp4_fwd_prequant(qq[:2], kq[:2], vq[:2], (B, H, N, D), causal=w.causal, fmt=shape, out=o)
 
-    for _ in range(2):
-        attn_only()
+    warm(torch, attn_only)                       # as the 128-query workgroups' block below
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record()
     for _ in range(args.steps):
@@ -714,7 +713,7 @@ def main():
                      "frac": attn_tflops / PEAK_FP4_TFLOPS,
                      "traffic": traffic_from_counters("wg256" if wg else "default") if w.bkv == 256 else None,
                      "kernel": ("attn_fp4_mx_kernel<%d,256,false,0,false,%d,1>" % (D, 8 if wg else 4) if w.bkv == 256
-                                else "attn_fp4_mx_kernel<%d,%d,false,0,false>" % (D, w.bkv)),
+                                else "attn_fp4_mx_kernel<%d,%d,false,0,false,4,1>" % (D, w.bkv)),
                      "kernel_ms": t_attn * 1e3,
                      "issue_ceilings": ceilings},
         "accuracy_vs_exact": acc,

@@ -53,7 +53,9 @@ typedef enum {
 #define SAGE_BKV256         0x80u /* KV tile of 256 tokens (MXFP4 attention only)          */
 #define SAGE_WG256          0x100u /* 256 queries per workgroup instead of 128: each K^/V^T
                                       tile is fetched from L2 once per 256 queries (about
-                                      half the fetch traffic) for about 1% more time.  Only
+                                      half the fetch traffic) for 0 to 4% more time.  A
+                                      call with too few queries for the GPU runs 64-query
+                                      workgroups with or without it.  Only
                                       with SAGE_BKV256, non-causal, without SAGE_SMOOTH_Q;
                                       otherwise SAGE_ERR_UNSUPPORTED.  Same results.      */
 #define SAGE_FMT_ALL_BITS   0x1FFu
@@ -81,11 +83,13 @@ typedef enum {
  *       transposed (Appendix, "Transposing V"), natural token order, tokens
  *       >= N are zero.
  * kmean: fp32 [B,H,D], the per-(b,h) channel mean of K over the N tokens,
- * computed as an exact fp64 sum divided by N and rounded to fp32.
+ * computed as an fp64 sum divided by N and rounded to fp32 (the sum is exact
+ * for fp16 up to 2^13 tokens at full range, and for bf16 while a channel's
+ * largest and smallest nonzero magnitudes are within 2^45 / N).
  *
  * Smoothing Q (SAGE_SMOOTH_Q; Algorithm 1, "Smoothing Q of SageAttention2"):
  * Q is split into blocks of 128 consecutive rows (the last block holds the
- * rest); qbar[b,h,i,:] is the mean of block i (exact fp64 sum / rows, rounded
+ * rest); qbar[b,h,i,:] is the mean of block i (fp64 sum / rows, rounded
  * to fp32) and Q^ = phi(fl32(Q - qbar)).  The attention adds the GEMV
  * qbar_i . K'_k to every score of block i, with K' = fl32(K - kmean) (K when
  * SAGE_NO_SMOOTH_K) and the dot product evaluated as a chain of fp32 fused
@@ -146,6 +150,7 @@ size_t sage_attn_fp4_workspace_size(int B, int H, int N, int D, unsigned fmt);
  * tile flags together are SAGE_ERR_INVALID_ARG).  The tile changes only the
  * rounding of P (per-tile row maxima), not the quantized layouts.
  * Softmax scale is 1/sqrt(D).  causal = 1 keeps key j for query i iff j <= i.
+ * A head's result is the same bits whatever other heads share the call.
  *  q, k, v  : 16-bit [B,H,N,D], 16-byte aligned
  *  o        : [B,H,N,D] fp32 (SAGE_OUT_F32) or input dtype, 16-byte aligned
  * The internal workspace comes from hipMallocAsync on `stream` and is freed

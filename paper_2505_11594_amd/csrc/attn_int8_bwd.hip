@@ -32,14 +32,15 @@
 // LDS, one block ahead of the block being computed (dK with one workgroup of
 // four waves for two of a CU: single-buffered, each operand's next loads issued
 // once every wave has read it).  Nothing inside a block
-// waits for those loads: each kernel keeps one LDS array (see sage_common.h),
-// its inner barriers order LDS only, dK stores a block's dS^ state after the
-// next block's first barrier, and dQ reads the row sums a block ahead.  With the
-// waits that each of these brought, one forward and backward of B1 H32 N8192
-// D128 took 5836 us, without them 5224 us; B2 H12 N1000 D64 causal 148 -> 138 us.
-// Buffer loads and maxima and row sums exchanged without LDS: 5224 -> 5146 and
-// 138 -> 132 us (the forward's share of that included).  With the quantizers in
-// fewer launches and dK as below: 4422 and 105 us.
+// waits for the next block's loads: each kernel keeps one LDS array (see
+// sage_common.h), its inner barriers order LDS only, and dQ reads the row sums a
+// block ahead.  dK stores a block's dS^ codes inside the block and waits for them
+// with the next block's first loads; the row sums and s_dS follow after the next
+// block's first barrier.  One forward and backward of B1 H32 N8192 D128 and of
+// B2 H12 N1000 D64 causal: 5836 and 148 us with the waits that several LDS
+// arrays and full barriers brought, 5224 and 138 without them, 5146 and 132 with
+// buffer loads and with maxima and row sums exchanged without LDS, 4520 and
+// 104 with the quantizers in fewer launches and dK as below.
 #include "sage_common.h"
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -141,12 +142,6 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 
 __device__ __forceinline__ void bw_wait_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-// vmcnt(n) for the counts used below (n < 16: the low field of the immediate)
-template <int N>
-__device__ __forceinline__ void bw_wait_vm() {
-  static_assert(N >= 0 && N < 16, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
-}
 
 // The dV and dK kernels: a workgroup owns 128 keys (4 waves x 32) of one
 // (b,h) and walks the query blocks; S = Q^ K^T puts a key in each lane's
@@ -868,7 +863,8 @@ __global__ __launch_bounds__(256, 3) void attn_i8_bwd_dq_ds_kernel(
   }
 }
 
-// The dK kernel for g heads from h0 on; QH = 2 where its workgroups do not outnumber the CUs.
+// The dK kernel for g heads from h0 on; QH = 2 where its workgroups do not outnumber
+// the CUs of a gfx950 (256).
 template <int D, bool CAUSAL, bool BF16, bool STORE_DS>
 static hipError_t launch_dk(const int8_t* qc, const float* qs, const int8_t* qt, const int8_t* kc, const float* ks,
                             const uint16_t* v, const uint16_t* dout, const float* drow, const float* lb, float* dk,

@@ -6,9 +6,12 @@ namespace sage {
 
 // ---------------------------------------------------------------------------
 // Smoothing K, pass 1: per-chunk fp64 column sums.  Block (chunk, bh) sums
-// tokens [chunk * KM_CHUNK, ...) of K[bh] for every channel.  Every value is a
-// 16-bit float, so the fp64 partial sums are exact for the token counts used
-// here and the final mean does not depend on the summation order.
+// tokens [chunk * KM_CHUNK, ...) of K[bh] for every channel.  The sums are exact,
+// and the mean does not depend on their order, while the values' bits and the
+// count fit 53: always for fp16 (40 bits of range) up to 2^13 tokens per channel
+// at full range and more where it is less; for bf16 while a channel's largest and
+// smallest nonzero values are within 2^(45 - log2 N).  Beyond that each addition
+// rounds to 2^-53 of the partial sum.
 // ---------------------------------------------------------------------------
 constexpr int KM_CHUNK = 512;
 constexpr int KM_THREADS = 256;
@@ -46,7 +49,13 @@ __device__ __forceinline__ void kmean_partial(const uint16_t* __restrict__ k, do
 }
 
 // Partial sums of up to this many chunks are added by K's quantizer itself
-// (each of its workgroups reads them all), more by a pass of their own.
+// (each of its workgroups reads them all), more by a pass of their own.  A call
+// in us, pass of its own -> inline: 4 heads x 1024, D = 128 (2 chunks) 22.5 ->
+// 20.8, D = 64 21.2 -> 18.8, 4 x 4096 (8), D = 128 44.7 -> 42.6, 32 x 4096, D = 64
+// 124.2 -> 122.9 (D = 128 170.1 -> 170.9, 128 x 4096 619 -> 622).  With up to 64
+// inline the loads of a short sum cost more (32 x 4096 175.6, 128 x 4096 641) and the
+// long ones gain nothing: 4 x 8192 (16) 100.7 -> 100.4, 32 x 8192 550 -> 559, 8 x
+// 32768 (64) 1955 -> 1977.
 constexpr int KM_INLINE = 8;
 
 // mean[c] = fl32(sum of the head's partial sums / N), by the first D threads;

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(KM_THREADS) void kmean_partial_kernel(const uint16_
 
 // Pass 2: mu = fl32(fl64(sum) / N).  One workgroup per (b,h): 256 / D
 // threads per channel sum strided chunks, then one of them adds the partial
-// sums (exact in fp64, so the order does not matter).
+// sums.
 template <int D>
 __global__ __launch_bounds__(256) void kmean_final_kernel(const double* __restrict__ part, float* __restrict__ mu,
                                                           int N, int nchunk) {
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void quant_q_kernel(const uint16_t* __restrict
 
 // Q with smoothing (Algorithm 1): qbar[bh, b, c] = mean of Q[bh, t, c] over the
 // QB rows t of query block b (the last block holds the remaining rows) -- an
-// fp64 sum, exact for 16-bit inputs, so the order does not matter, divided by
+// fp64 sum (exact as the K mean's is, see kmean.h), divided by
 // the row count and rounded once to fp32 -- and the codes of Q - qbar.  One
 // workgroup per block keeps its rows in registers between the two, so Q is read
 // once (a mean pass of its own read it again: 32 us beside the quantizer's 41
@@ -312,8 +312,9 @@ __global__ __launch_bounds__(256) void quant_q_smooth_kernel(const uint16_t* __r
 }
 
 // K: a workgroup takes KRB rows of one head (four units per thread, all loads
-// issued before the first is used: 82 -> 67 us on B1 H32 N32768 D128 against
-// one), subtracts the head's mean -- read from mu, or (part given, up to
+// issued before the first is used, without branches, which would make each wait
+// for the one before: B1 H32 N32768 D128 75 us with them, 50.5 without),
+// subtracts the head's mean -- read from mu, or (part given, up to
 // KM_INLINE chunks) summed here from the partial sums, which saves the pass
 // between them -- and stores each token at its permuted position.  Rows N ..
 // Np - 1 get zero codes and unit scales.
@@ -637,7 +638,7 @@ hipError_t launch_quant_q(const void* q, float* qbar, void* codes, void* scales,
 }
 
 // bias [BH, nqb, Np] fp32; Np is a multiple of 128.  The 512-key tiles are taken
-// when they give every CU a workgroup and more than one wave of each has blocks.
+// when they give every CU of a gfx950 (256) a workgroup and more than one wave of each has blocks.
 hipError_t launch_qk_bias(const void* k, const float* mu, const float* qbar, float* bias, int BH, int N, int Np, int D,
                           bool bf16, hipStream_t st) {
   const int nqb = qmean_blocks(N);

@@ -269,7 +269,11 @@ hipError_t launch_quant_i8_k(const void* k, double* part, float* mu, void* codes
                                  bf16, st);
 }
 
-// Up to this many elements (BH Np D) the tensors share a launch, as in the FP4 quantizers.
+// Up to this many elements (BH Np D) the tensors share a launch, the FP4 quantizers'
+// line.  Forward, D = 128, in us, apart -> shared: 4 heads x 1024 40.5 -> 33.3, 64 x
+// 1024 (2^23) 70.2 -> 60.2, 32 x 4096 (2^24) 243 -> 237; backward 111 -> 95, 198 -> 181,
+// 959 -> 953.  (Here sharing still gains past it: 256 x 1024, 2^25, 193 -> 185 and
+// 673 -> 655; 512 x 1024, 2^26, 370 -> 364 and 1283 -> 1267.)
 constexpr long long I8_PREP_MAX_ELEMS = 1LL << 24;
 
 template <bool BWD>
