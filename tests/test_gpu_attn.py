@@ -330,16 +330,14 @@ def test_attn_with_and_without_kv_groups(N, D, bkv, causal, wg):
 
 @pytest.mark.parametrize("N", [129, 300, 520, 1100])
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("bkv", [64, 128, 256])
-@pytest.mark.parametrize("mode", ["plain", "causal", "wg256", "smooth_q", "smooth_q_causal"])
+@pytest.mark.parametrize("mode, bkv", [(m, b) for m in ("plain", "causal", "smooth_q", "smooth_q_causal")
+                                       for b in (64, 128, 256)] + [("wg256", 256)])  # the flag takes 256-key tiles
 def test_attn_bits_of_a_head_do_not_depend_on_the_number_of_heads(N, D, bkv, mode):
     """Two heads alone (two KV groups where there are two tiles to share, 64
     queries a workgroup) and 400 copies of them (one group, 128 or 256 queries)
     give the same bits, an odd number of tiles included; with smoothing Q, whose
     bias both paths add, also against the oracle.  16-bit outputs at N % 8 == 0."""
     torch = torch_dev()
-    if mode == "wg256" and bkv != 256:
-        pytest.skip("256-query workgroups take 256-key tiles")
     causal, sq = mode.endswith("causal"), mode.startswith("smooth_q")
     say("attn few and many heads N=%d D=%d bkv=%d %s" % (N, D, bkv, mode))
     in_dtype = N % 2

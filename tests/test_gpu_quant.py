@@ -124,3 +124,30 @@ def test_quant_work_split_ragged(fmt):
     q, k, v = wl.make_inputs(B, H, N, D, 1, seed=4090 + fmt, k_bias_var=4.0, outlier_frac=0.02)
     for role, x in ((0, q), (1, k), (2, v)):
         check_role(x, 1, role, fmt)
+
+
+@pytest.mark.parametrize("N", [129, 4097])
+@pytest.mark.parametrize("D", [64, 128])
+def test_quant_k_mean_at_any_float(N, D):
+    """K's mean lies at any 4-byte aligned address of the caller's: 2 chunks of
+    partial sums (added in the quantizer, which writes the mean) and 9 (a pass of
+    their own; the quantizer reads the mean back) give the same codes, scales and
+    mean at offsets of 0 to 3 floats, and write nothing beside the mean."""
+    torch = torch_dev()
+    say("quant k mean offset N=%d D=%d" % (N, D))
+    _, k, _ = wl.make_inputs(1, 3, N, D, 1, seed=77 + N + D, k_bias_var=4.0, outlier_frac=0.02)
+    x = to_dev(k, 1)
+    fmt = bd.SAGE_IN_BF16
+    codes, scales, mean = bd.sage_quant_fp4(x, bd.SAGE_ROLE_K)
+    ws = torch.empty(max(8, int(bd.lib().sage_quant_workspace_size(bd.SAGE_ROLE_K, 1, 3, N, D, fmt))),
+                     dtype=torch.uint8, device=x.device)
+    for off in range(4):
+        c, s = torch.full_like(codes, 0xAA), torch.full_like(scales, 0xAA)
+        buf = torch.full((3 * D + 8,), 12345.0, device=x.device)
+        at = buf[off:off + 3 * D]
+        rc = bd.lib().sage_quant_fp4(bd._ptr(x), bd.SAGE_ROLE_K, 1, 3, N, D, fmt, bd._ptr(c), bd._ptr(s), bd._ptr(at),
+                                     bd._ptr(ws), ws.numel(), bd._stream())
+        torch.cuda.synchronize()
+        assert rc == 0
+        assert torch.equal(c, codes) and torch.equal(s, scales) and torch.equal(at, mean.flatten())
+        assert bool((buf[:off] == 12345.0).all()) and bool((buf[off + 3 * D:] == 12345.0).all())
